@@ -32,14 +32,17 @@ int ensure_workspace(const egt_game* cg) {
   size_t elems = 0;
   for (int p = 0; p < 2; ++p)
     elems += 2 * (size_t)g->hp[p].n_seq * g->ld + (size_t)g->hp[p].n_nodes * g->ld;
-  elems += 16 + (size_t)kMaxTrees * kMaxPartials;
+  elems += kMaxPartials;
   void* blk = nullptr;
   hipError_t e = hipMalloc(&blk, elems * sizeof(double));
   if (e != hipSuccess) return fail(EGT_ENOMEM, std::string("hipMalloc (workspace): ") + hipGetErrorString(e));
   double* hs = nullptr;
-  e = hipHostMalloc((void**)&hs, 16 * sizeof(double), hipHostMallocDefault);
+  void* hs_dev = nullptr;  // the kernels write the saddle gap's partial sums there
+  e = hipHostMalloc((void**)&hs, 2 * (size_t)kMaxPartials * sizeof(double), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(&hs_dev, hs, 0);
   if (e != hipSuccess) {
     (void)hipFree(blk);
+    if (hs) (void)hipHostFree(hs);
     return fail(EGT_ENOMEM, std::string("hipHostMalloc (workspace): ") + hipGetErrorString(e));
   }
   double* cur = (double*)blk;
@@ -52,7 +55,8 @@ int ensure_workspace(const egt_game* cg) {
     cur += (size_t)g->hp[p].n_nodes * g->ld;
   }
   g->ws.scal = cur;
-  g->ws.hscal = hs;
+  g->ws.hpart = hs;
+  g->ws.hpart_dev = (double*)hs_dev;
   g->ws.block = blk;
   return EGT_OK;
 }
@@ -163,11 +167,7 @@ int egt_smoothed_br(const egt_game* g, int player, const double* grad, double mu
     const Workspace& w = g->ws;
     const Pass ps{player, grad, 1.0, nullptr, 0.0, mu, w.v[player], w.qb[player]};
     const Epilogue e{strat_out, nullptr, 0.0, nullptr};
-    EGT_HIP(launch_passes(g, &ps, 1, &e, value_out ? w.scal + 16 : nullptr, stream));
-    if (value_out) {
-      EGT_HIP(launch_sum_partials(g, w.scal + 16, 1, w.scal, stream));
-      EGT_HIP(hipMemcpyAsync(value_out, w.scal, sizeof(double), hipMemcpyDeviceToDevice, stream));
-    }
+    EGT_HIP(launch_value(g, ps, &e, w.scal, value_out, stream));
     return EGT_OK;
   });
 }
@@ -195,11 +195,7 @@ int egt_smoothed_br_mixed(const egt_game* g, int player, const float* grad, doub
     const Workspace& w = g->ws;
     const Pass ps{player, grad, 1.0, nullptr, 0.0, mu, w.v[player], w.qb[player]};
     const Epilogue e{strat_out, nullptr, 0.0, nullptr};
-    EGT_HIP(launch_passes(g, &ps, 1, &e, value_out ? w.scal + 16 : nullptr, stream, kF32));
-    if (value_out) {
-      EGT_HIP(launch_sum_partials(g, w.scal + 16, 1, w.scal, stream));
-      EGT_HIP(hipMemcpyAsync(value_out, w.scal, sizeof(double), hipMemcpyDeviceToDevice, stream));
-    }
+    EGT_HIP(launch_value(g, ps, &e, w.scal, value_out, stream, kF32));
     return EGT_OK;
   });
 }
@@ -212,9 +208,7 @@ int egt_best_response(const egt_game* g, int player, const double* grad, double*
     if (rc) return rc;
     const Workspace& w = g->ws;
     const Pass ps{player, grad, 1.0, nullptr, 0.0, 0.0, w.v[player], nullptr};
-    EGT_HIP(launch_passes(g, &ps, 1, nullptr, w.scal + 16, stream));
-    EGT_HIP(launch_sum_partials(g, w.scal + 16, 1, w.scal, stream));
-    EGT_HIP(hipMemcpyAsync(value_out, w.scal, sizeof(double), hipMemcpyDeviceToDevice, stream));
+    EGT_HIP(launch_value(g, ps, nullptr, w.scal, value_out, stream));
     return EGT_OK;
   });
 }
@@ -238,14 +232,16 @@ int egt_saddle_gap(const egt_game* g, const double* x, const double* y, double* 
     EGT_HIP(launch_gradient(g, 1, x, w.grad[1], stream));
     const Pass ps[2] = {{0, w.grad[0], 1.0, nullptr, 0.0, 0.0, w.v[0], nullptr},
                         {1, w.grad[1], -1.0, nullptr, 0.0, 0.0, w.v[1], nullptr}};
-    EGT_HIP(launch_passes(g, ps, 2, nullptr, w.scal + 16, stream));
-    EGT_HIP(launch_sum_partials(g, w.scal + 16, 2, w.scal, stream));
-    EGT_HIP(hipMemcpyAsync(w.hscal, w.scal, 2 * sizeof(double), hipMemcpyDeviceToHost, stream));
-    EGT_HIP(hipStreamSynchronize(stream));
+    // the partial sums go straight to pinned host memory and are added here, in
+    // the order launch_sum_partials adds them: no sum and copy launches to wait for
+    EGT_HIP(launch_passes(g, ps, 2, nullptr, w.hpart_dev, stream));
+    if ((rc = wait_for([&] { return hipStreamQuery(stream); }, [&] { return hipStreamSynchronize(stream); }))) return rc;
+    const int nb = n_partials(g);
+    const double v0 = sum_in_order(w.hpart, nb), v1 = sum_in_order(w.hpart + nb, nb);
     // gap = max_y x^T A y - min_x x^T A y = -BR_y(-A^T x) - BR_x(A y)
-    if (gap) *gap = -w.hscal[1] - w.hscal[0];
-    if (br_min_x) *br_min_x = w.hscal[0];
-    if (br_max_y) *br_max_y = -w.hscal[1];
+    if (gap) *gap = -v1 - v0;
+    if (br_min_x) *br_min_x = v0;
+    if (br_max_y) *br_max_y = -v1;
     return EGT_OK;
   });
 }

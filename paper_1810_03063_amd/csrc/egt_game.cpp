@@ -801,12 +801,12 @@ int free_game(egt_game* g) {
   if (!g) return EGT_OK;
   int st = EGT_OK;
   const bool dev_owned = (g->mem.base && g->owns_mem) || (g->mx.block && g->mx.owned);
-  if (dev_owned || g->ws.block || g->ws.hscal) {
+  if (dev_owned || g->ws.block || g->ws.hpart) {
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess && g->mem.base && g->owns_mem) e = hipFree(g->mem.base);
     if (e == hipSuccess && g->mx.block && g->mx.owned) e = hipFree(g->mx.block);
     if (e == hipSuccess && g->ws.block) e = hipFree(g->ws.block);
-    if (e == hipSuccess && g->ws.hscal) e = hipHostFree(g->ws.hscal);
+    if (e == hipSuccess && g->ws.hpart) e = hipHostFree(g->ws.hpart);
     if (e != hipSuccess) st = hip_fail(e, "free_game");
   }
   delete g;

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -245,7 +246,7 @@ struct GameOffsets {
 
 // Scratch of the single-operation entry points (egt_smoothed_br,
 // egt_best_response, egt_saddle_gap): per player a gradient, a q_bar and a
-// node-value buffer, plus device scalars.  Allocated on first use, owned by
+// node-value buffer, plus room for one tree's partial sums (scal).  Allocated on first use, owned by
 // the game.
 struct Workspace {
   void* block = nullptr;
@@ -253,7 +254,8 @@ struct Workspace {
   double* qb[2] = {};
   double* v[2] = {};
   double* scal = nullptr;
-  double* hscal = nullptr;  // pinned host mirror of scal
+  double* hpart = nullptr;  // pinned host memory for the saddle gap's partial sums, and its device address
+  double* hpart_dev = nullptr;
 };
 
 // Precision-form tables (built on first use): W in BF16 bits over the slot
@@ -325,6 +327,43 @@ size_t fused_lds_bytes(int hands, int cap_tab_bytes, int cap_nodes, int cap_seqs
 
 // out[k] = sum of the n_partials(g) partials of tree k, in order.
 hipError_t launch_sum_partials(const egt_game* g, const double* partial, int count, double* out, hipStream_t s);
+
+// One pass with its tree value in the device double *value_out (null: no
+// value); scratch holds n_partials(g) doubles.
+hipError_t launch_value(const egt_game* g, const Pass& p, const Epilogue* epi, double* scratch, double* value_out,
+                        hipStream_t s, Prec prec = kF64);
+
+// part[0] + ... + part[nb - 1] added in order from 0, the reads running ahead
+// of the chain of additions.
+__host__ __device__ inline double sum_in_order(const double* part, int nb) {
+  constexpr int kAhead = 16;
+  double s = 0.0;
+  int b = 0;
+  for (; b + kAhead <= nb; b += kAhead) {
+    double v[kAhead];
+    for (int u = 0; u < kAhead; ++u) v[u] = part[b + u];
+    for (int u = 0; u < kAhead; ++u) s += v[u];
+  }
+  for (; b < nb; ++b) s += part[b];
+  return s;
+}
+
+// Waits until `done` reports completion: polls for up to kSpinSeconds (a
+// blocking wait wakes up tens of microseconds late, which an iteration of
+// ~100 us cannot afford), then blocks, so that many concurrent solves do not
+// keep every host core busy.
+template <class Query, class Block>
+int wait_for(Query done, Block block) {
+  constexpr double kSpinSeconds = 200e-6;
+  const auto t0 = std::chrono::steady_clock::now();
+  hipError_t e;
+  while ((e = done()) == hipErrorNotReady &&
+         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() < kSpinSeconds) {
+  }
+  if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(e, "query");
+  EGT_HIP(block());
+  return EGT_OK;
+}
 
 // Top-down pass: q = product of q_bar along the sequence's chain.  Writes q to
 // q_out (may be null) and (1 - tau) x_prev + tau q to comb_out (may be null).

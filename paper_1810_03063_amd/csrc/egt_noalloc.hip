@@ -48,15 +48,18 @@ int scratch_for_device(int dev, void** out) {
 
 // out = {gap, br_max_y, br_min_x} from the two trees' root partials, each
 // tree's partials added in order from 0 (the order egt_saddle_gap uses), so
-// the two entry points agree bit for bit.
-__global__ __launch_bounds__(64) void gap_from_partials_kernel(const double* partial, int nb, double* out) {
+// the two entry points agree bit for bit; a wavefront per tree, the partials
+// loaded into LDS at once so that the chain of additions does not wait for
+// memory.
+__global__ __launch_bounds__(128) void gap_from_partials_kernel(const double* partial, int nb, double* out) {
+  __shared__ double part[2][kMaxPartials];
+  __shared__ double s[2];
+  const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int b = lane; b < nb; b += 64) part[k][b] = partial[(size_t)k * nb + b];
+  __syncthreads();
+  if (lane == 0) s[k] = sum_in_order(part[k], nb);
+  __syncthreads();
   if (threadIdx.x != 0) return;
-  double s[2];
-  for (int k = 0; k < 2; ++k) {
-    double v = 0.0;
-    for (int b = 0; b < nb; ++b) v += partial[(size_t)k * nb + b];
-    s[k] = v;
-  }
   // gap = max_y x^T A y - min_x x^T A y = -BR_y(-A^T x) - BR_x(A y)
   out[0] = -s[1] - s[0];
   out[1] = -s[1];
@@ -116,7 +119,7 @@ extern "C" int egt_saddle_gap_noalloc(const egt_game* g, const double* x, const 
   const Pass ps[2] = {{0, grad[0], 1.0, nullptr, 0.0, 0.0, V[0], nullptr},
                       {1, grad[1], -1.0, nullptr, 0.0, 0.0, V[1], nullptr}};
   EGT_HIP(launch_passes(g, ps, 2, nullptr, partial, stream));
-  hipLaunchKernelGGL(gap_from_partials_kernel, dim3(1), dim3(64), 0, stream, partial, n_partials(g), out3);
+  hipLaunchKernelGGL(gap_from_partials_kernel, dim3(1), dim3(128), 0, stream, partial, n_partials(g), out3);
   EGT_HIP(hipGetLastError());
   return EGT_OK;
 }

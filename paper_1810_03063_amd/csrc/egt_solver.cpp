@@ -145,23 +145,6 @@ int enqueue_values(egt_state* st, int trees, hipStream_t, const double* part = n
   return EGT_OK;
 }
 
-// Waits until `done` reports completion: polls for up to kSpinSeconds (a
-// blocking wait wakes up tens of microseconds late, which an iteration of
-// ~100 us cannot afford), then blocks, so that many concurrent solves do not
-// keep every host core busy.
-template <class Query, class Block>
-int wait_for(Query done, Block block) {
-  constexpr double kSpinSeconds = 200e-6;
-  const auto t0 = std::chrono::steady_clock::now();
-  hipError_t e;
-  while ((e = done()) == hipErrorNotReady &&
-         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() < kSpinSeconds) {
-  }
-  if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(e, "query");
-  EGT_TRY(block());
-  return EGT_OK;
-}
-
 // Adds each pending tree's partials in order into hscal[k] (the launch has
 // completed).
 int read_values(egt_state* st) {
@@ -169,8 +152,7 @@ int read_values(egt_state* st) {
   const int trees = st->pending_trees;
   st->pending_trees = 0;
   for (int k = 0; k < trees; ++k) {
-    double v = 0.0;
-    for (int b = 0; b < nb; ++b) v += st->pending_part[k * nb + b];
+    const double v = sum_in_order(st->pending_part + (size_t)k * nb, nb);
     if (!std::isfinite(v)) return fail(EGT_ENUMERIC, "non-finite value in the EGT driver");
     st->hscal[k] = v;
   }
