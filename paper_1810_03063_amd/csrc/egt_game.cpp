@@ -273,7 +273,7 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
     for (int i = hp.level_begin[l]; i < hp.level_begin[l + 1]; ++i)
       hp.level_max_act[l] = std::max(hp.level_max_act[l], hp.node_nact[i]);
   }
-  // table image of the single-launch pass
+  // table image, sequence and node records
   const FusedTabLayout L = fused_tab_layout(nn, ns);
   hp.fused_tab.assign((size_t)L.bytes, 0);
   std::vector<int> vslot(nn, -1);
@@ -288,6 +288,15 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
   }
   std::memcpy(img + L.cbeg, hp.child_begin.data(), sizeof(int) * (size_t)(ns + 1));
   if (ns) std::memcpy(img + L.spar, hp.seq_parent.data(), sizeof(int) * (size_t)ns);
+  hp.seq_rec.resize(ns);
+  hp.node_rec.resize(nn);
+  for (int i = 0; i < nn; ++i) {
+    const int lev = hp.node_level[i] - 1;
+    hp.node_rec[i] = NodeRec{hp.node_first_seq[i], hp.node_nact[i], vslot[i], lev, hp.node_beta[i], hp.node_logn[i]};
+    for (int s = hp.node_first_seq[i]; s < hp.node_first_seq[i] + hp.node_nact[i]; ++s)
+      hp.seq_rec[s] = SeqRec{hp.seq_parent[s], hp.child_begin[s], hp.child_begin[s + 1] - hp.child_begin[s], vslot[i],
+                             lev, {0, 0, 0}};
+  }
   return EGT_OK;
 }
 
@@ -341,6 +350,8 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
     po[p].roots = add(hp.roots.data(), hp.roots.size() * sizeof(int));
     po[p].belief = add(b[p].data(), b[p].size() * sizeof(double));
     po[p].ftab = add(hp.fused_tab.data(), hp.fused_tab.size());
+    po[p].srec = add(hp.seq_rec.data(), hp.seq_rec.size() * sizeof(SeqRec));
+    po[p].nrec = add(hp.node_rec.data(), hp.node_rec.size() * sizeof(NodeRec));
     po[p].trec = add(hp.term_rec.data(), hp.term_rec.size() * sizeof(TermRec));
     po[p].anc = add(hp.anc.data(), hp.anc.size() * sizeof(int));
     po[p].titems = add(hp.term_items.data(), hp.term_items.size() * sizeof(TermItem));
@@ -369,6 +380,7 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   EGT_HIP(hipDeviceGetAttribute(&g->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device));
   if (g->lds_per_block < 64 * 1024) g->lds_per_block = 64 * 1024;
   if (g->lds_per_cu < g->lds_per_block) g->lds_per_cu = g->lds_per_block;
+  g->fused_passes = fits_fused(g);
   return EGT_OK;
 }
 
@@ -501,12 +513,9 @@ int build_game_host(const egt_game_desc* d, egt_game** out) {
         hp.term_items.push_back(TermItem{{hp.term_rec[(size_t)pending * stride], none}, {pending, -1}, {0, 0}});
     }
   }
-  // enough 4-hand blocks to spread over the chip; 16-hand blocks for tiny hand counts
-  g->fused_hands = g->ld >= 512 ? 4 : 16;
-  g->fused_passes =
-      fused_lds_bytes(g->fused_hands, (int)std::max(g->hp[0].fused_tab.size(), g->hp[1].fused_tab.size()),
-                      std::max(g->hp[0].n_nodes, g->hp[1].n_nodes),
-                      std::max(g->hp[0].n_seq, g->hp[1].n_seq)) <= kFusedLdsLimit;
+  // enough 4-hand blocks to spread over the chip; 16-hand blocks for small hand
+  // counts, unless a thread would hold more than four (sequence, hand) pairs
+  g->fused_hands = g->ld < 512 && 16 * std::max(g->hp[0].n_seq, g->hp[1].n_seq) <= 4 * kFusedThreads ? 16 : 4;
   for (const RawTerminal& t : en.terms) (t.kind == 0 ? g->n_fold : g->n_show)++;
   for (int p = 0; p < 2; ++p)
     for (double b : g->hp[p].node_beta) g->max_beta = std::max(g->max_beta, b);
@@ -678,11 +687,7 @@ int build_general_host(const egt_general_desc* d, egt_game** out) {
       hp.sp_ptr[r + 1] += hp.sp_ptr[r];
     }
   }
-  g->fused_hands = 16;
-  g->fused_passes =
-      fused_lds_bytes(g->fused_hands, (int)std::max(g->hp[0].fused_tab.size(), g->hp[1].fused_tab.size()),
-                      std::max(g->hp[0].n_nodes, g->hp[1].n_nodes),
-                      std::max(g->hp[0].n_seq, g->hp[1].n_seq)) <= kFusedLdsLimit;
+  g->fused_hands = 1;
   for (int p = 0; p < 2; ++p)
     for (double b : g->hp[p].node_beta) g->max_beta = std::max(g->max_beta, b);
   g->perm = {0};
@@ -736,7 +741,8 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.roots = (const int*)at(po[p].roots);
     dp.belief = (const double*)at(po[p].belief);
     dp.fused_tab = at(po[p].ftab);
-    dp.fused_tab16 = (int)(hp.fused_tab.size() / 16);
+    dp.seq_rec = (const SeqRec*)at(po[p].srec);
+    dp.node_rec = (const NodeRec*)at(po[p].nrec);
     dp.term_rec = (const TermRec*)at(po[p].trec);
     dp.anc = (const int*)at(po[p].anc);
     dp.term_stride = std::max(1, hp.max_terms_per_seq);

@@ -16,10 +16,23 @@ namespace egt {
 constexpr int kMaxActions = 16;  // actions per decision node
 constexpr int kMaxDepth = 16;    // sequences on a root-to-leaf chain of one player (and levels)
 constexpr int kMaxTrees = 4;     // trees evaluated by one bottom-up launch
-constexpr size_t kFusedLdsLimit = 64 * 1024;  // LDS budget of one single-launch pass block
+constexpr int kFusedThreads = 512;  // threads of one single-launch pass block, at most
+constexpr int kFusedTasks = 8;      // (sequence, hand) pairs of one of its threads, at most
 
-// Table image of one player's treeplex for the single-launch pass, staged
-// into LDS verbatim with 16-byte copies:
+// One sequence and one node as the single-launch passes read them: the
+// sequence's parent (-1 at a root), the value slots [c0, c0 + n_child) of its
+// child nodes, its own node's value slot and level (0 = lowest); the node's
+// first sequence, number of actions, value slot, level, dilation weight and
+// log(number of actions).
+struct SeqRec {
+  int parent, c0, n_child, slot, level, pad[3];
+};
+struct NodeRec {
+  int first, na, slot, level;
+  double beta, logn;
+};
+
+// Table image of one player's treeplex for the level path:
 //   rec  int4[N]    {first sequence, number of actions, value slot, 0}
 //   prm  double4[N] {beta, 1 / beta, log(number of actions), 0}
 //   cbeg int[S + 1] child-slot range of each sequence (CSR over child nodes)
@@ -99,13 +112,14 @@ struct DPlayer {
   const double* term_coef;     // player 2's chips at the terminal (times the sign at a showdown)
   const int* roots;            // [n_roots] root node ids
   const double* belief;        // [ld] this player's prior in slot order, 0 in the padding
-  const void* fused_tab;       // the single-launch pass's table image (FusedTabLayout), 16-byte units
+  const void* fused_tab;       // the table image (FusedTabLayout)
+  const SeqRec* seq_rec;       // [n_seq]
+  const NodeRec* node_rec;     // [n_nodes]
   const int* anc;              // [n_seq][kMaxDepth] sequences on the path root -> s (s last), -1 after
   const TermRec* term_rec;     // [n_seq][term_stride] terminals of each sequence, padded with kind -1
   int term_stride;             // max terminals per sequence (>= 1)
   const TermItem* term_items;  // [n_items] when every sequence has at most two terminals, else null
   int n_items;
-  int fused_tab16;             // its size in 16-byte units
   const int* seq_nact;         // [n_seq] number of actions of the sequence's decision node
   // General games: this player's rows of the payoff operator in CSR (A for
   // player 1, A^T for player 2), columns in the opponent's library order.
@@ -218,7 +232,9 @@ struct HostPlayer {
   std::vector<int> term_begin, term_opp, term_kind;
   std::vector<double> term_coef;
   std::vector<int> roots;
-  std::vector<unsigned char> fused_tab;  // table image of the single-launch pass
+  std::vector<unsigned char> fused_tab;  // table image (FusedTabLayout)
+  std::vector<SeqRec> seq_rec;
+  std::vector<NodeRec> node_rec;
   std::vector<TermRec> term_rec;         // [n_seq][max(1, max_terms_per_seq)]
   std::vector<TermItem> term_items;      // work items of the looping product kernel (at most two terminals each)
   std::vector<int> anc;                  // [n_seq][kMaxDepth]
@@ -239,7 +255,7 @@ struct DeviceBlock {  // one device allocation holding many tables
 struct GameOffsets {
   struct Player {
     size_t first, nact, beta, logn, spar, cbeg, child, tbeg, topp, tkind, tcoef, roots, belief, ftab, trec, anc,
-        titems, snact, sptr, scol, sval;
+        titems, snact, sptr, scol, sval, srec, nrec;
   } p[2];
   size_t cbeg, htab, hpos;
 };
@@ -297,7 +313,7 @@ struct egt_game {
   double max_beta = 0;
   bool general = false;       // a general game (egt_build_general_game): CSR products, one live slot
   bool fused_passes = false;  // both treeplexes' tables fit one block's LDS: single-launch passes
-  int fused_hands = 4;        // hands per block of the single-launch pass (4 or 16)
+  int fused_hands = 4;        // hands per block of the single-launch pass (4 or 16; 1 in a general game)
 };
 
 namespace egt {
@@ -323,7 +339,10 @@ hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, d
 hipError_t launch_passes(const egt_game* g, const Pass* p, int count, const Epilogue* epi, double* partial,
                          hipStream_t s, Prec prec = kF64);
 int n_partials(const egt_game* g);
-size_t fused_lds_bytes(int hands, int cap_tab_bytes, int cap_nodes, int cap_seqs);
+// LDS of one fused-pass block (dual: with the best responses beside).
+size_t fused_lds_bytes(int hands, int cap_nodes, int cap_seqs, bool dual);
+// Whether a game's smoothed best responses take the fused pass.
+bool fits_fused(const egt_game* g);
 
 // out[k] = sum of the n_partials(g) partials of tree k, in order.
 hipError_t launch_sum_partials(const egt_game* g, const double* partial, int count, double* out, hipStream_t s);

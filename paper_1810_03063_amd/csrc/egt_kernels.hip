@@ -30,7 +30,6 @@ namespace {
 
 constexpr int kPassThreads = 64;       // per-level pass: one wavefront per (node, 64 hands)
 constexpr int kInternalWaves = 8;       // level path: wavefronts per node block (4 blocks fill a CU's 32 wave slots)
-constexpr int kFusedSlots = 64;        // fused pass: node slots per block (x HB hands per slot)
 
 // The per-information-set arithmetic of Section 4's smoothed best response in
 // the association of its formulas, every operation rounded on its own (the
@@ -65,6 +64,41 @@ __device__ inline double qbar(double w, double sum, double rsum) {
 __device__ inline double lse_value(double m, double temp, double sum, double logn) {
   return (m - temp * log(sum)) + temp * logn;
 }
+
+// The fused pass's FP64 weights, with temp's reciprocal known before the shift
+// is: for y = 1/temp rounded, q0 = x y is within two ulps of x/temp, and two
+// corrections by the exact remainder, q <- q + (x - temp q) y, give the rounded
+// quotient (Markstein; the second starts within one ulp) -- 5 dependent
+// operations of 5 cycles where a division takes 106 cycles of a chain that
+// nothing else runs beside.  Exact remainders need temp in [2^-900, 2^900]
+// (temp_inverse is 0 outside, and the wavefront divides) and x above some
+// 2^-960, below which the quotient's exponential is 1 whatever its last bit.  A
+// quotient below -1e4 (an overflowed one has no remainder) is left as q0: its
+// exponential is 0.  (On the lowest level of the level path, which is bound by
+// memory latency, the same exchange gained nothing: 31.3 to 32.0 us at 5938
+// sequences.)
+template <class TG>
+__device__ inline double temp_inverse(double temp) {
+  return std::is_same<TG, float>::value || (temp >= 0x1p-900 && temp <= 0x1p900) ? 1.0 / temp : 0.0;
+}
+template <class TG>
+__device__ inline double lse_weight_by_inverse(double m, double g, double temp, double itemp) {
+  if constexpr (std::is_same<TG, float>::value) {
+    return lse_weight<TG>(m, g, temp, itemp);
+  } else {
+    const double x = m - g;
+    double q;
+    if (__any(itemp == 0.0)) {
+      q = x / temp;
+    } else {
+      const double q0 = x * itemp;
+      q = __builtin_fma(__builtin_fma(-temp, q0, x), itemp, q0);
+      q = __builtin_fma(__builtin_fma(-temp, q, x), itemp, q);
+      q = q0 < -1e4 ? q0 : q;
+    }
+    return exp(q);
+  }
+}
 // cA a + cB b (the mixed gradient of the prox, or a single scaled gradient).
 __device__ inline double lin2(double cA, double a, double cB, double b) { return cA * a + cB * b; }
 
@@ -83,34 +117,60 @@ __device__ inline double lin2(double cA, double a, double cB, double b) { return
 // ---------------------------------------------------------------------------
 
 // ---------------------------------------------------------------------------
-// Fused pass for trees whose tables fit in LDS.  Block = (tree k, HB hands),
-// 64 node slots x HB hands.
-//   1. Stage in LDS, all loads in flight together: the player's table image
-//      (FusedTabLayout), the combined gradient cA gA + cB gB of the block's
-//      hands and, for the epilogue, x_prev.
-//   2. Bottom-up, one level at a time (a block barrier after each phase):
-//      (a) sequence phase (levels above the lowest): g~_s = g_s + the values
-//          of the child nodes of s, read from their contiguous value slots;
-//      (b) node phase: the smoothed (or plain) best response at each
-//          (node, hand) from the g~ of its actions, writing the node value to
-//          its slot and q_bar.  Tasks are (sequence, hand) / (node, hand)
-//          pairs spread over all threads.
+// Fused pass for trees that fit in LDS: block = (tree k, HB hands).
+//
+// A launch moves a few MB; its time is the chain of dependent steps of each
+// level and the instructions around them: index arithmetic, loops over a node's
+// actions, look-ups of tables (cycle stamps of a form that kept the tables in
+// LDS, on the 223-sequence tree: of 24,000 cycles a block, 14,000 in three
+// levels whose own chain -- minimum, division, exponential, logarithm -- takes
+// about 1,000 each).  So a thread keeps the records of its (sequence, hand)
+// pairs and of its node task in registers, and whatever the next level does not
+// wait for is left until the levels are done.  223 sequences x 1081 hands, one
+// tree: 14.3 -> 11.1 us; with the best responses beside, two trees: 17.9 ->
+// 15.1 us; Leduc hold'em, which fits since a block may hold one hand: 20.4 ->
+// 10.7 us for one tree against a launch per level.
+//   1. Staging: every thread loads the records of its K sequences and of its
+//      node and, at the same time, the combined gradient cA gA + cB gB and the
+//      epilogue's x_prev; the gradient goes to LDS.
+//   2. Bottom-up, a block barrier after each phase of a level:
+//      (a) sequences above the lowest level: g~_s = g_s + the values of the
+//          child nodes of s, read from their contiguous value slots;
+//      (b) nodes: minimum, weights (to LDS), their sum (to LDS) and the node
+//          value, by two lanes per (node, hand) on the lowest level (its nodes
+//          have few actions, and the block's 512 threads are then one task
+//          each on a tree of 63 such nodes) and by four above it.
 //   3. The block's partial root sum (the tree value is a sum over (root, hand)).
-//   4. Top-down, level by level from the roots: q[s] = q[parent] * q_bar[s]
-//      in place, then the epilogue (1 - tau) x_prev + tau q.  Slots h >= n
-//      (the row padding) are written 0.
+//   4. q_bar = weight / sum, one sequence per thread, then top-down, level by
+//      level from the roots, q[s] = q[parent] * q_bar[s], and the epilogue
+//      (1 - tau) x_prev + tau q.  Slots h >= n (the row padding) are written 0.
+// The additions, minima and products are those of one thread evaluating a node
+// by itself, in its order, so the bits are too.
 //
 // The grid is one-dimensional over (tree, hand block) and spread so that each
 // XCD (workgroups go round-robin over the 8 XCDs) gets a contiguous range of
 // hand blocks: neighbouring blocks share cache lines of every row, and those
 // then meet in one L2.
 // ---------------------------------------------------------------------------
+struct FusedTree {
+  const SeqRec* seq;
+  const NodeRec* node;
+  const void* gA;
+  const void* gB;
+  const void* x_prev;
+  void* q_out;
+  void* comb_out;
+  void* g_out;
+  void* qb_out;
+  double cA, cB, mu, tau, g_scale;
+  int S, N, C, n_roots, n_levels, n_leaf, dual;  // n_leaf: nodes of the lowest level
+};
+
 struct FusedArgs {
-  PassSet ps;
-  Epilogue epi[kMaxTrees];
-  double* partial;  // [count][n_hblocks] or null (device or pinned host memory)
-  int cap_tab, cap_nodes, cap_seqs;
-  int n_hblocks;  // hand blocks per tree (ld / HB)
+  FusedTree t[kMaxTrees];
+  double* partial;  // [trees (and dual trees)][n_hblocks] or null (device or pinned host memory)
+  int count, n, ld, n_hblocks;  // hand blocks per tree
+  int cap_nodes, cap_seqs;
 };
 
 // Bijection of [0, total): workgroup L (on XCD L % 8) -> position, with each
@@ -121,245 +181,270 @@ __device__ inline int xcd_spread(int L, int total) {
   return x * q + min(x, r) + j;
 }
 
-// One (node, hand) task of the node phase: g~ of the node's actions in Gl,
-// value to the node's slot in Vs, q_bar to Ql (smoothed, want_q).  Every
-// action's g~ is read up front (indices clamped into the node), so the reads
-// overlap.  temp = mu beta_v.
-template <class TG, int HB>
-__device__ __forceinline__ void fused_node(const int4* rec, const double2* prm, const double* Gl, double* Ql,
-                                           double* Vs, int v, int hl, double mu, bool want_q) {
-  const int4 r = rec[v];
-  const int s0 = r.x, na = r.y;
-  double g[kMaxActions];
-#pragma unroll
-  for (int k = 0; k < kMaxActions; ++k) g[k] = Gl[(s0 + min(k, na - 1)) * HB + hl];
-  double m = g[0];
-#pragma unroll
-  for (int k = 1; k < kMaxActions; ++k)
-    if (k < na) m = fmin(m, g[k]);
-  if (!(mu > 0.0)) {
-    Vs[r.z * HB + hl] = m;
-    return;
-  }
-  const double2 p0 = prm[2 * v], p1 = prm[2 * v + 1];  // {beta, 1 / beta}, {log n_v, 0}
-  const double temp = mu * p0.x, itemp = inv_or_zero<TG>(temp);
-  double sum = 0.0;
-#pragma unroll
-  for (int k = 0; k < kMaxActions; ++k) {
-    if (k < na) {
-      g[k] = lse_weight<TG>(m, g[k], temp, itemp);
-      sum += g[k];
-    }
-  }
-  Vs[r.z * HB + hl] = lse_value(m, temp, sum, p1.x);
-  if (want_q) {
-    const double rs = inv_or_zero<TG>(sum);
-#pragma unroll
-    for (int k = 0; k < kMaxActions; ++k)
-      if (k < na) Ql[(s0 + k) * HB + hl] = (double)(TG)qbar<TG>(g[k], sum, rs);
-  }
+// A double moved within every aligned quad of lanes (DPP quad permute).
+template <int CTRL>
+__device__ inline double quad_move(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-template <int HB, class TG>
-__global__ __launch_bounds__(kFusedSlots * HB) void sbr_fused_kernel(FusedArgs a) {
-  constexpr int kThreads = kFusedSlots * HB;
-  constexpr int kU = 4;   // gradient loads in flight per thread and batch
-  constexpr int kTU = 2;  // table loads per thread in the first batch
-  extern __shared__ __align__(16) unsigned char fused_lds[];
+// x + p[0] + p[HB] + ... (cnt > 0 entries, added in order).  The last run reads
+// up to three entries past the end; the arrays leave room for that.
+template <int HB>
+__device__ __forceinline__ double add_run(double x, const double* p, int cnt) {
+  for (int c = 0; c < cnt; c += 4, p += 4 * HB) {
+    const double v0 = p[0], v1 = p[HB], v2 = p[2 * HB], v3 = p[3 * HB];
+    x += v0;
+    if (c + 1 < cnt) x += v1;
+    if (c + 2 < cnt) x += v2;
+    if (c + 3 < cnt) x += v3;
+  }
+  return x;
+}
+
+// One (node, hand) task of the node phase by 2 or (quad) 4 adjacent lanes, b the
+// lane's place: g~ of the node's actions at G, lane b taking actions b, b + 2 or
+// b + 4, ...; the minimum crosses the lanes by DPP.
+template <int HB>
+__device__ __forceinline__ double lanes_min(const double* G, int na, int b, bool quad) {
+  const int step = quad ? 4 : 2;
+  double m = G[min(b, na - 1) * HB];
+  for (int a = b + step; a < na; a += step) m = fmin(m, G[a * HB]);
+  m = fmin(m, quad_move<0xb1>(m));             // lanes 1 0 3 2
+  if (quad) m = fmin(m, quad_move<0x4e>(m));  // lanes 2 3 0 1
+  return m;
+}
+
+// Smoothed: weights to W, their sum (every lane adds them in action order, the
+// lanes' weights by DPP) and the node value returned.
+template <class TG, int HB>
+__device__ __forceinline__ double lanes_node(const double* G, double* W, int na, int b, bool quad, double temp,
+                                             double itemp, double logn, double* sum_out) {
+  const double m = lanes_min<HB>(G, na, b, quad);
+  const int step = quad ? 4 : 2;
+  double sum = 0.0;
+#pragma unroll 1
+  for (int a = 0; a < na; a += step) {
+    const int own = a + b;
+    const double w = lse_weight_by_inverse<TG>(m, G[min(own, na - 1) * HB], temp, itemp);
+    if (own < na) W[own * HB] = w;
+    if (quad) {
+      const double w0 = quad_move<0x00>(w), w1 = quad_move<0x55>(w), w2 = quad_move<0xaa>(w), w3 = quad_move<0xff>(w);
+      sum += w0;
+      if (a + 1 < na) sum += w1;
+      if (a + 2 < na) sum += w2;
+      if (a + 3 < na) sum += w3;
+    } else {
+      const double w0 = quad_move<0xa0>(w), w1 = quad_move<0xf5>(w);  // lanes 0 0 2 2, 1 1 3 3
+      sum += w0;
+      if (a + 1 < na) sum += w1;
+    }
+  }
+  *sum_out = sum;
+  return lse_value(m, temp, sum, logn);
+}
+
+constexpr int kFusedPad = 16;  // entries past the end of an LDS array that a run may read
+
+template <int HB, int K, class TG>
+__global__ __launch_bounds__(kFusedThreads, K <= 2 ? 8 : K <= 4 ? 5 : 2) void sbr_fused_kernel(FusedArgs a) {
+  extern __shared__ __align__(16) double fused_lds[];
   const int nb = a.n_hblocks;
   const int P = xcd_spread((int)blockIdx.x, (int)gridDim.x);
   const int k = P / nb, hblk = P % nb;
-  const TreePass& t = a.ps.t[k];
-  const Epilogue& e = a.epi[k];
-  const int N = t.P.n_nodes, S = t.P.n_seq;
-  const FusedTabLayout L = fused_tab_layout(N, S);
-  const int4* rec = (const int4*)(fused_lds + L.rec);
-  const double2* prm = (const double2*)(fused_lds + L.prm);
-  const int* cbeg = (const int*)(fused_lds + L.cbeg);
-  const int* spar = (const int*)(fused_lds + L.spar);
-  double* Gl = (double*)(fused_lds + a.cap_tab);  // [cap_seqs][HB] gradient, then g~
-  double* Ql = Gl + (size_t)a.cap_seqs * HB;      // [cap_seqs][HB] q_bar, then q
-  double* Xl = Ql + (size_t)a.cap_seqs * HB;      // [cap_seqs][HB] x_prev of the epilogue
-  double* Vs = Xl + (size_t)a.cap_seqs * HB;      // [cap_nodes][HB] node values by slot
-  // a dual tree (VB; every tree of the launch is then dual) also takes the
-  // best response to the same gradient: its g~ and node values beside
-  const bool dual = t.VB != nullptr && t.mu > 0.0;
-  double* GBl = Vs + (size_t)a.cap_nodes * HB;  // [cap_seqs][HB] dual: gradient, then the best response's g~
-  double* VBs = GBl + (size_t)a.cap_seqs * HB;  // [cap_nodes][HB] dual: best-response node values
-  const int tid = threadIdx.x;
-  const int h0 = hblk * HB, n = a.ps.n;
-  const size_t ld = a.ps.ld;
-  const int SH = S * HB;
-
-  // 1. staging
-  const uint4* tab = (const uint4*)t.P.fused_tab;
-  uint4* tl = (uint4*)fused_lds;
-  const int T16 = t.P.fused_tab16;
+  const FusedTree& t = a.t[k];
+  const int S = t.S, N = t.N, n = a.n, n_levels = t.n_levels, ld = a.ld;
+  const double mu = t.mu;
+  const bool smooth = mu > 0.0;
+  // a dual tree (every tree of the launch is then dual) also takes the best
+  // response to the same gradient: its g~ and node values beside
+  const bool dual = t.dual != 0;
+  const int sl = (a.cap_seqs + kFusedPad) * HB, nl = (a.cap_nodes + kFusedPad) * HB;
+  double* Gl = fused_lds;  // [seqs][HB] gradient, then g~
+  double* Wl = Gl + sl;    // [seqs][HB] weights, then q_bar and q
+  double* Vs = Wl + sl;    // [nodes][HB] node values by slot
+  double* Sl = Vs + nl;    // [nodes][HB] weight sums by slot
+  double* GBl = Sl + nl;   // [seqs][HB] dual: gradient, then the best response's g~
+  double* VBs = GBl + sl;  // [nodes][HB] dual: best-response node values
+  const int tid = threadIdx.x, T = blockDim.x;
+  const int h0 = hblk * HB;
   const TG* gA = (const TG*)t.gA;
   const TG* gB = (const TG*)t.gB;
-  const TG* x_prev = (const TG*)e.x_prev;
-  const bool want_x = e.comb_out != nullptr;
-  TG* g_out = (TG*)e.g_out;
-  uint4 tb[kTU];
+  const TG* x_prev = (const TG*)t.x_prev;
+  TG* g_out = (TG*)t.g_out;
+  TG* q_out = (TG*)t.q_out;
+  TG* comb_out = (TG*)t.comb_out;
+  TG* qb_out = (TG*)t.qb_out;
+  const bool want_q = (q_out || comb_out || qb_out) && smooth;
+
+  // 1. this thread's (sequence, hand) pairs j = u T + tid, as LDS indices
+  // packed in pairs (a block has at most kFusedTasks * kFusedThreads of them)
+  constexpr unsigned kNone = 0xffffu;
+  unsigned child[K];     // first child's value slot, number of children
+  unsigned par_slot[K];  // parent (kNone at a root), own node's slot
+  int lev[K];            // level, -1: no pair here
+  double vx[K];
+  double va[K], vb[K];
 #pragma unroll
-  for (int u = 0; u < kTU; ++u) {
-    const int i = u * kThreads + tid;
-    tb[u] = i < T16 ? tab[i] : make_uint4(0u, 0u, 0u, 0u);
-  }
-  for (int base = 0; base < SH; base += kThreads * kU) {
-    double va[kU], vb[kU], vx[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int i = base + u * kThreads + tid;
-      const int hh = h0 + i % HB;
-      va[u] = vb[u] = vx[u] = 0.0;
-      if (i < SH && hh < n) {
-        const size_t idx = (size_t)(i / HB) * ld + hh;
-        va[u] = (double)gA[idx];
-        if (gB) vb[u] = (double)gB[idx];
-        if (want_x) vx[u] = (double)x_prev[idx];
-      }
-    }
-    if (base == 0) {
-#pragma unroll
-      for (int u = 0; u < kTU; ++u) {
-        const int i = u * kThreads + tid;
-        if (i < T16) tl[i] = tb[u];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int i = base + u * kThreads + tid;
-      if (i < SH) {
-        const double x = gB ? lin2(t.cA, va[u], t.cB, vb[u]) : t.cA * va[u];
-        if (dual) GBl[i] = x;
-        if (want_x) Xl[i] = vx[u];
-        if (g_out) {
-          g_out[(size_t)(i / HB) * ld + h0 + i % HB] = (TG)(x * e.g_scale);  // 0 in the padding
-          Gl[i] = (double)(TG)x;  // continue with the stored gradient (g_scale = +-1)
-        } else {
-          Gl[i] = x;
-        }
-      }
+  for (int u = 0; u < K; ++u) {
+    const int j = u * T + tid, s = j / HB, hl = j % HB, h = h0 + hl;
+    va[u] = vb[u] = vx[u] = 0.0;
+    child[u] = par_slot[u] = 0u;
+    lev[u] = -1;
+    if (s < S && h < n) {
+      const size_t idx = (size_t)s * ld + h;
+      const SeqRec r = t.seq[s];
+      va[u] = (double)gA[idx];
+      if (gB) vb[u] = (double)gB[idx];
+      if (comb_out) vx[u] = (double)x_prev[idx];
+      child[u] = (unsigned)(r.c0 * HB + hl) | ((unsigned)r.n_child << 16);
+      par_slot[u] = (r.parent >= 0 ? (unsigned)(r.parent * HB + hl) : kNone) | ((unsigned)(r.slot * HB + hl) << 16);
+      lev[u] = r.level;
     }
   }
-  if (SH == 0) {
+  // Node tasks, numbered through: two per (node, hand) of the lowest level, then
+  // four per (node, hand) of the others, where there are fewer.  The thread's
+  // first one stays in registers; a tree with more tasks than threads reads the
+  // others' records when their level comes.
+  const int n_leaf = t.n_leaf, leaf_tasks = n_leaf * HB * 2, quad0 = (leaf_tasks + 3) & ~3;
+  const int n_tasks = quad0 + (N - n_leaf) * HB * 4;
+  struct Task {
+    int na_level, at_slot;  // level -1: none here; LDS indices
+    double temp, itemp, logn;
+  };
+  auto task_of = [&](int q) {
+    const bool quad = q >= quad0;
+    const int i = quad ? (q - quad0) / 4 : q / 2, v = (quad ? n_leaf : 0) + i / HB, hl = i % HB;
+    Task d{1 | (-1 << 8), 0, 1.0, 1.0, 0.0};
+    if ((quad ? q < n_tasks : q < leaf_tasks) && h0 + hl < n) {
+      const NodeRec r = t.node[v];
+      const double temp = mu * r.beta;
+      d = Task{r.na | (r.level << 8), (r.first * HB + hl) | ((r.slot * HB + hl) << 16), temp,
+               smooth ? temp_inverse<TG>(temp) : 0.0, r.logn};
+    }
+    return d;
+  };
+  const Task own = task_of(tid);
 #pragma unroll
-    for (int u = 0; u < kTU; ++u) {
-      const int i = u * kThreads + tid;
-      if (i < T16) tl[i] = tb[u];
+  for (int u = 0; u < K; ++u) {
+    const int j = u * T + tid, s = j / HB;
+    if (s < S) {
+      double x = gB ? lin2(t.cA, va[u], t.cB, vb[u]) : t.cA * va[u];
+      if (dual) GBl[j] = x;
+      if (g_out) {
+        g_out[(size_t)s * ld + h0 + j % HB] = (TG)(x * t.g_scale);  // 0 in the padding
+        x = (double)(TG)x;  // continue with the stored gradient (g_scale = +-1)
+      }
+      Gl[j] = x;
     }
   }
-  for (int i = kTU * kThreads + tid; i < T16; i += kThreads) tl[i] = tab[i];
   __syncthreads();
 
   // 2. bottom-up
-  const bool want_q = (e.q_out || e.comb_out || e.qb_out) && t.mu > 0.0;
-  const double mu = t.mu;
-  for (int l = 0; l < t.n_levels; ++l) {
+  auto run_task = [&](const Task& d, bool quad, int b) {
+    const int na = d.na_level & 0xff, at = d.at_slot & 0xffff, slot = (int)((unsigned)d.at_slot >> 16);
+    if (dual || !smooth) {
+      const double m = lanes_min<HB>((dual ? GBl : Gl) + at, na, b, quad);
+      if (b == 0) (dual ? VBs : Vs)[slot] = m;
+      if (!smooth) return;
+    }
+    double sum;
+    const double v = lanes_node<TG, HB>(Gl + at, Wl + at, na, b, quad, d.temp, d.itemp, d.logn, &sum);
+    if (b == 0) {
+      Vs[slot] = v;
+      Sl[slot] = sum;
+    }
+  };
+  for (int l = 0; l < n_levels; ++l) {
     if (l > 0) {
-      const int sb0 = t.seq_level_begin[l], cnt = (t.seq_level_begin[l + 1] - sb0) * HB;
-      for (int i = tid; i < cnt; i += kThreads) {
-        const int s = sb0 + i / HB, hl = i % HB;
-        const int c0 = cbeg[s], c1 = cbeg[s + 1];
-        if (h0 + hl >= n || c0 == c1) continue;
-        double x = Gl[s * HB + hl];
-        int c = c0;
-        for (; c + 4 <= c1; c += 4) {
-          const double v0 = Vs[c * HB + hl], v1 = Vs[(c + 1) * HB + hl];
-          const double v2 = Vs[(c + 2) * HB + hl], v3 = Vs[(c + 3) * HB + hl];
-          x += v0;
-          x += v1;
-          x += v2;
-          x += v3;
-        }
-        for (; c < c1; ++c) x += Vs[c * HB + hl];
-        Gl[s * HB + hl] = x;
-        if (dual) {  // the same additions on the best-response values
-          double xb = GBl[s * HB + hl];
-          int cb = c0;
-          for (; cb + 4 <= c1; cb += 4) {
-            const double v0 = VBs[cb * HB + hl], v1 = VBs[(cb + 1) * HB + hl];
-            const double v2 = VBs[(cb + 2) * HB + hl], v3 = VBs[(cb + 3) * HB + hl];
-            xb += v0;
-            xb += v1;
-            xb += v2;
-            xb += v3;
-          }
-          for (; cb < c1; ++cb) xb += VBs[cb * HB + hl];
-          GBl[s * HB + hl] = xb;
-        }
+#pragma unroll
+      for (int u = 0; u < K; ++u) {
+        const int j = u * T + tid, c0 = (int)(child[u] & 0xffffu), cn = (int)(child[u] >> 16);
+        if (lev[u] != l || cn == 0) continue;
+        Gl[j] = add_run<HB>(Gl[j], Vs + c0, cn);
+        if (dual) GBl[j] = add_run<HB>(GBl[j], VBs + c0, cn);  // the same additions on the best-response values
       }
       __syncthreads();
     }
-    const int nb0 = t.level_begin[l], cnt = (t.level_begin[l + 1] - nb0) * HB;
-    for (int i = tid; i < cnt; i += kThreads) {
-      const int v = nb0 + i / HB, hl = i % HB;
-      if (h0 + hl < n) {
-        fused_node<TG, HB>(rec, prm, Gl, Ql, Vs, v, hl, mu, want_q);
-        if (dual) fused_node<TG, HB>(rec, prm, GBl, nullptr, VBs, v, hl, 0.0, false);  // mu = 0: the minimum
-      }
+    Task d = own;
+#pragma unroll 1
+    for (int q = tid;;) {
+      if ((d.na_level >> 8) == l) run_task(d, l > 0, q & (l > 0 ? 3 : 1));
+      if ((q += T) >= n_tasks) break;
+      d = task_of(q);
     }
     __syncthreads();
   }
 
-  // the local strategies, for a later top-down pass (0 in the padding)
-  if (e.qb_out && want_q) {
-    TG* qb_out = (TG*)e.qb_out;
-    for (int i = tid; i < SH; i += kThreads) {
-      const int hh = h0 + i % HB;
-      qb_out[(size_t)(i / HB) * ld + hh] = hh < n ? (TG)Ql[i] : (TG)0;
+  // 3. partial root sums, in the block's last HB threads: the tree's, and a
+  // dual tree's best response after the launch's trees
+  const int rt = tid - (T - HB);
+  if (a.partial && rt >= 0) {
+    double sv = 0.0, sb = 0.0;
+    if (h0 + rt < n) {
+      sv = add_run<HB>(0.0, Vs + t.C * HB + rt, t.n_roots);
+      if (dual) sb = add_run<HB>(0.0, VBs + t.C * HB + rt, t.n_roots);
+    }
+#pragma unroll
+    for (int off = HB / 2; off > 0; off >>= 1) {
+      sv += __shfl_down(sv, off, HB);
+      sb += __shfl_down(sb, off, HB);
+    }
+    if (rt == 0) {
+      a.partial[(size_t)k * nb + hblk] = sv;
+      if (dual) a.partial[(size_t)(a.count + k) * nb + hblk] = sb;
     }
   }
 
-  // 3. partial root sum
-  if (a.partial && tid < HB) {
-    double sv = 0.0;
-    if (h0 + tid < n) {
-      const int C = N - t.P.n_roots;
-      for (int r = 0; r < t.P.n_roots; ++r) sv += Vs[(C + r) * HB + tid];
-    }
+  // 4. local strategies, top-down and epilogue (0 in the padding)
+  if (want_q) {
+    double qv[K];
 #pragma unroll
-    for (int off = HB / 2; off > 0; off >>= 1) sv += __shfl_down(sv, off, HB);
-    if (tid == 0) a.partial[(size_t)k * nb + hblk] = sv;
-  }
-  if (a.partial && dual && tid < HB) {  // the best response's, after the launch's trees
-    double sv = 0.0;
-    if (h0 + tid < n) {
-      const int C = N - t.P.n_roots;
-      for (int r = 0; r < t.P.n_roots; ++r) sv += VBs[(C + r) * HB + tid];
+    for (int u = 0; u < K; ++u) {
+      const int j = u * T + tid, s = j / HB;
+      qv[u] = 0.0;
+      if (lev[u] >= 0) {
+        const double sum = Sl[par_slot[u] >> 16];
+        qv[u] = (double)(TG)qbar<TG>(Wl[j], sum, inv_or_zero<TG>(sum));
+      }
+      if (qb_out && s < S) qb_out[(size_t)s * ld + h0 + j % HB] = (TG)qv[u];
     }
+    if (q_out || comb_out) {
 #pragma unroll
-    for (int off = HB / 2; off > 0; off >>= 1) sv += __shfl_down(sv, off, HB);
-    if (tid == 0) a.partial[(size_t)(a.ps.count + k) * nb + hblk] = sv;
+      for (int u = 0; u < K; ++u)
+        if (lev[u] > 0) Wl[u * T + tid] = qv[u];  // the lowest level has no children
+      for (int l = n_levels - 2; l >= 0; --l) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+          const unsigned par = par_slot[u] & 0xffffu;
+          if (lev[u] != l || par == kNone) continue;
+          qv[u] = (double)((TG)Wl[par] * (TG)qv[u]);
+          if (l > 0) Wl[u * T + tid] = qv[u];
+        }
+      }
+      const TG tau = (TG)t.tau, one_m_tau = (TG)(1.0 - t.tau);
+#pragma unroll
+      for (int u = 0; u < K; ++u) {
+        const int j = u * T + tid, s = j / HB;
+        if (s >= S) continue;
+        const size_t idx = (size_t)s * ld + h0 + j % HB;
+        const TG q = (TG)qv[u];
+        if (q_out) q_out[idx] = q;
+        if (comb_out) comb_out[idx] = one_m_tau * (TG)vx[u] + tau * q;
+      }
+    }
   }
 
-  // 4. top-down and epilogue
-  if (e.q_out || e.comb_out) {
-    for (int l = t.n_levels - 1; l >= 0; --l) {
-      const int sb0 = t.seq_level_begin[l], cnt = (t.seq_level_begin[l + 1] - sb0) * HB;
-      for (int i = tid; i < cnt; i += kThreads) {
-        const int s = sb0 + i / HB, hl = i % HB;
-        const int par = spar[s];
-        if (h0 + hl < n && par >= 0) Ql[s * HB + hl] = (double)((TG)Ql[par * HB + hl] * (TG)Ql[s * HB + hl]);
-      }
-      __syncthreads();
-    }
-    TG* q_out = (TG*)e.q_out;
-    TG* comb_out = (TG*)e.comb_out;
-    const TG tau = (TG)e.tau, one_m_tau = (TG)(1.0 - e.tau);
-    for (int i = tid; i < SH; i += kThreads) {
-      const int hh = h0 + i % HB;
-      const size_t idx = (size_t)(i / HB) * ld + hh;
-      if (hh >= n) {
-        if (q_out) q_out[idx] = (TG)0;
-        if (comb_out) comb_out[idx] = (TG)0;
-        continue;
-      }
-      const TG q = (TG)Ql[i];
-      if (q_out) q_out[idx] = q;
-      if (comb_out) comb_out[idx] = one_m_tau * (TG)Xl[i] + tau * q;
-    }
+  // one live slot (HB = 1, one block per tree): the block also writes the rows' padding
+  if constexpr (HB == 1) {
+    const int pad = ld - 1;
+    TG* outs[4] = {g_out, want_q ? qb_out : nullptr, q_out, comb_out};
+    for (int o = 0; o < 4; ++o)
+      if (outs[o])
+        for (int i = tid; i < S * pad; i += T) outs[o][(size_t)(i / pad) * ld + 1 + i % pad] = (TG)0;
   }
 }
 
@@ -914,63 +999,122 @@ static void fill_pass_set(const egt_game* g, const Pass* p, int count, PassSet& 
   }
 }
 
-int n_partials(const egt_game* g) { return g->fused_passes ? g->ld / g->fused_hands : 1; }
+// Hand blocks of the fused pass: every slot of a row is in one; a general
+// game's one live slot is a block of its own, which writes the padding too.
+static int fused_hblocks(const egt_game* g) { return g->fused_hands == 1 ? 1 : g->ld / g->fused_hands; }
 
-size_t fused_lds_bytes(int hands, int cap_tab_bytes, int cap_nodes, int cap_seqs) {
-  return (size_t)cap_tab_bytes + sizeof(double) * (3 * (size_t)cap_seqs + (size_t)cap_nodes) * hands;
+int n_partials(const egt_game* g) { return g->fused_passes ? fused_hblocks(g) : 1; }
+
+size_t fused_lds_bytes(int hands, int cap_nodes, int cap_seqs, bool dual) {
+  const size_t seqs = (size_t)(cap_seqs + kFusedPad) * hands, nodes = (size_t)(cap_nodes + kFusedPad) * hands;
+  return sizeof(double) * (dual ? 3 * seqs + 3 * nodes : 2 * seqs + 2 * nodes);
+}
+
+// The fused pass or a launch per level.  A block's time grows with the
+// (sequence, hand) pairs K per thread, the level path's with its levels (four
+// or five launches of at least 4 us each) until its launches fill the chip.
+// Where the fused pass has a block for every compute unit and more, and in its
+// one block of a general game, the paths meet near K = 3 (one step of EGT; 1081
+// hands: 286 sequences 98 against 101 us, 520 sequences 158 against 122;
+// general: 336 sequences 71 against 92 us, 936 sequences 91 against 96, 1240
+// sequences 96 against 97); with blocks for part of the chip only, near K = 6
+// (105 and 351 hands, 520 sequences: 84 against 92 and 88 against 100 us; 967
+// sequences: 112 against 106 and 118 against 119).
+bool fits_fused(const egt_game* g) {
+  const int seqs = std::max(g->hp[0].n_seq, g->hp[1].n_seq), nodes = std::max(g->hp[0].n_nodes, g->hp[1].n_nodes);
+  const bool part = g->fused_hands > 1 && 2 * fused_hblocks(g) <= g->n_cu;
+  const int tasks = part ? 5 : 3;
+  return seqs * g->fused_hands <= tasks * kFusedThreads &&
+         fused_lds_bytes(g->fused_hands, nodes, seqs, false) <= (size_t)g->lds_per_block;
+}
+
+// The fewest (sequence, hand) pairs per thread that 512 threads allow.
+template <int HB, class TG>
+static void fused_launch_hands(const FusedArgs& a, int pairs, dim3 grid, size_t lds, hipStream_t s) {
+  const dim3 block((unsigned)std::min(kFusedThreads, std::max(256, (pairs + 63) / 64 * 64)));
+  if (pairs <= kFusedThreads)
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, 1, TG>), grid, block, lds, s, a);
+  else if (pairs <= 2 * kFusedThreads)
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, 2, TG>), grid, block, lds, s, a);
+  else if (pairs <= 4 * kFusedThreads)
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, 4, TG>), grid, block, lds, s, a);
+  else
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, 8, TG>), grid, block, lds, s, a);
+}
+
+// All passes in one launch of the fused kernel.
+template <class TG>
+static hipError_t fused_launch(const egt_game* g, const Pass* p, int count, const Epilogue* epi, double* partial,
+                               hipStream_t s) {
+  const int hb = g->fused_hands;
+  FusedArgs a;
+  a.cap_nodes = std::max(g->hp[0].n_nodes, g->hp[1].n_nodes);
+  a.cap_seqs = std::max(g->hp[0].n_seq, g->hp[1].n_seq);
+  // dual passes inside the kernel when every pass is dual, every one is
+  // smoothed and the extra LDS fits; otherwise each becomes a second tree
+  // with mu = 0 after the others
+  bool any_dual = false;
+  bool in_kernel = fused_lds_bytes(hb, a.cap_nodes, a.cap_seqs, true) <= (size_t)g->lds_per_block;
+  for (int k = 0; k < count; ++k) {
+    any_dual = any_dual || p[k].VB;
+    in_kernel = in_kernel && p[k].VB && p[k].mu > 0.0;
+  }
+  int nt = 0;
+  auto add = [&](const Pass& q, double mu, const Epilogue& e) {
+    const HostPlayer& hp = g->hp[q.player];
+    FusedTree& t = a.t[nt++];
+    t.seq = g->dp[q.player].seq_rec;
+    t.node = g->dp[q.player].node_rec;
+    t.gA = q.gA;
+    t.gB = q.gB;
+    t.x_prev = e.x_prev;
+    t.q_out = e.q_out;
+    t.comb_out = e.comb_out;
+    t.g_out = e.g_out;
+    t.qb_out = e.qb_out;
+    t.cA = q.cA;
+    t.cB = q.cB;
+    t.mu = mu;
+    t.tau = e.tau;
+    t.g_scale = e.g_scale;
+    t.S = hp.n_seq;
+    t.N = hp.n_nodes;
+    t.C = (int)hp.child.size();
+    t.n_roots = (int)hp.roots.size();
+    t.n_levels = hp.n_levels;
+    t.n_leaf = hp.n_levels > 0 ? hp.level_begin[1] : 0;
+    t.dual = in_kernel;
+  };
+  const Epilogue none{nullptr, nullptr, 0.0, nullptr, nullptr, 0.0};
+  for (int k = 0; k < count; ++k) add(p[k], p[k].mu, epi ? epi[k] : none);
+  for (int k = 0; any_dual && !in_kernel && k < count; ++k) {
+    if (!p[k].VB) continue;
+    if (nt >= kMaxTrees) return hipErrorInvalidValue;
+    add(p[k], 0.0, none);
+  }
+  a.partial = partial;
+  a.count = nt;
+  a.n = g->n;
+  a.ld = g->ld;
+  a.n_hblocks = fused_hblocks(g);
+  const dim3 grid((unsigned)(a.n_hblocks * nt));
+  const size_t lds = fused_lds_bytes(hb, a.cap_nodes, a.cap_seqs, in_kernel);
+  const int pairs = a.cap_seqs * hb;
+  if (hb == 4)
+    fused_launch_hands<4, TG>(a, pairs, grid, lds, s);
+  else if (hb == 16)
+    fused_launch_hands<16, TG>(a, pairs, grid, lds, s);
+  else
+    fused_launch_hands<1, TG>(a, pairs, grid, lds, s);
+  return hipGetLastError();
 }
 
 template <class TG>
 static hipError_t passes_launch(const egt_game* g, const Pass* p, int count, const Epilogue* epi, double* partial,
                                 hipStream_t s) {
+  if (g->fused_passes) return fused_launch<TG>(g, p, count, epi, partial, s);
   bool any_dual = false;
   for (int k = 0; k < count; ++k) any_dual = any_dual || p[k].VB != nullptr;
-  const int n_epi = count;  // epilogues belong to the passes as given
-  if (g->fused_passes) {
-    const int cap_tab = (int)std::max(g->hp[0].fused_tab.size(), g->hp[1].fused_tab.size());
-    const int cap_nodes = std::max(g->hp[0].n_nodes, g->hp[1].n_nodes);
-    const int cap_seqs = std::max(g->hp[0].n_seq, g->hp[1].n_seq);
-    const size_t dual_lds = sizeof(double) * (size_t)g->fused_hands * ((size_t)cap_seqs + (size_t)cap_nodes);
-    // dual passes inside the kernel when every pass is dual, every one is
-    // smoothed and the extra LDS fits; otherwise each becomes a second tree
-    // with mu = 0 after the others
-    bool all_dual = true;
-    for (int k = 0; k < count; ++k) all_dual = all_dual && p[k].VB != nullptr && p[k].mu > 0.0;
-    const bool in_kernel =
-        any_dual && all_dual &&
-        fused_lds_bytes(g->fused_hands, cap_tab, cap_nodes, cap_seqs) + dual_lds <= (size_t)g->lds_per_block;
-    Pass q[kMaxTrees];
-    int nq = 0;
-    for (int k = 0; k < count; ++k) {
-      q[nq] = p[k];
-      if (!in_kernel) q[nq].VB = nullptr;
-      ++nq;
-    }
-    for (int k = 0; any_dual && !in_kernel && k < count; ++k) {
-      if (!p[k].VB) continue;
-      if (nq >= kMaxTrees) return hipErrorInvalidValue;
-      q[nq++] = Pass{p[k].player, p[k].gA, p[k].cA, p[k].gB, p[k].cB, 0.0, p[k].VB, nullptr};
-    }
-    p = q;
-    count = nq;
-    FusedArgs a;
-    fill_pass_set(g, p, count, a.ps);
-    for (int k = 0; k < kMaxTrees; ++k)
-      a.epi[k] = (epi && k < n_epi) ? epi[k] : Epilogue{nullptr, nullptr, 0.0, nullptr, nullptr, 0.0};
-    a.partial = partial;
-    a.cap_tab = (int)std::max(g->hp[0].fused_tab.size(), g->hp[1].fused_tab.size());
-    a.cap_nodes = std::max(g->hp[0].n_nodes, g->hp[1].n_nodes);
-    a.cap_seqs = std::max(g->hp[0].n_seq, g->hp[1].n_seq);
-    const int hb = g->fused_hands;
-    const size_t lds = fused_lds_bytes(hb, a.cap_tab, a.cap_nodes, a.cap_seqs) + (in_kernel ? dual_lds : 0);
-    a.n_hblocks = g->ld / hb;
-    const dim3 grid((unsigned)(a.n_hblocks * count));
-    if (hb == 4)
-      hipLaunchKernelGGL((sbr_fused_kernel<4, TG>), grid, dim3(kFusedSlots * 4), lds, s, a);
-    else
-      hipLaunchKernelGGL((sbr_fused_kernel<16, TG>), grid, dim3(kFusedSlots * 16), lds, s, a);
-    return hipGetLastError();
-  }
   PassSet a;
   fill_pass_set(g, p, count, a);
   for (int k = 0; k < count; ++k) {
