@@ -38,11 +38,12 @@ FLAGS = [
 ]
 
 
-# The fused pass holds the polynomial constants of exp and log in registers for
-# its whole level loop when the compiler hoists them there: 100 registers and
-# two blocks per compute unit instead of 64 and four.
+# The fused passes hold the constants of exp, log and divisions in registers for
+# their whole level loop when the compiler hoists them there (the smoothed best
+# response: 100 registers and two blocks per compute unit instead of 64 and four).
 SOURCE_FLAGS = {
     "egt_kernels.hip": ["-mllvm", "-disable-machine-licm"],
+    "egt_cfr.hip": ["-mllvm", "-disable-machine-licm"],
 }
 
 

@@ -295,7 +295,7 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
     hp.node_rec[i] = NodeRec{hp.node_first_seq[i], hp.node_nact[i], vslot[i], lev, hp.node_beta[i], hp.node_logn[i]};
     for (int s = hp.node_first_seq[i]; s < hp.node_first_seq[i] + hp.node_nact[i]; ++s)
       hp.seq_rec[s] = SeqRec{hp.seq_parent[s], hp.child_begin[s], hp.child_begin[s + 1] - hp.child_begin[s], vslot[i],
-                             lev, {0, 0, 0}};
+                             lev, hp.node_nact[i], {0, 0}};
   }
   return EGT_OK;
 }
@@ -514,8 +514,8 @@ int build_game_host(const egt_game_desc* d, egt_game** out) {
     }
   }
   // enough 4-hand blocks to spread over the chip; 16-hand blocks for small hand
-  // counts, unless a thread would hold more than four (sequence, hand) pairs
-  g->fused_hands = g->ld < 512 && 16 * std::max(g->hp[0].n_seq, g->hp[1].n_seq) <= 4 * kFusedThreads ? 16 : 4;
+  // counts, unless a thread would hold more than three (sequence, hand) pairs
+  g->fused_hands = g->ld < 512 && 16 * std::max(g->hp[0].n_seq, g->hp[1].n_seq) <= 3 * kFusedThreads ? 16 : 4;
   for (const RawTerminal& t : en.terms) (t.kind == 0 ? g->n_fold : g->n_show)++;
   for (int p = 0; p < 2; ++p)
     for (double b : g->hp[p].node_beta) g->max_beta = std::max(g->max_beta, b);

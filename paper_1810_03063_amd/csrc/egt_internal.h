@@ -17,15 +17,15 @@ constexpr int kMaxActions = 16;  // actions per decision node
 constexpr int kMaxDepth = 16;    // sequences on a root-to-leaf chain of one player (and levels)
 constexpr int kMaxTrees = 4;     // trees evaluated by one bottom-up launch
 constexpr int kFusedThreads = 512;  // threads of one single-launch pass block, at most
-constexpr int kFusedTasks = 8;      // (sequence, hand) pairs of one of its threads, at most
+constexpr int kFusedTasks = 5;      // (sequence, hand) pairs of one of its threads, at most
 
 // One sequence and one node as the single-launch passes read them: the
 // sequence's parent (-1 at a root), the value slots [c0, c0 + n_child) of its
-// child nodes, its own node's value slot and level (0 = lowest); the node's
-// first sequence, number of actions, value slot, level, dilation weight and
-// log(number of actions).
+// child nodes, its own node's value slot, level (0 = lowest) and number of
+// actions; the node's first sequence, number of actions, value slot, level,
+// dilation weight and log(number of actions).
 struct SeqRec {
-  int parent, c0, n_child, slot, level, pad[3];
+  int parent, c0, n_child, slot, level, na, pad[2];
 };
 struct NodeRec {
   int first, na, slot, level;
@@ -324,9 +324,13 @@ namespace egt {
 
 // grad_out = A v_opp (player 0) or A^T v_opp (player 1); general games take
 // the CSR product (launch_spmv).
-hipError_t launch_spmv(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s);
-hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, double* grad_out,
-                           hipStream_t s);
+// With absmax (device) every block also writes its largest |entry| there; *blocks
+// receives how many (at most absmax_capacity(g)).
+int absmax_capacity(const egt_game* g);
+hipError_t launch_spmv(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,
+                       double* absmax = nullptr, int* blocks = nullptr);
+hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,
+                           double* absmax = nullptr, int* blocks = nullptr);
 
 // count (1..kMaxTrees) independent passes in as few launches as possible:
 // bottom-up over every level; when `partial` is not null, the tree values as
@@ -341,8 +345,9 @@ hipError_t launch_passes(const egt_game* g, const Pass* p, int count, const Epil
 int n_partials(const egt_game* g);
 // LDS of one fused-pass block (dual: with the best responses beside).
 size_t fused_lds_bytes(int hands, int cap_nodes, int cap_seqs, bool dual);
-// Whether a game's smoothed best responses take the fused pass.
+// Whether a game's smoothed best responses take the fused pass; its hand blocks.
 bool fits_fused(const egt_game* g);
+int fused_hblocks(const egt_game* g);
 
 // out[k] = sum of the n_partials(g) partials of tree k, in order.
 hipError_t launch_sum_partials(const egt_game* g, const double* partial, int count, double* out, hipStream_t s);

@@ -22,6 +22,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "egt_device.h"
 #include "egt_internal.h"
 
 namespace egt {
@@ -173,14 +174,6 @@ struct FusedArgs {
   int cap_nodes, cap_seqs;
 };
 
-// Bijection of [0, total): workgroup L (on XCD L % 8) -> position, with each
-// XCD's workgroups on consecutive positions.
-__device__ inline int xcd_spread(int L, int total) {
-  const int q = total / 8, r = total % 8;
-  const int x = L % 8, j = L / 8;
-  return x * q + min(x, r) + j;
-}
-
 // A double moved within every aligned quad of lanes (DPP quad permute).
 template <int CTRL>
 __device__ inline double quad_move(double x) {
@@ -188,20 +181,6 @@ __device__ inline double quad_move(double x) {
   const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-// x + p[0] + p[HB] + ... (cnt > 0 entries, added in order).  The last run reads
-// up to three entries past the end; the arrays leave room for that.
-template <int HB>
-__device__ __forceinline__ double add_run(double x, const double* p, int cnt) {
-  for (int c = 0; c < cnt; c += 4, p += 4 * HB) {
-    const double v0 = p[0], v1 = p[HB], v2 = p[2 * HB], v3 = p[3 * HB];
-    x += v0;
-    if (c + 1 < cnt) x += v1;
-    if (c + 2 < cnt) x += v2;
-    if (c + 3 < cnt) x += v3;
-  }
-  return x;
 }
 
 // One (node, hand) task of the node phase by 2 or (quad) 4 adjacent lanes, b the
@@ -246,10 +225,8 @@ __device__ __forceinline__ double lanes_node(const double* G, double* W, int na,
   return lse_value(m, temp, sum, logn);
 }
 
-constexpr int kFusedPad = 16;  // entries past the end of an LDS array that a run may read
-
 template <int HB, int K, class TG>
-__global__ __launch_bounds__(kFusedThreads, K <= 2 ? 8 : K <= 4 ? 5 : 2) void sbr_fused_kernel(FusedArgs a) {
+__global__ __launch_bounds__(kFusedThreads, K <= 2 ? 8 : K <= 3 ? 5 : 4) void sbr_fused_kernel(FusedArgs a) {
   extern __shared__ __align__(16) double fused_lds[];
   const int nb = a.n_hblocks;
   const int P = xcd_spread((int)blockIdx.x, (int)gridDim.x);
@@ -1001,7 +978,7 @@ static void fill_pass_set(const egt_game* g, const Pass* p, int count, PassSet& 
 
 // Hand blocks of the fused pass: every slot of a row is in one; a general
 // game's one live slot is a block of its own, which writes the padding too.
-static int fused_hblocks(const egt_game* g) { return g->fused_hands == 1 ? 1 : g->ld / g->fused_hands; }
+int fused_hblocks(const egt_game* g) { return g->fused_hands == 1 ? 1 : g->ld / g->fused_hands; }
 
 int n_partials(const egt_game* g) { return g->fused_passes ? fused_hblocks(g) : 1; }
 
@@ -1023,12 +1000,12 @@ size_t fused_lds_bytes(int hands, int cap_nodes, int cap_seqs, bool dual) {
 bool fits_fused(const egt_game* g) {
   const int seqs = std::max(g->hp[0].n_seq, g->hp[1].n_seq), nodes = std::max(g->hp[0].n_nodes, g->hp[1].n_nodes);
   const bool part = g->fused_hands > 1 && 2 * fused_hblocks(g) <= g->n_cu;
-  const int tasks = part ? 5 : 3;
+  const int tasks = part ? kFusedTasks : 3;
   return seqs * g->fused_hands <= tasks * kFusedThreads &&
          fused_lds_bytes(g->fused_hands, nodes, seqs, false) <= (size_t)g->lds_per_block;
 }
 
-// The fewest (sequence, hand) pairs per thread that 512 threads allow.
+// 1, 2, 3 or 5 (sequence, hand) pairs per thread, the fewest that 512 threads allow.
 template <int HB, class TG>
 static void fused_launch_hands(const FusedArgs& a, int pairs, dim3 grid, size_t lds, hipStream_t s) {
   const dim3 block((unsigned)std::min(kFusedThreads, std::max(256, (pairs + 63) / 64 * 64)));
@@ -1036,10 +1013,10 @@ static void fused_launch_hands(const FusedArgs& a, int pairs, dim3 grid, size_t 
     hipLaunchKernelGGL((sbr_fused_kernel<HB, 1, TG>), grid, block, lds, s, a);
   else if (pairs <= 2 * kFusedThreads)
     hipLaunchKernelGGL((sbr_fused_kernel<HB, 2, TG>), grid, block, lds, s, a);
-  else if (pairs <= 4 * kFusedThreads)
-    hipLaunchKernelGGL((sbr_fused_kernel<HB, 4, TG>), grid, block, lds, s, a);
+  else if (pairs <= 3 * kFusedThreads)
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, 3, TG>), grid, block, lds, s, a);
   else
-    hipLaunchKernelGGL((sbr_fused_kernel<HB, 8, TG>), grid, block, lds, s, a);
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, 5, TG>), grid, block, lds, s, a);
 }
 
 // All passes in one launch of the fused kernel.

@@ -36,6 +36,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "egt_internal.h"
 
@@ -70,6 +71,12 @@ __device__ inline double wave_inclusive_scan(double x) {
   return x;
 }
 
+// The largest x >= 0 over the wavefront, in every lane.
+__device__ inline double wave_max(double x) {
+  for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
+  return x;
+}
+
 template <class TV, class TO>
 struct ProdArgs {
   DPlayer own;
@@ -81,6 +88,7 @@ struct ProdArgs {
   int groups;
   const TermItem* items;   // work items instead of whole sequences, or null
   int n_items;
+  double* absmax;  // MAX: each block's largest |entry|
 };
 
 // HPT = hands per thread (n <= 256 HPT).  MINW = waves per SIMD the register
@@ -88,7 +96,9 @@ struct ProdArgs {
 // TAB = the per-hand tables (index table, own prior) staged once per block in
 // LDS behind the groups' arrays, which leaves the registers to the staging
 // and the accumulators (used when the device's LDS per block allows it).
-template <class TV, class TO, int HPT, int MINW, bool TAB>
+// MAX = also the block's largest |entry| (one store per block: atomics of every
+// wavefront on one word took 19 us at 223 sequences).
+template <class TV, class TO, int HPT, int MINW, bool TAB, bool MAX>
 __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdArgs<TV, TO> a) {
   extern __shared__ __align__(16) double lds[];
   __shared__ double wave_total[2][kGroupThreads / 64];
@@ -193,6 +203,7 @@ __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdAr
   double acc[HPT];
 #pragma unroll
   for (int k = 0; k < HPT; ++k) acc[k] = 0.0;
+  double top = 0.0;  // MAX: this thread's largest |entry|
   while (w < n_work) {
     // uniform within a group
     const bool active = tr.kind >= 0;
@@ -350,7 +361,11 @@ __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdAr
         TO* row = a.out + (size_t)s_out * ld;
 #pragma unroll
         for (int k = 0; k < HPT; ++k)
-          if (k < cnt) row[beg + k] = (TO)(acc[k] * ((TAB ? bown_l[beg + k] : bown[k]) * a.H.invZ));
+          if (k < cnt) {
+            const TO x = (TO)(acc[k] * ((TAB ? bown_l[beg + k] : bown[k]) * a.H.invZ));
+            row[beg + k] = x;
+            if constexpr (MAX) top = fmax(top, fabs((double)x));
+          }
         for (int i = n + gt; i < ld; i += kGroupThreads) row[i] = (TO)0;
       }
 #pragma unroll
@@ -369,6 +384,15 @@ __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdAr
     tr1 = tr2;
     s1 = s2;
     comb1 = comb2;
+  }
+  if constexpr (MAX) {
+    top = wave_max(top);
+    if (lane == 0) wave_total[grp][wig] = top;  // the last round ended in a barrier
+    __syncthreads();
+    if (tid == 0) {
+      for (int v = 1; v < (int)blockDim.x / 64; ++v) top = fmax(top, wave_total[v / (kGroupThreads / 64)][v % (kGroupThreads / 64)]);
+      a.absmax[blockIdx.x] = top;
+    }
   }
 }
 
@@ -481,26 +505,35 @@ size_t align2(size_t x) { return (x + 1) / 2 * 2; }
 // fixed xor butterfly (every lane ends with the same sum); the row's slot 0
 // gets the sum and its padding slots 1 .. ld - 1 are written 0.
 __global__ __launch_bounds__(256) void spmv_kernel(const int64_t* ptr, const int* col, const double* val,
-                                                   const double* v, int ld, int n_rows, double* out) {
+                                                   const double* v, int ld, int n_rows, double* out,
+                                                   double* absmax) {
+  __shared__ double top[4];
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n_rows) return;
-  const int64_t k0 = ptr[row], k1 = ptr[row + 1];
+  const bool live = row < n_rows;
+  const int64_t k0 = live ? ptr[row] : 0, k1 = live ? ptr[row + 1] : 0;
   double acc = 0.0;
   for (int64_t k = k0 + lane; k < k1; k += 64) acc += val[k] * v[(size_t)col[k] * ld];
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
   double* o = out + (size_t)row * ld;
-  for (int i = lane; i < ld; i += 64) o[i] = i == 0 ? acc : 0.0;
+  for (int i = lane; live && i < ld; i += 64) o[i] = i == 0 ? acc : 0.0;
+  if (absmax) {  // the block's largest |entry|
+    if (lane == 0) top[threadIdx.x >> 6] = fabs(acc);
+    __syncthreads();
+    if (threadIdx.x == 0) absmax[blockIdx.x] = fmax(fmax(fmax(fmax(0.0, top[0]), top[1]), top[2]), top[3]);
+  }
 }
 
 }  // namespace
 
-hipError_t launch_spmv(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s) {
+hipError_t launch_spmv(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,
+                       double* absmax, int* blocks) {
   const DPlayer& P = g->dp[player];
   if (!g->general || !P.sp_ptr) return hipErrorInvalidValue;
+  if (blocks) *blocks = (P.n_seq + 3) / 4;
   if (P.n_seq == 0) return hipSuccess;
   hipLaunchKernelGGL(spmv_kernel, dim3((unsigned)((P.n_seq + 3) / 4)), dim3(256), 0, s, P.sp_ptr, P.sp_col, P.sp_val,
-                     v_opp, g->ld, P.n_seq, grad_out);
+                     v_opp, g->ld, P.n_seq, grad_out, absmax);
   return hipGetLastError();
 }
 
@@ -510,7 +543,8 @@ size_t product_group_doubles(const egt_game* g) { return align2((size_t)g->n + 1
 size_t product_table_bytes(const egt_game* g) { return (16 + 8) * (size_t)g->n; }
 
 template <class TV, class TO>
-static hipError_t product_launch(const egt_game* g, int player, const TV* v_opp, TO* grad_out, hipStream_t s) {
+static hipError_t product_launch(const egt_game* g, int player, const TV* v_opp, TO* grad_out, hipStream_t s,
+                                 double* absmax, int* n_blocks) {
   ProdArgs<TV, TO> a;
   a.own = g->dp[player];
   a.b_opp = g->dp[1 - player].belief;
@@ -520,6 +554,7 @@ static hipError_t product_launch(const egt_game* g, int player, const TV* v_opp,
   a.show_sign = player == 0 ? 1.0 : -1.0;
   a.items = nullptr;
   a.n_items = 0;
+  a.absmax = absmax;
   // two blocks per compute unit: each takes at most half of the CU's LDS
   const size_t budget = (size_t)g->lds_per_cu / 2;
   auto lds_bytes = [&](int gr) { return sizeof(double) * align2(gr * product_group_doubles(g)); };
@@ -536,31 +571,38 @@ static hipError_t product_launch(const egt_game* g, int player, const TV* v_opp,
     a.n_items = g->dp[player].n_items;
   }
   const int units = a.items ? a.n_items : g->dp[player].n_seq;
-  if (units == 0) return hipSuccess;
   const int blocks = std::min(units, 2 * g->n_cu);
+  if (n_blocks) *n_blocks = blocks;
+  if (units == 0) return hipSuccess;
   const dim3 grid(blocks), block(kGroupThreads * groups);
-  if (g->n <= 2 * kGroupThreads) {
-    if (tab)
-      hipLaunchKernelGGL((product_kernel<TV, TO, 2, 4, true>), grid, block, lds, s, a);
+  auto launch = [&](auto hpt, auto minw) {
+    constexpr int H = decltype(hpt)::value, W = decltype(minw)::value;
+    if (absmax && tab)
+      hipLaunchKernelGGL((product_kernel<TV, TO, H, W, true, true>), grid, block, lds, s, a);
+    else if (absmax)
+      hipLaunchKernelGGL((product_kernel<TV, TO, H, W, false, true>), grid, block, lds, s, a);
+    else if (tab)
+      hipLaunchKernelGGL((product_kernel<TV, TO, H, W, true, false>), grid, block, lds, s, a);
     else
-      hipLaunchKernelGGL((product_kernel<TV, TO, 2, 4, false>), grid, block, lds, s, a);
-  } else if (g->n <= 5 * kGroupThreads) {
-    if (tab)
-      hipLaunchKernelGGL((product_kernel<TV, TO, 5, 4, true>), grid, block, lds, s, a);
-    else
-      hipLaunchKernelGGL((product_kernel<TV, TO, 5, 4, false>), grid, block, lds, s, a);
-  } else {
-    if (tab)
-      hipLaunchKernelGGL((product_kernel<TV, TO, 8, 2, true>), grid, block, lds, s, a);
-    else
-      hipLaunchKernelGGL((product_kernel<TV, TO, 8, 2, false>), grid, block, lds, s, a);
-  }
+      hipLaunchKernelGGL((product_kernel<TV, TO, H, W, false, false>), grid, block, lds, s, a);
+  };
+  if (g->n <= 2 * kGroupThreads)
+    launch(std::integral_constant<int, 2>(), std::integral_constant<int, 4>());
+  else if (g->n <= 5 * kGroupThreads)
+    launch(std::integral_constant<int, 5>(), std::integral_constant<int, 4>());
+  else
+    launch(std::integral_constant<int, 8>(), std::integral_constant<int, 2>());
   return hipGetLastError();
 }
 
-hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s) {
-  if (g->general) return launch_spmv(g, player, v_opp, grad_out, s);
-  return product_launch<double, double>(g, player, v_opp, grad_out, s);
+int absmax_capacity(const egt_game* g) {
+  return std::max(2 * g->n_cu, (std::max(g->hp[0].n_seq, g->hp[1].n_seq) + 3) / 4);
+}
+
+hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,
+                           double* absmax, int* blocks) {
+  if (g->general) return launch_spmv(g, player, v_opp, grad_out, s, absmax, blocks);
+  return product_launch<double, double>(g, player, v_opp, grad_out, s, absmax, blocks);
 }
 
 hipError_t launch_gradient_fold_f32(const egt_game* g, int player, const float* v_opp, float* grad_out,

@@ -1,18 +1,20 @@
-"""The single-launch smoothed best response at the sizes where its layout
-changes: 1, 2, 4 and 8 (sequence, hand) pairs per thread with 16 and 4 hands
+"""The single-launch smoothed best response and regret update at the sizes where its layout
+changes: 1, 2, 3 and 5 (sequence, hand) pairs per thread with 16 and 4 hands
 per block and with one live slot, trees just below and above the switch to a
 launch per level, nodes of one to ten actions (lane pairs and quads past their
 first round), and temperatures and gradients at the ends of the range, where
 the shift's quotient cannot be formed from a reciprocal.
 
 Tolerances are those of the operations elsewhere: strategies 1e-12 absolute,
-values 1e-13 of the size of the terms they add."""
+values 1e-13 of the size of the terms they add, CFR iterates 1e-10 of the
+largest entry."""
 import numpy as np
 import pytest
 
 from instances import make_instance
 from instances.efg import random_efg
 from instances.endgames import river
+from oracle import Cfr as OracleCfr
 from oracle import Problem
 from oracle.general import GeneralProblem
 from tests.layout import Layout
@@ -25,10 +27,10 @@ HALVES, QUARTERS, SEVEN = (0.5, 1.0, 2.0), (0.25, 0.5, 1.0, 2.0), (0.25, 0.5, 0.
 RIVER = [
     (5, (0.5, 1.0), 0),  # 10, 16 hands per block
     (5, HALVES, 1),      # 49
-    (5, HALVES, 2),      # 127, four pairs per thread
-    (5, (0.5, 1.0), 4),  # 157, over four: 4 hands per block
+    (5, (0.5, 1.0), 2),  # 64, two pairs per thread
+    (5, HALVES, 2),      # 127, over three: 4 hands per block
     (5, QUARTERS, 2),    # 286
-    (8, (0.25, 0.5, 0.75, 1.0, 2.0), 2),  # 520, 8 pairs per thread
+    (8, (0.25, 0.5, 0.75, 1.0, 2.0), 2),  # 520, 5 pairs per thread
     (8, QUARTERS, 3),    # 808, a launch per level
     (10, SEVEN, 1),      # 190, 595 hands, ten actions
     (13, QUARTERS, 2),   # 286, 1081 hands
@@ -65,6 +67,25 @@ def test_river_sizes(egt, ranks, fracs, raises):
     for p in (0, 1):
         print(f"[case] {inst.n_hands} hands, {G.n_seq[p]} sequences, player {p}", flush=True)
         check(egt, G, P, L, 10.0 * rng.standard_normal((P.n_seq[p], P.n)), p, 0.5)
+    G.close()
+
+
+@pytest.mark.parametrize("variant", ["CFR", "CFR_PLUS"])
+@pytest.mark.parametrize("ranks,fracs,raises", RIVER[:3] + RIVER[4:7] + RIVER[8:9])
+def test_regret_update_sizes(egt, ranks, fracs, raises, variant):
+    inst = river("x", 4, ranks, "ranking_ties10", 0.5, 1000.0, 20000.0, fracs, raises)
+    P, G = Problem(inst), egt.Game(inst)
+    L, C, D = Layout(G, P), OracleCfr(P, variant), egt.Cfr(G, variant)
+    print(f"[case] {variant} {inst.n_hands} hands, {G.n_seq} sequences", flush=True)
+    for _ in range(4):
+        C.step()
+        D.step(1)
+        got = D.get()
+        for p, key in ((0, "x"), (1, "y")):
+            for mine, want in ((got[key], C.cur[p]), (got[key + "_avg"], C.avg[p])):
+                assert torch.all(mine[:, P.n:] == 0)
+                assert np.abs(L.from_lib(p, mine.cpu().numpy()) - want).max() <= 1e-10 * np.abs(want).max()
+    D.close()
     G.close()
 
 
