@@ -235,7 +235,7 @@ int egt_saddle_gap(const egt_game* g, const double* x, const double* y, double* 
     // the partial sums go straight to pinned host memory and are added here, in
     // the order launch_sum_partials adds them: no sum and copy launches to wait for
     EGT_HIP(launch_passes(g, ps, 2, nullptr, w.hpart_dev, stream));
-    if ((rc = wait_for([&] { return hipStreamQuery(stream); }, [&] { return hipStreamSynchronize(stream); }))) return rc;
+    EGT_HIP(hipStreamSynchronize(stream));
     const int nb = n_partials(g);
     const double v0 = sum_in_order(w.hpart, nb), v1 = sum_in_order(w.hpart + nb, nb);
     // gap = max_y x^T A y - min_x x^T A y = -BR_y(-A^T x) - BR_x(A y)

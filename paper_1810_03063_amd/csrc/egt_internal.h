@@ -4,7 +4,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -370,23 +369,6 @@ __host__ __device__ inline double sum_in_order(const double* part, int nb) {
   }
   for (; b < nb; ++b) s += part[b];
   return s;
-}
-
-// Waits until `done` reports completion: polls for up to kSpinSeconds (a
-// blocking wait wakes up tens of microseconds late, which an iteration of
-// ~100 us cannot afford), then blocks, so that many concurrent solves do not
-// keep every host core busy.
-template <class Query, class Block>
-int wait_for(Query done, Block block) {
-  constexpr double kSpinSeconds = 200e-6;
-  const auto t0 = std::chrono::steady_clock::now();
-  hipError_t e;
-  while ((e = done()) == hipErrorNotReady &&
-         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() < kSpinSeconds) {
-  }
-  if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(e, "query");
-  EGT_HIP(block());
-  return EGT_OK;
 }
 
 // Top-down pass: q = product of q_bar along the sequence's chain.  Writes q to

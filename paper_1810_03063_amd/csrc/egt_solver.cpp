@@ -159,10 +159,11 @@ int read_values(egt_state* st) {
   return EGT_OK;
 }
 
-// Waits for the stream, then read_values.
+// Waits for the stream, then read_values.  (Polling hipStreamQuery instead found
+// the end 6 to 10 us later: a step on 105 hands 61 against 52 us.)
 int finish_values(egt_state* st, hipStream_t s) {
-  const int rc = wait_for([&] { return hipStreamQuery(s); }, [&] { return hipStreamSynchronize(s); });
-  return rc ? rc : read_values(st);
+  EGT_TRY(hipStreamSynchronize(s));
+  return read_values(st);
 }
 
 int fetch_values(egt_state* st, int trees, hipStream_t s) {
@@ -817,8 +818,7 @@ int solve_loop_pipelined(egt_state* st, hipStream_t s, const std::atomic<bool>* 
       spec = true;
     }
     // decide the current attempt
-    hipEvent_t ev = st->ev[cur];
-    if ((rc = wait_for([&] { return hipEventQuery(ev); }, [&] { return hipEventSynchronize(ev); }))) return rc;
+    EGT_TRY(hipEventSynchronize(st->ev[cur]));
     st->pending_trees = trees;
     st->pending_part = st->hpart;
     if ((rc = read_values(st))) return rc;
