@@ -44,6 +44,7 @@ FLAGS = [
 SOURCE_FLAGS = {
     "egt_kernels.hip": ["-mllvm", "-disable-machine-licm"],
     "egt_cfr.hip": ["-mllvm", "-disable-machine-licm"],
+    "egt_product.hip": ["-mllvm", "-disable-machine-licm"],
 }
 
 

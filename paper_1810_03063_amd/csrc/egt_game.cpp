@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <map>
 #include <memory>
 #include <numeric>
 #include <set>
@@ -300,6 +301,71 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
   return EGT_OK;
 }
 
+// Rounds of the paired product kernel for `blocks` blocks: sequences with the
+// same numbers of folds and showdowns are paired, a pair's rounds (its folds,
+// then its showdowns) go to one block, the most loaded pair first to the least
+// loaded block.  A fold round takes about half a showdown round's LDS traffic.
+void schedule_rounds(HostPlayer& hp, int blocks) {
+  struct Item {
+    std::vector<ProdRound> r;
+    int cost;
+  };
+  std::vector<Item> items;
+  std::map<std::pair<int, int>, int> pending;  // (folds, showdowns) -> unpaired sequence
+  auto emit = [&](int s0, int s1) {
+    Item it;
+    it.cost = 0;
+    const int seq[2] = {s0, s1};
+    std::vector<int> t[2][2];  // [kind][slot]
+    for (int j = 0; j < 2; ++j)
+      if (seq[j] >= 0)
+        for (int q = hp.term_begin[seq[j]]; q < hp.term_begin[seq[j] + 1]; ++q) t[hp.term_kind[q]][j].push_back(q);
+    for (int kind = 0; kind < 2; ++kind)
+      for (size_t k = 0; k < t[kind][0].size(); ++k) {
+        ProdRound r{{-1, -1}, {s0, s1}, {0.0, 0.0}, kind, 0};
+        for (int j = 0; j < 2; ++j)
+          if (k < t[kind][j].size()) {
+            r.opp[j] = hp.term_opp[t[kind][j][k]];
+            r.coef[j] = hp.term_coef[t[kind][j][k]];
+          }
+        it.r.push_back(r);
+        it.cost += kind == 0 ? 1 : 2;
+      }
+    if (it.r.empty()) it.r.push_back(ProdRound{{-1, -1}, {s0, s1}, {0.0, 0.0}, -1, 0});
+    it.r.back().last = 1;
+    items.push_back(std::move(it));
+  };
+  for (int s = 0; s < hp.n_seq; ++s) {
+    std::pair<int, int> key{0, 0};
+    for (int q = hp.term_begin[s]; q < hp.term_begin[s + 1]; ++q) ++(hp.term_kind[q] == 0 ? key.first : key.second);
+    const auto at = pending.find(key);
+    if (at == pending.end()) {
+      pending[key] = s;
+    } else {
+      emit(at->second, s);
+      pending.erase(at);
+    }
+  }
+  for (const auto& p : pending) emit(p.second, -1);
+  std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
+  blocks = std::max(1, std::min(blocks, (int)items.size()));
+  std::vector<std::vector<const Item*>> of(blocks);
+  std::set<std::pair<int, int>> load;  // (cost, block)
+  for (int b = 0; b < blocks; ++b) load.insert({0, b});
+  for (const Item& it : items) {
+    const std::pair<int, int> least = *load.begin();
+    load.erase(load.begin());
+    of[least.second].push_back(&it);
+    load.insert({least.first + it.cost, least.second});
+  }
+  hp.rounds.clear();
+  hp.round_begin.assign(1, 0);
+  for (const auto& list : of) {
+    for (const Item* it : list) hp.rounds.insert(hp.rounds.end(), it->r.begin(), it->r.end());
+    hp.round_begin.push_back((int)hp.rounds.size());
+  }
+}
+
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace
@@ -317,9 +383,19 @@ const char* last_error_cstr() { return g_last_error.c_str(); }
 // The upload image of every table (one device block), the device views' sizes
 // and the device attributes the launchers use.
 int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vector<uint4>& htab,
-                 const std::vector<unsigned>& hpos, const std::vector<double> (&b)[2]) {
+                 const std::vector<unsigned>& hpos, const std::vector<unsigned short>& card_slot,
+                 const std::vector<double> (&b)[2]) {
   const int n = g->n, cph = g->cph, nc = g->n_cards;
   const double Z = g->Z;
+  EGT_HIP(hipGetDevice(&g->device));
+  EGT_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, g->device));
+  if (g->n_cu < 1) g->n_cu = 1;
+  EGT_HIP(hipDeviceGetAttribute(&g->lds_per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device));
+  EGT_HIP(hipDeviceGetAttribute(&g->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device));
+  if (g->lds_per_block < 64 * 1024) g->lds_per_block = 64 * 1024;
+  if (g->lds_per_cu < g->lds_per_block) g->lds_per_cu = g->lds_per_block;
+  const int round_blocks = g->general ? 0 : paired_product_blocks(g, card_begin);
+  for (int p = 0; p < 2 && round_blocks > 0; ++p) schedule_rounds(g->hp[p], round_blocks);
   struct Piece {
     const void* src;
     size_t bytes;
@@ -350,6 +426,8 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
     po[p].roots = add(hp.roots.data(), hp.roots.size() * sizeof(int));
     po[p].belief = add(b[p].data(), b[p].size() * sizeof(double));
     po[p].ftab = add(hp.fused_tab.data(), hp.fused_tab.size());
+    po[p].rounds = add(hp.rounds.data(), hp.rounds.size() * sizeof(ProdRound));
+    po[p].rbeg = add(hp.round_begin.data(), hp.round_begin.size() * sizeof(int));
     po[p].srec = add(hp.seq_rec.data(), hp.seq_rec.size() * sizeof(SeqRec));
     po[p].nrec = add(hp.node_rec.data(), hp.node_rec.size() * sizeof(NodeRec));
     po[p].trec = add(hp.term_rec.data(), hp.term_rec.size() * sizeof(TermRec));
@@ -363,6 +441,7 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   g->offs.cbeg = add(card_begin.data(), card_begin.size() * sizeof(int));
   g->offs.htab = add(htab.data(), htab.size() * sizeof(uint4));
   g->offs.hpos = add(hpos.data(), hpos.size() * sizeof(unsigned));
+  g->offs.cslot = add(card_slot.data(), card_slot.size() * sizeof(unsigned short));
 
   g->img.assign(total, 0);
   for (const Piece& pc : pieces)
@@ -373,13 +452,6 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   g->dh.n_cards = nc;
   g->dh.n_card_slots = card_begin[nc] + nc;
   g->dh.invZ = 1.0 / Z;
-  EGT_HIP(hipGetDevice(&g->device));
-  EGT_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, g->device));
-  if (g->n_cu < 1) g->n_cu = 1;
-  EGT_HIP(hipDeviceGetAttribute(&g->lds_per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, g->device));
-  EGT_HIP(hipDeviceGetAttribute(&g->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device));
-  if (g->lds_per_block < 64 * 1024) g->lds_per_block = 64 * 1024;
-  if (g->lds_per_cu < g->lds_per_block) g->lds_per_cu = g->lds_per_block;
   g->fused_passes = fits_fused(g);
   return EGT_OK;
 }
@@ -592,7 +664,9 @@ int build_game_host(const egt_game_desc* d, egt_game** out) {
   if (!(Z > 0) || !std::isfinite(Z)) return fail(EGT_EINVAL, "no compatible deal has positive belief");
   g->Z = Z;
 
-  int rc = finish_image(g, card_begin, htab, hpos, b);
+  std::vector<unsigned short> card_slot;
+  for (const auto& L : lists) card_slot.insert(card_slot.end(), L.begin(), L.end());
+  int rc = finish_image(g, card_begin, htab, hpos, card_slot, b);
   if (rc) return rc;
   *out = guard.release();
   return EGT_OK;
@@ -703,7 +777,7 @@ int build_general_host(const egt_general_desc* d, egt_game** out) {
   const std::vector<int> card_begin = {0, 1};
   const std::vector<uint4> htab = {make_uint4(0u, 0u, 0u, 0u)};
   const std::vector<unsigned> hpos = {0u};
-  const int rc = finish_image(g, card_begin, htab, hpos, b);
+  const int rc = finish_image(g, card_begin, htab, hpos, {0}, b);
   if (rc) return rc;
   *out = guard.release();
   return EGT_OK;
@@ -741,6 +815,9 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.roots = (const int*)at(po[p].roots);
     dp.belief = (const double*)at(po[p].belief);
     dp.fused_tab = at(po[p].ftab);
+    dp.n_round_blocks = hp.rounds.empty() ? 0 : (int)hp.round_begin.size() - 1;
+    dp.rounds = hp.rounds.empty() ? nullptr : (const ProdRound*)at(po[p].rounds);
+    dp.round_begin = (const int*)at(po[p].rbeg);
     dp.seq_rec = (const SeqRec*)at(po[p].srec);
     dp.node_rec = (const NodeRec*)at(po[p].nrec);
     dp.term_rec = (const TermRec*)at(po[p].trec);
@@ -756,6 +833,7 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
   g->dh.card_begin = (const int*)at(g->offs.cbeg);
   g->dh.htab = (const uint4*)at(g->offs.htab);
   g->dh.hpos = (const unsigned*)at(g->offs.hpos);
+  g->dh.card_slot = (const unsigned short*)at(g->offs.cslot);
   return EGT_OK;
 }
 

@@ -94,6 +94,17 @@ struct TermItem {
   int pad[2];
 };
 
+// One round of the paired product kernel: a terminal of one kind of each of two
+// sequences (opponent's last sequence, -1 = empty; player 2's chips; the
+// sequence, -1 = none), and whether the two sequences end with it.
+struct ProdRound {
+  int opp[2];
+  int seq[2];
+  double coef[2];
+  int kind;  // 0 fold, 1 showdown, -1 no terminal: the two rows are zero
+  int last;
+};
+
 struct DPlayer {
   int n_seq;
   int n_nodes;
@@ -117,6 +128,9 @@ struct DPlayer {
   const int* anc;              // [n_seq][kMaxDepth] sequences on the path root -> s (s last), -1 after
   const TermRec* term_rec;     // [n_seq][term_stride] terminals of each sequence, padded with kind -1
   int term_stride;             // max terminals per sequence (>= 1)
+  const ProdRound* rounds;     // the paired product kernel's rounds, block by block, or null
+  const int* round_begin;      // [n_round_blocks + 1]
+  int n_round_blocks;
   const TermItem* term_items;  // [n_items] when every sequence has at most two terminals, else null
   int n_items;
   const int* seq_nact;         // [n_seq] number of actions of the sequence's decision node
@@ -150,6 +164,7 @@ struct DHands {
   const int* card_begin;       // [n_cards + 1]
   const uint4* htab;           // [n]
   const unsigned* hpos;        // [n]
+  const unsigned short* card_slot;  // [card_begin[n_cards]] the slots holding each card, ascending
   double invZ;                 // 1 / sum of b1 b2 over compatible deals
 };
 
@@ -236,6 +251,8 @@ struct HostPlayer {
   std::vector<NodeRec> node_rec;
   std::vector<TermRec> term_rec;         // [n_seq][max(1, max_terms_per_seq)]
   std::vector<TermItem> term_items;      // work items of the looping product kernel (at most two terminals each)
+  std::vector<ProdRound> rounds;         // rounds of the paired product kernel and their first per block
+  std::vector<int> round_begin;
   std::vector<int> anc;                  // [n_seq][kMaxDepth]
   std::vector<int> seq_nact;             // [n_seq] actions of the sequence's node
   std::vector<std::string> seq_keys;
@@ -254,9 +271,9 @@ struct DeviceBlock {  // one device allocation holding many tables
 struct GameOffsets {
   struct Player {
     size_t first, nact, beta, logn, spar, cbeg, child, tbeg, topp, tkind, tcoef, roots, belief, ftab, trec, anc,
-        titems, snact, sptr, scol, sval, srec, nrec;
+        titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
   } p[2];
-  size_t cbeg, htab, hpos;
+  size_t cbeg, htab, hpos, cslot;
 };
 
 // Scratch of the single-operation entry points (egt_smoothed_br,
@@ -326,6 +343,9 @@ namespace egt {
 // With absmax (device) every block also writes its largest |entry| there; *blocks
 // receives how many (at most absmax_capacity(g)).
 int absmax_capacity(const egt_game* g);
+// Blocks the paired product kernel runs with on this game's larger tree, or 0
+// when the other kernel is the better one (or this one cannot take the hands).
+int paired_product_blocks(const egt_game* g, const std::vector<int>& card_begin);
 hipError_t launch_spmv(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,
                        double* absmax = nullptr, int* blocks = nullptr);
 hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,

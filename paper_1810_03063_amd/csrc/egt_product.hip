@@ -396,6 +396,209 @@ __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdAr
   }
 }
 
+// Large trees: two terminals of one kind per round.
+//
+// A block is one wave group; a round takes a terminal of each of two sequences,
+// their reaches side by side in LDS as {first, second}, so that every index, LDS
+// instruction, bank conflict and barrier of the evaluation above serves both
+// (it is bound by LDS: of a showdown's 3,300 cycles of LDS pipe two thirds are
+// the evaluation's scattered reads).  A pair of sequences has its folds and
+// showdowns added by the same threads, with no second group to meet, and a fold
+// round forms only the totals.  The card lists are gathered from the strength
+// order (a thread's quarter of a list, at most kQR slots, sits in registers as
+// indices), so nothing is scattered.  Rounds are dealt to the blocks at build
+// (ProdRound), three blocks a compute unit.  5938 sequences: 1081 hands 51.9 ->
+// 42.7 us, 595 hands 40.8 -> 29.7, 351 hands 31.4 -> 19.3, 105 hands 24.5 ->
+// 14.6; now LDS and VALU are each busy a third of the time (counters), the rest
+// is the latency of a round's chain between barriers at 12 wavefronts per
+// compute unit, which its LDS and registers allow.
+// Every sum is the one product_kernel takes, in its order.
+struct RoundArgs {
+  DPlayer own;
+  const double* b_opp;
+  DHands H;
+  const double* v_opp;
+  double* out;
+  double show_sign;
+  double* absmax;  // MAX: each block's largest |entry|
+};
+
+__device__ inline double2 operator+(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ inline double2 operator-(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+
+template <int HPT, int MINW, bool MAX>
+__global__ __launch_bounds__(kGroupThreads, MINW) void product_pairs_kernel(RoundArgs a) {
+  extern __shared__ __align__(16) double2 lds2[];
+  __shared__ double2 wave_total[kGroupThreads / 64];
+  const int n = a.H.n, ld = a.H.ld, cph = a.H.cph;
+  double2* R = lds2;          // [n + 1] reach, then its exclusive prefix and total, in strength order
+  double2* E = lds2 + n + 1;  // [n_card_slots] exclusive prefixes and totals by card
+  const int gt = threadIdx.x, lane = gt & 63, wig = gt >> 6;
+  const int chunk = (n + kGroupThreads - 1) / kGroupThreads;
+  const int beg = min(gt * chunk, n), cnt = min(beg + chunk, n) - beg;
+
+  double bo[HPT];
+#pragma unroll
+  for (int k = 0; k < HPT; ++k) bo[k] = gt + k * kGroupThreads < n ? a.b_opp[gt + k * kGroupThreads] : 0.0;
+  // this thread's quarter of card gt / 4's list: slots, two to a word
+  const int card = gt >> 2, sub = gt & 3;
+  const bool has_card = card < a.H.n_cards;
+  const int cb = has_card ? a.H.card_begin[card] : 0, len = has_card ? a.H.card_begin[card + 1] - cb : 0;
+  const int qlen = (len + 3) >> 2, lo = min(sub * qlen, len), ql = min(lo + qlen, len) - lo;
+  unsigned slots[kQR / 2];
+#pragma unroll
+  for (int j = 0; j < kQR / 2; ++j) {
+    const unsigned s0 = 2 * j < ql ? a.H.card_slot[cb + lo + 2 * j] : 0u;
+    const unsigned s1 = 2 * j + 1 < ql ? a.H.card_slot[cb + lo + 2 * j + 1] : 0u;
+    slots[j] = s0 | (s1 << 16);
+  }
+  double2* L = E + cb + card;  // the card's list in E, its total behind
+
+  const ProdRound* rounds = a.own.rounds;
+  int ri = a.own.round_begin[blockIdx.x];
+  const int rend = a.own.round_begin[blockIdx.x + 1];
+  double v0[HPT], v1[HPT];
+  auto load_rows = [&](int r) {
+    const int o0 = rounds[r].opp[0], o1 = rounds[r].opp[1];
+    const double* p0 = o0 >= 0 ? a.v_opp + (size_t)o0 * ld : nullptr;
+    const double* p1 = o1 >= 0 ? a.v_opp + (size_t)o1 * ld : nullptr;
+#pragma unroll
+    for (int k = 0; k < HPT; ++k) {
+      const int i = gt + k * kGroupThreads;
+      v0[k] = (p0 && i < n) ? p0[i] : 1.0;
+      v1[k] = (p1 && i < n) ? p1[i] : 1.0;
+    }
+  };
+  if (ri < rend) load_rows(ri);
+  double2 acc[HPT];
+#pragma unroll
+  for (int k = 0; k < HPT; ++k) acc[k] = make_double2(0.0, 0.0);
+  double top = 0.0;  // MAX: this thread's largest |entry|
+  for (; ri < rend; ++ri) {
+    const ProdRound rd = rounds[ri];  // uniform
+    if (rd.kind >= 0) {
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) {
+        const int i = gt + k * kGroupThreads;
+        if (i < n) R[i] = make_double2(bo[k] * v0[k], bo[k] * v1[k]);
+      }
+    }
+    if (ri + 1 < rend) load_rows(ri + 1);  // in flight while this round runs
+    if (rd.kind >= 0) {
+      __syncthreads();
+      // per-card prefixes (folds: totals), the quarter totals by DPP within the
+      // card's quad
+      if (has_card) {
+        double2 part = make_double2(0.0, 0.0);
+        double2 v[kQR];
+#pragma unroll
+        for (int j = 0; j < kQR; j += 2) {
+          unsigned w = slots[j / 2];
+          asm volatile("" : "+v"(w));  // unpacked here each round: kept unpacked the indices would spill
+          v[j] = j < ql ? R[w & 0xffffu] : make_double2(0.0, 0.0);
+          v[j + 1] = j + 1 < ql ? R[w >> 16] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int j = 0; j < kQR; ++j)
+          if (j < ql) part = part + v[j];
+        const double2 p0 = make_double2(dpp_move<0x00, 0xf>(part.x), dpp_move<0x00, 0xf>(part.y));
+        const double2 p1 = make_double2(dpp_move<0x55, 0xf>(part.x), dpp_move<0x55, 0xf>(part.y));
+        const double2 p2 = make_double2(dpp_move<0xaa, 0xf>(part.x), dpp_move<0xaa, 0xf>(part.y));
+        double2 run = sub == 0 ? make_double2(0.0, 0.0) : sub == 1 ? p0 : sub == 2 ? p0 + p1 : (p0 + p1) + p2;
+#pragma unroll
+        for (int j = 0; j < kQR; ++j) {
+          if (j < ql) {
+            if (rd.kind == 1) L[lo + j] = run;
+            run = run + v[j];
+          }
+        }
+        if (sub == 3) L[len] = run;
+      }
+      __builtin_amdgcn_sched_barrier(0);  // what follows takes the lists' registers
+      // the index table from the cache, each round: it arrives behind the scan
+      uint4 ht[HPT];
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) ht[k] = k < cnt ? a.H.htab[beg + k] : make_uint4(0u, 0u, 0u, 0u);
+      // strength order: this thread's contiguous hands, and the group's scan
+      double2 rloc[HPT];
+      double2 local = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) rloc[k] = k < cnt ? R[beg + k] : make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) local = local + rloc[k];
+      const double2 incl = make_double2(wave_inclusive_scan(local.x), wave_inclusive_scan(local.y));
+      if (lane == 63) wave_total[wig] = incl;
+      __syncthreads();
+      {
+        double2 run = incl - local;
+        for (int q = 0; q < wig; ++q) run = run + wave_total[q];
+#pragma unroll
+        for (int k = 0; k < HPT; ++k) {
+          if (k < cnt) {
+            if (rd.kind == 1) R[beg + k] = run;
+            run = run + rloc[k];
+          }
+        }
+        if (cnt > 0 && beg + cnt == n) R[n] = run;
+      }
+      __syncthreads();
+      const double2 T = R[n];
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) {
+        if (k < cnt) {
+          const uint4 t = ht[k];
+          double2 op;
+          if (rd.kind == 0) {
+            op = T - E[t.y & 0xffffu];
+            if (cph == 2) op = op - E[t.z >> 16] + rloc[k];
+          } else {
+            double2 weaker = R[t.w & 0xffffu] - E[t.x & 0xffffu];
+            double2 stronger = (T - R[t.w >> 16]) - (E[t.y & 0xffffu] - E[t.x >> 16]);
+            if (cph == 2) {
+              weaker = weaker - E[t.y >> 16];
+              stronger = stronger - (E[t.z >> 16] - E[t.z & 0xffffu]);
+            }
+            op = stronger - weaker;
+            op.x = a.show_sign * op.x;
+            op.y = a.show_sign * op.y;
+          }
+          acc[k].x += rd.coef[0] * op.x;
+          acc[k].y += rd.coef[1] * op.y;
+        }
+      }
+      __syncthreads();  // the next round rewrites R and E
+    }
+    if (rd.last) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (rd.seq[j] < 0) continue;
+        double* row = a.out + (size_t)rd.seq[j] * ld;
+#pragma unroll
+        for (int k = 0; k < HPT; ++k) {
+          if (k < cnt) {
+            const double x = (j == 0 ? acc[k].x : acc[k].y) * (a.own.belief[beg + k] * a.H.invZ);
+            row[beg + k] = x;
+            if constexpr (MAX) top = fmax(top, fabs(x));
+          }
+        }
+        for (int i = n + gt; i < ld; i += kGroupThreads) row[i] = 0.0;
+      }
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) acc[k] = make_double2(0.0, 0.0);
+    }
+  }
+  if constexpr (MAX) {
+    top = wave_max(top);
+    __syncthreads();
+    if (lane == 0) wave_total[wig].x = top;
+    __syncthreads();
+    if (gt == 0) {
+      for (int v = 1; v < kGroupThreads / 64; ++v) top = fmax(top, wave_total[v].x);
+      a.absmax[blockIdx.x] = top;
+    }
+  }
+}
+
 // Precision form, fold terminals only (the BF16 GEMM adds the showdown
 // terminals' part afterwards), in FP32: one block per own sequence.  For each
 // fold terminal of the sequence the opponent's reach r(h') is staged into the
@@ -595,13 +798,49 @@ static hipError_t product_launch(const egt_game* g, int player, const TV* v_opp,
   return hipGetLastError();
 }
 
+// LDS of one block of the paired kernel.
+static size_t paired_lds(int n, int n_card_slots) { return sizeof(double2) * ((size_t)n + 1 + n_card_slots); }
+
+int paired_product_blocks(const egt_game* g, const std::vector<int>& card_begin) {
+  int longest = 0;
+  for (int c = 0; c < g->n_cards; ++c) longest = std::max(longest, card_begin[c + 1] - card_begin[c]);
+  // its registers hold five hands and a quarter list of kQR slots per thread, a
+  // card's quad is one of 64
+  if (g->n > 5 * kGroupThreads || longest > 4 * kQR || g->n_cards > kGroupThreads / 4) return 0;
+  // Few sequences leave a pair's fold and showdown waiting for each other in one
+  // block where two groups took them side by side: the kernels cross between
+  // 520 and 808 sequences (1081 hands: 9.7 against 11.7 us, then 13.5 against
+  // 12.3; 595 hands: 8.3 against 9.4, then 10.5 against 9.6).
+  const int seqs = std::min(g->hp[0].n_seq, g->hp[1].n_seq);
+  if (2 * seqs <= 5 * g->n_cu) return 0;
+  const size_t lds = paired_lds(g->n, card_begin[g->n_cards] + g->n_cards);
+  const int fit = (int)std::min<size_t>(g->n <= 2 * kGroupThreads ? 4 : 3, (size_t)g->lds_per_cu / (lds + 256));
+  return fit >= 2 ? fit * g->n_cu : 0;
+}
+
 int absmax_capacity(const egt_game* g) {
-  return std::max(2 * g->n_cu, (std::max(g->hp[0].n_seq, g->hp[1].n_seq) + 3) / 4);
+  return std::max(4 * g->n_cu, (std::max(g->hp[0].n_seq, g->hp[1].n_seq) + 3) / 4);
 }
 
 hipError_t launch_gradient(const egt_game* g, int player, const double* v_opp, double* grad_out, hipStream_t s,
                            double* absmax, int* blocks) {
   if (g->general) return launch_spmv(g, player, v_opp, grad_out, s, absmax, blocks);
+  const DPlayer& P = g->dp[player];
+  if (P.rounds) {
+    RoundArgs a{P, g->dp[1 - player].belief, g->dh, v_opp, grad_out, player == 0 ? 1.0 : -1.0, absmax};
+    if (blocks) *blocks = P.n_round_blocks;
+    const size_t lds = paired_lds(g->n, g->dh.n_card_slots);
+    const dim3 grid((unsigned)P.n_round_blocks), block(kGroupThreads);
+    if (g->n <= 2 * kGroupThreads && absmax)
+      hipLaunchKernelGGL((product_pairs_kernel<2, 4, true>), grid, block, lds, s, a);
+    else if (g->n <= 2 * kGroupThreads)
+      hipLaunchKernelGGL((product_pairs_kernel<2, 4, false>), grid, block, lds, s, a);
+    else if (absmax)
+      hipLaunchKernelGGL((product_pairs_kernel<5, 3, true>), grid, block, lds, s, a);
+    else
+      hipLaunchKernelGGL((product_pairs_kernel<5, 3, false>), grid, block, lds, s, a);
+    return hipGetLastError();
+  }
   return product_launch<double, double>(g, player, v_opp, grad_out, s, absmax, blocks);
 }
 
