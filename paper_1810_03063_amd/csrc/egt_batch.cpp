@@ -51,7 +51,7 @@ struct Slot {
   const egt_game* g = nullptr;
   egt_game* own_game = nullptr;  // admitted by description: the batch's, tables in the arena
   std::vector<unsigned char> mx_img;  // its precision-form tables, uploaded by the worker
-  size_t mx_off[2][4] = {};
+  egt::MixedOffsets mx_off{};
   int64_t game_bytes = 0, mx_bytes = 0;  // arena bytes ahead of the state
   egt_solve_opts opts{};
   egt_state* st = nullptr;
@@ -316,8 +316,8 @@ int egt_batch_admit_desc(egt_batch* b, const egt_game_desc* desc, const egt_solv
   int rc = build_game_host(desc, &g);
   if (rc) return rc;
   std::vector<unsigned char> mx_img;
-  size_t mx_off[2][4] = {};
-  if (mixed && (rc = mixed_tables_image(g, mx_img, mx_off))) {
+  MixedOffsets mx_off{};
+  if (mixed && (rc = mixed_tables_image(g, mx_img, &mx_off))) {
     free_game(g);
     return rc;
   }
@@ -337,7 +337,7 @@ int egt_batch_admit_desc(egt_batch* b, const egt_game_desc* desc, const egt_solv
   sl.g = g;
   sl.own_game = g;
   sl.mx_img.swap(mx_img);
-  std::memcpy(sl.mx_off, mx_off, sizeof(mx_off));
+  sl.mx_off = mx_off;
   sl.game_bytes = gbytes;
   sl.mx_bytes = mbytes;
   sl.opts = o;

@@ -442,6 +442,10 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   g->offs.htab = add(htab.data(), htab.size() * sizeof(uint4));
   g->offs.hpos = add(hpos.data(), hpos.size() * sizeof(unsigned));
   g->offs.cslot = add(card_slot.data(), card_slot.size() * sizeof(unsigned short));
+  std::vector<unsigned> hand_cards(n);
+  for (int i = 0; i < n; ++i)
+    hand_cards[i] = (unsigned)g->slot_cards[(size_t)i * cph] | (cph == 2 ? (unsigned)g->slot_cards[(size_t)i * cph + 1] << 16 : 0u);
+  g->offs.hcard = add(hand_cards.data(), hand_cards.size() * sizeof(unsigned));
 
   g->img.assign(total, 0);
   for (const Piece& pc : pieces)
@@ -834,6 +838,7 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
   g->dh.htab = (const uint4*)at(g->offs.htab);
   g->dh.hpos = (const unsigned*)at(g->offs.hpos);
   g->dh.card_slot = (const unsigned short*)at(g->offs.cslot);
+  g->dh.hand_cards = (const unsigned*)at(g->offs.hcard);
   return EGT_OK;
 }
 

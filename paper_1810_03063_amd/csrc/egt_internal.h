@@ -165,6 +165,7 @@ struct DHands {
   const uint4* htab;           // [n]
   const unsigned* hpos;        // [n]
   const unsigned short* card_slot;  // [card_begin[n_cards]] the slots holding each card, ascending
+  const unsigned* hand_cards;       // [n] the hand's cards a | b << 16
   double invZ;                 // 1 / sum of b1 b2 over compatible deals
 };
 
@@ -237,7 +238,6 @@ enum Prec { kF64 = 0, kF32 = 1 };
 // ---------------------------------------------------------------------------
 struct HostPlayer {
   int n_seq = 0, n_nodes = 0, n_levels = 0, max_chain = 0, max_terms_per_seq = 0, max_level_width = 0;
-  int n_show_cols = 0;  // showdown columns of the precision form (set when its tables are built)
   std::vector<int> node_first_seq, node_nact, node_level;
   std::vector<double> node_beta, node_logn;
   std::vector<int> level_begin;  // [n_levels + 1]
@@ -273,7 +273,7 @@ struct GameOffsets {
     size_t first, nact, beta, logn, spar, cbeg, child, tbeg, topp, tkind, tcoef, roots, belief, ftab, trec, anc,
         titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
   } p[2];
-  size_t cbeg, htab, hpos, cslot;
+  size_t cbeg, htab, hpos, cslot, hcard;
 };
 
 // Scratch of the single-operation entry points (egt_smoothed_br,
@@ -290,18 +290,45 @@ struct Workspace {
   double* hpart_dev = nullptr;
 };
 
+// One round of the precision form's fold kernel: a fold terminal of each of one or
+// four sequences (fields as ProdRound); bit j of `add`: sequence j's row already holds
+// its showdown.
+struct FoldRound {
+  int opp[4];
+  int seq[4];
+  float coef[4];
+  int kind;  // 0 fold, -1 no terminal: zero rows
+  int add;
+  int last;
+  int pad;
+};
+
+// Where the pieces of a precision-form table image lie, per player.
+struct MixedOffsets {
+  struct Player {
+    size_t own, opp, coef, b32, folds;
+    int n_show, n_folds, fold_width;
+  } p[2];
+  bool by_columns;
+};
+
 // Precision-form tables (built on first use): W in BF16 bits over the slot
-// order, padded to kpad x kpad, and per player the showdown columns.
+// order, padded to kpad x kpad, per player the showdown columns and the fold
+// rounds.
 struct MixedTables {
   void* block = nullptr;
   bool owned = true;  // false: the block lies in a serving batch's arena
   int kpad = 0;
   const unsigned short* W = nullptr;
+  bool by_columns = false;  // W in the operand order of the column-block GEMM, which both players take
   int L[2] = {0, 0};
   const int* col_own[2] = {nullptr, nullptr};
   const int* col_opp[2] = {nullptr, nullptr};
   const double* col_coef[2] = {nullptr, nullptr};
   const float* belief32[2] = {nullptr, nullptr};  // [ld] each player's prior in FP32
+  const FoldRound* folds[2] = {nullptr, nullptr};
+  int n_folds[2] = {0, 0};
+  int fold_width[2] = {1, 1};  // sequences per fold round
 };
 
 }  // namespace egt
@@ -407,19 +434,19 @@ hipError_t launch_axpby(int64_t count, double a, const void* X, double b, const 
 // out = in converted FP32 -> FP64 (in_prec kF32) or FP64 -> FP32 (in_prec kF64).
 hipError_t launch_convert(int64_t count, const void* in, Prec in_prec, void* out, hipStream_t s);
 
-// Fold part of the product in FP32 for the precision form: like
-// launch_gradient, but showdown terminals are skipped (their contribution is
-// added by launch_show_gemm) and vectors are FP32.
+// Fold part of the product in FP32 for the precision form, after
+// launch_show_gemm: added to the rows that have a showdown, written to the others.
 hipError_t launch_gradient_fold_f32(const egt_game* g, int player, const float* v_opp, float* grad_out,
                                     hipStream_t s);
 
-// Precision form: W and the showdown columns (once per game); the product
-// fold part (FP32 O(n)) + showdown part (BF16 hi/lo MFMA GEMM, FP32 output).
+// Precision form: W, the showdown columns and the fold rounds (once per game);
+// the product: showdown part (BF16 hi/lo MFMA GEMM, FP32 output) + fold part
+// (FP32 O(n)).
 int ensure_mixed_tables(const egt_game* g);
 // The same tables as a host image (no device work): its size, then the upload
 // into caller memory (owned = false: the memory is not the game's to free).
-int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, size_t off[2][4]);
-int mixed_tables_upload(egt_game* g, const std::vector<unsigned char>& img, const size_t off[2][4], void* dev,
+int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, MixedOffsets* off);
+int mixed_tables_upload(egt_game* g, const std::vector<unsigned char>& img, const MixedOffsets& off, void* dev,
                         bool owned, hipStream_t s);
 hipError_t launch_show_gemm(const egt_game* g, int player, const float* v_opp, float* grad_out, hipStream_t s);
 hipError_t launch_gradient_mixed(const egt_game* g, int player, const float* v_opp, float* grad_out, hipStream_t s);

@@ -10,11 +10,10 @@
 // showdown columns r_z form Y (n x L), and C = W Y is computed as
 // W Y_hi + W Y_lo with Y_hi = bf16(Y) and Y_lo = bf16(Y - Y_hi): W is exact in
 // BF16, each BF16 x BF16 product is exact in FP32, the accumulation is FP32.
-// The fold terminals keep their O(n) per-card evaluation (in FP32) in
-// launch_gradient_fold_f32, which also zeroes the other rows; the
-// GEMM epilogue then adds the showdown part.  Each own sequence has at most
-// one showdown terminal (checked when the tables are built), so every output
-// element is updated by exactly one lane.
+// Each own sequence has at most one showdown terminal (checked when the tables
+// are built), so the GEMM writes every element of a row it has; the fold
+// terminals keep their O(n) per-card evaluation (in FP32) in
+// launch_gradient_fold_f32, which then adds to those rows and writes the others.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,6 +28,7 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 mfma_bf16x8;
 
 constexpr int kTile = 32;     // output hands x showdown columns per block (one 32x32 MFMA tile)
 constexpr int kKWaves = 16;   // waves per block, each contracting every 16th k-step of 16 hands
@@ -68,7 +68,7 @@ struct GemmArgs {
   const double* b_own;      // [ld]
   double scale;             // sign / Z
   const float* v_opp;       // opponent strategy [S_o][ld]
-  float* out;               // own gradient [S_own][ld], fold part already written
+  float* out;               // own gradient [S_own][ld]
 };
 
 // One 32 x 32 output tile (hands m0.., columns n0..) per block.  The k-steps
@@ -143,13 +143,13 @@ __global__ __launch_bounds__(64 * kKWaves) void show_gemm_kernel(GemmArgs a) {
   __syncthreads();
   // one lane per output element: hands fastest, so each row is written coalesced
   const int h = m0 + (tid & 31), cl = tid >> 5, j = n0 + cl;
-  if (j < a.L && h < a.n) {
+  if (j < a.L) {  // a row's padding has prior 0
     float sum = 0.0f;
 #pragma unroll
     for (int w = 0; w < kKWaves; ++w) sum += red[(w * kTile + cl) * kRedStride + (tid & 31)];
     const double c = a.col_coef[j] * a.scale;
     float* row = a.out + (size_t)a.col_own[j] * a.ld;
-    row[h] += (float)(c * a.b_own[h] * (double)sum);
+    row[h] = (float)(c * a.b_own[h] * (double)sum);
   }
 }
 
@@ -303,51 +303,218 @@ __global__ __launch_bounds__(256) void show_gemm_tiled_kernel(GemmArgs a) {
       ct[col * kTCS + row] = acc_hi[c][r] + acc_lo[c][r];
     }
   __syncthreads();
-  // Each thread updates one hand in kEpi columns per pass, with every load of
-  // a pass issued before its first store (a store could alias a later load,
-  // so the compiler would otherwise serialise the read-modify-writes).
-  constexpr int kEpi = 16;
+  // each thread writes one hand of every second column
   constexpr int kColsPerSweep = 256 / kTM;  // columns covered by one sweep of the threads
   const int row = tid % kTM, h = m0 + row;
-  const bool hok = h < a.n;
-  const double bo = hok ? a.b_own[h] : 0.0;
-#pragma unroll 1
-  for (int pass = 0; pass < kTN / (kColsPerSweep * kEpi); ++pass) {
-    int own[kEpi];
-    double cf[kEpi];
+  if (h >= a.ld) return;
+  const double bo = a.b_own[h];  // 0 in the padding
+#pragma unroll 4
+  for (int col = tid / kTM; col < kTN; col += kColsPerSweep) {
+    const int j = n0 + col;
+    if (j >= a.L) break;
+    const double c = a.col_coef[j] * a.scale;
+    a.out[(size_t)a.col_own[j] * a.ld + h] = (float)(c * bo * (double)ct[col * kTCS + row]);
+  }
+}
+
+// Many columns and at most kColsMaxLd hands: a block per 32 columns and part of
+// the hands, no barrier in the contraction.
+//
+// The tiled form above moves every operand through LDS in 34 steps with a
+// barrier each and splits each reach nine times (once per row block); its MFMA
+// pipes were busy 16% of the time.  Here the block forms the reaches of its 32
+// columns once, for all opponent hands, and keeps them in LDS as BF16 hi and lo
+// (32 columns x 1088 hands x 4 bytes = 139 KB of the 160); each of its 12
+// wavefronts owns MT tiles of 16 hands and runs over K on its own: its W
+// operands come straight from L2 in the order the instruction takes them (W is
+// stored that way: 1 KB contiguous per 16 hands x 32), two steps ahead in
+// registers, the reaches from LDS.  MT is the smallest for which a block per
+// compute unit is enough (3958 columns x 1088 hands: MT = 3, 248 blocks).
+// That product: 51.0 -> 28.9 us, of which 13 in the contraction (8.3 at the MFMA
+// peak) and 5 forming the reaches.
+// Operand layouts of v_mfma_f32_16x16x32_bf16 (lane l, element e < 8):
+//   A[l % 16][8 (l / 16) + e], B[8 (l / 16) + e][l % 16];
+//   accumulator r: row 4 (l / 16) + r, column l % 16.
+// LDS holds 16-byte units of 8 hands of a column at kc * 32 + (column ^ (kc % 8)),
+// kc = hand / 8: writes (consecutive kc of a column) and reads (16 columns of a
+// kc) both spread over the banks.
+constexpr int kColsBlock = 32, kColsWaves = 12;
+// from this many columns on; below, the K-split form has more wavefronts at work
+// (1081 hands, whole product: 149 columns 18.2 against 15.9 us, 347 columns 19.0
+// against 26.0)
+constexpr int kColsMinColumns = 256;
+constexpr int kColsMaxLd = 1216;  // the reaches of a block fit LDS
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+
+size_t cols_lds_bytes(int ld) { return (size_t)kColsBlock * ld * 4; }
+
+template <int MT>
+__global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(GemmArgs a, int parts) {
+  extern __shared__ __align__(16) uint4 bsm[];
+  const int nk8 = a.ld / 8, nks = a.ld / 32;
+  uint4* Bh = bsm;                     // [nk8][32] reach hi
+  uint4* Bl = bsm + kColsBlock * nk8;  // reach lo
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n0 = ((int)blockIdx.x / parts) * kColsBlock, part = (int)blockIdx.x % parts;
+  // the block's reaches
+  constexpr int kU = 3;  // units in flight per thread
+  const int total = kColsBlock * nk8;
+  for (int base = tid; base < total; base += 64 * kColsWaves * kU) {
+    float4 v[kU][2], b[kU][2];
+    int at[kU];
 #pragma unroll
-    for (int u = 0; u < kEpi; ++u) {
-      const int j = n0 + tid / kTM + kColsPerSweep * (pass * kEpi + u);
-      own[u] = -1;
-      cf[u] = 0.0;
-      if (hok && j < a.L) {
-        own[u] = a.col_own[j];
-        cf[u] = a.col_coef[j];
+    for (int u = 0; u < kU; ++u) {
+      const int i = base + u * 64 * kColsWaves;
+      const int col = i / nk8, kc = i - col * nk8, j = n0 + col;
+      at[u] = i < total ? kc * kColsBlock + (col ^ (kc & 7)) : -1;
+      const bool ok = i < total && j < a.L;
+      const float fill = ok ? 1.0f : 0.0f;  // the empty sequence has v = 1; no column has reach 0
+      v[u][0] = v[u][1] = make_float4(fill, fill, fill, fill);
+      b[u][0] = b[u][1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (ok) {
+        const int o = a.col_opp[j];
+        if (o >= 0) {
+          const float4* p = (const float4*)(a.v_opp + (size_t)o * a.ld + 8 * kc);
+          v[u][0] = p[0];
+          v[u][1] = p[1];
+        }
+        const float4* q = (const float4*)(a.b_opp32 + 8 * kc);
+        b[u][0] = q[0];
+        b[u][1] = q[1];
       }
     }
-    float cur[kEpi];
 #pragma unroll
-    for (int u = 0; u < kEpi; ++u) cur[u] = own[u] >= 0 ? a.out[(size_t)own[u] * a.ld + h] : 0.0f;
+    for (int u = 0; u < kU; ++u) {
+      if (at[u] < 0) continue;
+      const float4 b0 = b[u][0], b1 = b[u][1], v0 = v[u][0], v1 = v[u][1];
+      const float r[8] = {b0.x * v0.x, b0.y * v0.y, b0.z * v0.z, b0.w * v0.w,
+                          b1.x * v1.x, b1.y * v1.y, b1.z * v1.z, b1.w * v1.w};
+      bf16x8 hi, lo;
+      split8(r, hi, lo);
+      Bh[at[u]] = __builtin_bit_cast(uint4, hi);
+      Bl[at[u]] = __builtin_bit_cast(uint4, lo);
+    }
+  }
+  __syncthreads();
+  const int n_rt = a.ld / 16, rt0 = (part * kColsWaves + wave) * MT;
+  if (rt0 >= n_rt) return;
+  // W in operand order: [row tile][k step][lane], 16 bytes each; tiles past the
+  // last one repeat it and are not written
+  const uint4* A[MT];
 #pragma unroll
-    for (int u = 0; u < kEpi; ++u) {
-      if (own[u] < 0) continue;
-      const int col = tid / kTM + kColsPerSweep * (pass * kEpi + u);
-      const double c = cf[u] * a.scale;
-      a.out[(size_t)own[u] * a.ld + h] = cur[u] + (float)(c * bo * (double)ct[col * kTCS + row]);
+  for (int t = 0; t < MT; ++t) A[t] = (const uint4*)a.W + (size_t)min(rt0 + t, n_rt - 1) * nks * 64 + lane;
+  f32x4 hi[MT][2], lo[MT][2];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) hi[t][c] = lo[t][c] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int kAhead = 2;  // W steps in flight
+  uint4 w[kAhead + 1][MT];
+#pragma unroll
+  for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) w[q][t] = A[t][(size_t)min(q, nks - 1) * 64];
+  for (int ks0 = 0; ks0 < nks; ks0 += kAhead + 1) {
+#pragma unroll
+    for (int q = 0; q < kAhead + 1; ++q) {
+      const int ks = ks0 + q;
+      if (ks >= nks) break;
+      const int kn = min(ks + kAhead, nks - 1);
+#pragma unroll
+      for (int t = 0; t < MT; ++t) w[(q + kAhead) % (kAhead + 1)][t] = A[t][(size_t)kn * 64];
+      const int kc = 4 * ks + (lane >> 4), col = lane & 15;
+      const uint4* bh = Bh + kc * kColsBlock;
+      const uint4* bl = Bl + kc * kColsBlock;
+      const int c0 = col ^ (kc & 7), c1 = (16 + col) ^ (kc & 7);
+      const mfma_bf16x8 h0 = __builtin_bit_cast(mfma_bf16x8, bh[c0]), h1 = __builtin_bit_cast(mfma_bf16x8, bh[c1]);
+      const mfma_bf16x8 l0 = __builtin_bit_cast(mfma_bf16x8, bl[c0]), l1 = __builtin_bit_cast(mfma_bf16x8, bl[c1]);
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        const mfma_bf16x8 am = __builtin_bit_cast(mfma_bf16x8, w[q][t]);
+        hi[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, h0, hi[t][0], 0, 0, 0);
+        hi[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, h1, hi[t][1], 0, 0, 0);
+        lo[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, l0, lo[t][0], 0, 0, 0);
+        lo[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, l1, lo[t][1], 0, 0, 0);
+      }
+    }
+  }
+  // every element of a row has one writer; the padding has prior 0
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int j = n0 + 16 * c + (lane & 15);
+    if (j >= a.L) continue;
+    const double cf = a.col_coef[j] * a.scale;
+    float* row = a.out + (size_t)a.col_own[j] * a.ld;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      if (rt0 + t >= n_rt) continue;
+      const int h = 16 * (rt0 + t) + 4 * (lane >> 4);
+      float x[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[r] = (float)(cf * a.b_own[h + r] * (double)(hi[t][c][r] + lo[t][c][r]));
+      *(float4*)(row + h) = make_float4(x[0], x[1], x[2], x[3]);
     }
   }
 }
 
 }  // namespace
 
-// W (BF16 bits) and the per-player showdown column lists as one host image:
-// W at 0, then per player the FP32 prior (off[p][3]) and the column lists
-// (own sequence off[p][0], opponent sequence off[p][1], chips off[p][2]).
-int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, size_t off[2][4]) {
+// W (BF16 bits; in the column-block GEMM's operand order when both players take
+// it), and per player the FP32 prior, the showdown column lists and the fold
+// rounds, as one host image: W at 0, the rest at `off`.
+int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, MixedOffsets* off) {
   if (g->general) return fail(EGT_EINVAL, "the precision form needs a river endgame");
   const int n = g->n;
   const int kpad = g->ld;  // rows and columns padded like every vector
+  std::vector<int> own[2], opp[2];
+  std::vector<double> coef[2];
+  std::vector<FoldRound> folds[2];
+  for (int p = 0; p < 2; ++p) {
+    const HostPlayer& hp = g->hp[p];
+    std::vector<std::vector<int>> by_folds;  // by_folds[k]: sequences with k fold terminals
+    std::vector<char> has_show(hp.n_seq, 0);
+    for (int s = 0; s < hp.n_seq; ++s) {
+      int shows = 0, nf = 0;
+      for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t) {
+        if (hp.term_kind[t] != 1) {
+          ++nf;
+          continue;
+        }
+        if (++shows > 1) return fail(EGT_EINVAL, "precision form needs at most one showdown per sequence");
+        own[p].push_back(s);
+        opp[p].push_back(hp.term_opp[t]);
+        coef[p].push_back(hp.term_coef[t]);
+      }
+      has_show[s] = shows > 0;
+      if (nf == 0 && shows > 0) continue;  // the GEMM writes the row
+      if ((int)by_folds.size() <= nf) by_folds.resize(nf + 1);
+      by_folds[nf].push_back(s);
+    }
+    // sequences with the same number of folds, four at a time where one each
+    // would be more than four blocks per compute unit
+    const size_t w = hp.n_seq > 4 * g->n_cu ? 4 : 1;
+    off->p[p].fold_width = (int)w;
+    for (size_t nf = 0; nf < by_folds.size(); ++nf)
+      for (size_t i = 0; i < by_folds[nf].size(); i += w)
+        for (size_t k = 0; k < std::max<size_t>(nf, 1); ++k) {
+          FoldRound r{{-1, -1, -1, -1}, {-1, -1, -1, -1}, {0.0f, 0.0f, 0.0f, 0.0f}, nf ? 0 : -1, 0, k + 1 >= nf, 0};
+          for (size_t j = 0; j < w && i + j < by_folds[nf].size(); ++j) {
+            const int s = by_folds[nf][i + j];
+            r.seq[j] = s;
+            if (has_show[s]) r.add |= 1 << j;
+            size_t seen = 0;
+            for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t)
+              if (hp.term_kind[t] == 0 && seen++ == k) {
+                r.opp[j] = hp.term_opp[t];
+                r.coef[j] = (float)hp.term_coef[t];
+              }
+          }
+          folds[p].push_back(r);
+        }
+  }
   // slot order: strength ascending; compatibility from the cards of the slots
+  off->by_columns = kpad <= kColsMaxLd && (int)own[0].size() >= kColsMinColumns && (int)own[1].size() >= kColsMinColumns;
   std::vector<unsigned short> W((size_t)kpad * kpad, 0);
   for (int i = 0; i < n; ++i) {
     for (int k = 0; k < n; ++k) {
@@ -357,70 +524,71 @@ int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, size_
           if (g->slot_cards[(size_t)i * g->cph + x] == g->slot_cards[(size_t)k * g->cph + y]) share = true;
       if (share) continue;
       const int si = g->slot_strength[i], sk = g->slot_strength[k];
-      W[(size_t)i * kpad + k] = sk > si ? 0x3F80 : (sk < si ? 0xBF80 : 0);
-    }
-  }
-  std::vector<int> own[2], opp[2];
-  std::vector<double> coef[2];
-  for (int p = 0; p < 2; ++p) {
-    const HostPlayer& hp = g->hp[p];
-    for (int s = 0; s < hp.n_seq; ++s) {
-      int shows = 0;
-      for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t) {
-        if (hp.term_kind[t] != 1) continue;
-        if (++shows > 1) return fail(EGT_EINVAL, "precision form needs at most one showdown per sequence");
-        own[p].push_back(s);
-        opp[p].push_back(hp.term_opp[t]);
-        coef[p].push_back(hp.term_coef[t]);
-      }
+      const size_t at = !off->by_columns ? (size_t)i * kpad + k
+                                         : (((size_t)(i / 16) * (kpad / 32) + k / 32) * 64 + k % 32 / 8 * 16 + i % 16) * 8 + k % 8;
+      W[at] = sk > si ? 0x3F80 : (sk < si ? 0xBF80 : 0);
     }
   }
   // FP32 copies of the priors (the reach b v is formed in FP32)
   std::vector<float> b32[2];
   for (int p = 0; p < 2; ++p) b32[p].assign(g->hbelief[p].begin(), g->hbelief[p].end());
-  auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t wbytes = sizeof(unsigned short) * W.size();
-  size_t total = al(wbytes);
+  size_t total = 0;
+  auto add = [&](size_t bytes) {
+    const size_t at = total;
+    total += (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
+    return at;
+  };
+  add(sizeof(unsigned short) * W.size());
   for (int p = 0; p < 2; ++p) {
-    off[p][3] = total;
-    total += al(sizeof(float) * b32[p].size());
-  }
-  for (int p = 0; p < 2; ++p) {
-    off[p][0] = total;
-    total += al(sizeof(int) * std::max<size_t>(own[p].size(), 1));
-    off[p][1] = total;
-    total += al(sizeof(int) * std::max<size_t>(opp[p].size(), 1));
-    off[p][2] = total;
-    total += al(sizeof(double) * std::max<size_t>(coef[p].size(), 1));
+    MixedOffsets::Player& o = off->p[p];
+    o.b32 = add(sizeof(float) * b32[p].size());
+    o.own = add(sizeof(int) * own[p].size());
+    o.opp = add(sizeof(int) * opp[p].size());
+    o.coef = add(sizeof(double) * coef[p].size());
+    o.folds = add(sizeof(FoldRound) * folds[p].size());
+    o.n_show = (int)own[p].size();
+    o.n_folds = (int)folds[p].size();
   }
   img.assign(total, 0);
-  std::memcpy(img.data(), W.data(), wbytes);
+  auto put = [&](size_t at, const void* src, size_t bytes) {
+    if (bytes) std::memcpy(img.data() + at, src, bytes);
+  };
+  put(0, W.data(), sizeof(unsigned short) * W.size());
   for (int p = 0; p < 2; ++p) {
-    std::memcpy(img.data() + off[p][3], b32[p].data(), sizeof(float) * b32[p].size());
-    if (!own[p].empty()) {
-      std::memcpy(img.data() + off[p][0], own[p].data(), sizeof(int) * own[p].size());
-      std::memcpy(img.data() + off[p][1], opp[p].data(), sizeof(int) * opp[p].size());
-      std::memcpy(img.data() + off[p][2], coef[p].data(), sizeof(double) * coef[p].size());
-    }
+    const MixedOffsets::Player& o = off->p[p];
+    put(o.b32, b32[p].data(), sizeof(float) * b32[p].size());
+    put(o.own, own[p].data(), sizeof(int) * own[p].size());
+    put(o.opp, opp[p].data(), sizeof(int) * opp[p].size());
+    put(o.coef, coef[p].data(), sizeof(double) * coef[p].size());
+    put(o.folds, folds[p].data(), sizeof(FoldRound) * folds[p].size());
   }
-  for (int p = 0; p < 2; ++p) const_cast<egt_game*>(g)->hp[p].n_show_cols = (int)own[p].size();
   return EGT_OK;
 }
 
-int mixed_tables_upload(egt_game* g, const std::vector<unsigned char>& img, const size_t off[2][4], void* dev,
-                        bool owned, hipStream_t s) {
-  EGT_HIP(hipMemcpyAsync(dev, img.data(), img.size(), hipMemcpyHostToDevice, s));
+static void point_mixed_tables(egt_game* g, const MixedOffsets& off, void* dev, bool owned) {
+  const unsigned char* base = (const unsigned char*)dev;
   g->mx.kpad = g->ld;
   g->mx.W = (const unsigned short*)dev;
+  g->mx.by_columns = off.by_columns;
   for (int p = 0; p < 2; ++p) {
-    g->mx.L[p] = g->hp[p].n_show_cols;
-    g->mx.col_own[p] = (const int*)((unsigned char*)dev + off[p][0]);
-    g->mx.col_opp[p] = (const int*)((unsigned char*)dev + off[p][1]);
-    g->mx.col_coef[p] = (const double*)((unsigned char*)dev + off[p][2]);
-    g->mx.belief32[p] = (const float*)((unsigned char*)dev + off[p][3]);
+    const MixedOffsets::Player& o = off.p[p];
+    g->mx.L[p] = o.n_show;
+    g->mx.col_own[p] = (const int*)(base + o.own);
+    g->mx.col_opp[p] = (const int*)(base + o.opp);
+    g->mx.col_coef[p] = (const double*)(base + o.coef);
+    g->mx.belief32[p] = (const float*)(base + o.b32);
+    g->mx.folds[p] = (const FoldRound*)(base + o.folds);
+    g->mx.n_folds[p] = o.n_folds;
+    g->mx.fold_width[p] = o.fold_width;
   }
   g->mx.owned = owned;
   g->mx.block = dev;
+}
+
+int mixed_tables_upload(egt_game* g, const std::vector<unsigned char>& img, const MixedOffsets& off, void* dev,
+                        bool owned, hipStream_t s) {
+  EGT_HIP(hipMemcpyAsync(dev, img.data(), img.size(), hipMemcpyHostToDevice, s));
+  point_mixed_tables(g, off, dev, owned);
   return EGT_OK;
 }
 
@@ -430,8 +598,8 @@ int ensure_mixed_tables(const egt_game* cg) {
   egt_game* g = const_cast<egt_game*>(cg);  // cached tables owned by the game
   if (g->mx.block) return EGT_OK;
   std::vector<unsigned char> img;
-  size_t off[2][4];
-  int rc = mixed_tables_image(g, img, off);
+  MixedOffsets off{};
+  int rc = mixed_tables_image(g, img, &off);
   if (rc) return rc;
   void* dev = nullptr;
   hipError_t e = hipMalloc(&dev, img.size());
@@ -441,18 +609,7 @@ int ensure_mixed_tables(const egt_game* cg) {
     (void)hipFree(dev);
     return hip_fail(e, "upload of precision tables");
   }
-  // the image is on the device now: point the tables at it (no second copy)
-  g->mx.kpad = g->ld;
-  g->mx.W = (const unsigned short*)dev;
-  for (int p = 0; p < 2; ++p) {
-    g->mx.L[p] = g->hp[p].n_show_cols;
-    g->mx.col_own[p] = (const int*)((unsigned char*)dev + off[p][0]);
-    g->mx.col_opp[p] = (const int*)((unsigned char*)dev + off[p][1]);
-    g->mx.col_coef[p] = (const double*)((unsigned char*)dev + off[p][2]);
-    g->mx.belief32[p] = (const float*)((unsigned char*)dev + off[p][3]);
-  }
-  g->mx.owned = true;
-  g->mx.block = dev;
+  point_mixed_tables(g, off, dev, true);
   return EGT_OK;
 }
 
@@ -472,6 +629,23 @@ hipError_t launch_show_gemm(const egt_game* g, int player, const float* v_opp, f
   a.scale = (player == 0 ? 1.0 : -1.0) / g->Z;
   a.v_opp = v_opp;
   a.out = grad_out;
+  if (m.by_columns) {
+    const int col_blocks = (a.L + kColsBlock - 1) / kColsBlock, n_rt = g->ld / 16;
+    const size_t lds = cols_lds_bytes(g->ld);
+    // blocks a compute unit holds: LDS, and two blocks' wavefronts
+    const int fit = g->n_cu * std::max(1, std::min(2, (int)((size_t)g->lds_per_cu / lds)));
+    auto parts_of = [&](int mt) { return (n_rt + kColsWaves * mt - 1) / (kColsWaves * mt); };
+    int mt = 1;
+    while (mt < 3 && col_blocks * parts_of(mt) > fit) ++mt;
+    const dim3 grid((unsigned)(col_blocks * parts_of(mt))), block(64 * kColsWaves);
+    if (mt == 1)
+      hipLaunchKernelGGL(show_gemm_cols_kernel<1>, grid, block, lds, s, a, parts_of(1));
+    else if (mt == 2)
+      hipLaunchKernelGGL(show_gemm_cols_kernel<2>, grid, block, lds, s, a, parts_of(2));
+    else
+      hipLaunchKernelGGL(show_gemm_cols_kernel<3>, grid, block, lds, s, a, parts_of(3));
+    return hipGetLastError();
+  }
   if (a.L >= kTiledMinColumns) {
     // enough columns for operand reuse to pay: the tiled form
     const unsigned tiles = (unsigned)(((a.L + kTN - 1) / kTN) * ((g->ld + kTM - 1) / kTM));
@@ -484,9 +658,9 @@ hipError_t launch_show_gemm(const egt_game* g, int player, const float* v_opp, f
 }
 
 hipError_t launch_gradient_mixed(const egt_game* g, int player, const float* v_opp, float* grad_out, hipStream_t s) {
-  hipError_t e = launch_gradient_fold_f32(g, player, v_opp, grad_out, s);
+  hipError_t e = launch_show_gemm(g, player, v_opp, grad_out, s);
   if (e != hipSuccess) return e;
-  return launch_show_gemm(g, player, v_opp, grad_out, s);
+  return launch_gradient_fold_f32(g, player, v_opp, grad_out, s);
 }
 
 }  // namespace egt
