@@ -8,9 +8,10 @@
 //    mu = 0 gives the best response;
 //  * the same steps one level per launch for large trees:
 //    bottom_up_leaf_pair_kernel (lowest level) or bottom_up_level_kernel
-//    (its one-hand-per-lane form), bottom_up_internal_kernel (levels with
-//    children, a wavefront per action, at most 8), root_sums_kernel, and
-//    top_down_pair_kernel or top_down_kernel;
+//    (its one-hand-per-lane form), bottom_up_wide_kernel (levels of many nodes
+//    with children, a wavefront per node) or bottom_up_internal_kernel (of few,
+//    a wavefront per action, at most 8), top_down_kernel, and root_sums_kernel
+//    where no top-down pass takes the root sums along;
 //  * small helpers (uniform point, a*x + b*y, max |x|).
 //
 // Every vector is double[rows][ld], hands (slots) fastest, so consecutive
@@ -30,6 +31,8 @@ namespace egt {
 namespace {
 
 constexpr int kPassThreads = 64;       // per-level pass: one wavefront per (node, 64 hands)
+constexpr int kDownWaves = 4;           // top-down pass: wavefronts per block
+constexpr int kLeafRegs = 4;           // lowest level: actions of a node held in registers
 constexpr int kInternalWaves = 8;       // level path: wavefronts per node block (4 blocks fill a CU's 32 wave slots)
 
 // The per-information-set arithmetic of Section 4's smoothed best response in
@@ -66,8 +69,7 @@ __device__ inline double lse_value(double m, double temp, double sum, double log
   return (m - temp * log(sum)) + temp * logn;
 }
 
-// The fused pass's FP64 weights, with temp's reciprocal known before the shift
-// is: for y = 1/temp rounded, q0 = x y is within two ulps of x/temp, and two
+// FP64 weights with temp's reciprocal known before the shift is: for y = 1/temp rounded, q0 = x y is within two ulps of x/temp, and two
 // corrections by the exact remainder, q <- q + (x - temp q) y, give the rounded
 // quotient (Markstein; the second starts within one ulp) -- 5 dependent
 // operations of 5 cycles where a division takes 106 cycles of a chain that
@@ -75,9 +77,7 @@ __device__ inline double lse_value(double m, double temp, double sum, double log
 // (temp_inverse is 0 outside, and the wavefront divides) and x above some
 // 2^-960, below which the quotient's exponential is 1 whatever its last bit.  A
 // quotient below -1e4 (an overflowed one has no remainder) is left as q0: its
-// exponential is 0.  (On the lowest level of the level path, which is bound by
-// memory latency, the same exchange gained nothing: 31.3 to 32.0 us at 5938
-// sequences.)
+// exponential is 0.
 template <class TG>
 __device__ inline double temp_inverse(double temp) {
   return std::is_same<TG, float>::value || (temp >= 0x1p-900 && temp <= 0x1p900) ? 1.0 / temp : 0.0;
@@ -498,6 +498,16 @@ __global__ __launch_bounds__(kPassThreads) void bottom_up_level_kernel(PassSet a
 // one 16-byte access per gradient row (8 bytes in FP32), half the wavefronts.
 // Used when every row pointer is aligned to two elements; per hand the
 // arithmetic is the one above, and slots h >= n are not written.
+//
+// A wavefront's rows are all requested before the first is used, and only the
+// first kLeafRegs actions of a node live in registers (most nodes have two;
+// further ones pass through LDS, a lane's own column), which makes 60 registers
+// and 8 wavefronts per SIMD of 102 and 4.  1777 nodes x 1081 hands (90 MB, 17.6
+// us at the rate of a large copy): 32 -> 27.5 us, in FP32 22.6 -> 19.9; two
+// trees with their best responses 61 -> 48.7.  What is left is latency and the
+// vector units, 68% busy, side by side: leaving the exponential of the
+// smallest action out (it is 1), 2 to 8 wavefronts per block or fewer registers
+// changed nothing.
 template <class TG>
 __device__ inline void store_pair(TG* p, double x0, double x1, bool both) {
   using V2 = typename std::conditional<std::is_same<TG, float>::value, float2, double2>::type;
@@ -512,7 +522,8 @@ __device__ inline void store_pair(TG* p, double x0, double x1, bool both) {
 }
 
 template <class TG>
-__global__ __launch_bounds__(kPassThreads) void bottom_up_leaf_pair_kernel(PassSet a) {
+__global__ __launch_bounds__(kPassThreads, 8) void bottom_up_leaf_pair_kernel(PassSet a) {
+  extern __shared__ double2 leaf_more[];
   using V2 = typename std::conditional<std::is_same<TG, float>::value, float2, double2>::type;
   int y = blockIdx.y, k = 0;
   while (k < a.count - 1 && y >= a.level_cnt[k]) {
@@ -530,32 +541,43 @@ __global__ __launch_bounds__(kPassThreads) void bottom_up_leaf_pair_kernel(PassS
   const int4 r = ((const int4*)(tab + L.rec))[v];
   const double2 p0 = ((const double2*)(tab + L.prm))[2 * v], p1 = ((const double2*)(tab + L.prm))[2 * v + 1];
   const int s0 = r.x, na = r.y;
-  const TG* gA = (const TG*)t.gA;
-  const TG* gB = (const TG*)t.gB;
-  TG* g_out = (TG*)t.g_out;
-  double g0[kMaxActions], g1[kMaxActions];
+  const TG* gA = (const TG*)t.gA + (size_t)s0 * ld + h;
+  const TG* gB = t.gB ? (const TG*)t.gB + (size_t)s0 * ld + h : nullptr;
+  TG* g_out = t.g_out ? (TG*)t.g_out + (size_t)s0 * ld + h : nullptr;
+  TG* QB = t.QB ? (TG*)t.QB + (size_t)s0 * ld + h : nullptr;
+  double2* more = leaf_more + threadIdx.x;  // g~ and weights of the actions from kLeafRegs on
   double m0 = INFINITY, m1 = INFINITY;
-#pragma unroll
-  for (int j = 0; j < kMaxActions; ++j) {
-    if (j < na) {
-      const size_t idx = (size_t)(s0 + j) * ld + h;
-      const V2 A = *(const V2*)(gA + idx);
-      double x0 = t.cA * (double)A.x, x1 = t.cA * (double)A.y;
-      if (gB) {
-        const V2 B = *(const V2*)(gB + idx);
-        x0 = lin2(t.cA, (double)A.x, t.cB, (double)B.x);
-        x1 = lin2(t.cA, (double)A.y, t.cB, (double)B.y);
-      }
-      if (g_out) {
-        store_pair(g_out + idx, x0 * t.g_scale, x1 * t.g_scale, both);
-        x0 = (double)(TG)x0;  // continue with the stored gradient (g_scale = +-1)
-        x1 = (double)(TG)x1;
-      }
-      g0[j] = x0;
-      g1[j] = x1;
-      m0 = fmin(m0, x0);
-      m1 = fmin(m1, x1);
+  auto combine = [&](int j, const V2& A, const V2& B, double& x0, double& x1) {
+    x0 = gB ? lin2(t.cA, (double)A.x, t.cB, (double)B.x) : t.cA * (double)A.x;
+    x1 = gB ? lin2(t.cA, (double)A.y, t.cB, (double)B.y) : t.cA * (double)A.y;
+    if (g_out) {
+      store_pair(g_out + j * ld, x0 * t.g_scale, x1 * t.g_scale, both);
+      x0 = (double)(TG)x0;  // continue with the stored gradient (g_scale = +-1)
+      x1 = (double)(TG)x1;
     }
+    m0 = fmin(m0, x0);
+    m1 = fmin(m1, x1);
+  };
+  double g0[kLeafRegs], g1[kLeafRegs];
+  {
+    V2 A[kLeafRegs], B[kLeafRegs];
+#pragma unroll
+    for (int j = 0; j < kLeafRegs; ++j)
+      if (j < na) {
+        A[j] = *(const V2*)(gA + j * ld);
+        if (gB) B[j] = *(const V2*)(gB + j * ld);
+      }
+#pragma unroll
+    for (int j = 0; j < kLeafRegs; ++j)
+      if (j < na) combine(j, A[j], B[j], g0[j], g1[j]);
+  }
+#pragma unroll 2
+  for (int j = kLeafRegs; j < na; ++j) {
+    V2 B;
+    if (gB) B = *(const V2*)(gB + j * ld);
+    double2 x;
+    combine(j, *(const V2*)(gA + j * ld), B, x.x, x.y);
+    more[(j - kLeafRegs) * kPassThreads] = x;
   }
   double* Vrow = t.V + (size_t)r.z * ld + h;
   if (!(t.mu > 0.0)) {
@@ -563,56 +585,59 @@ __global__ __launch_bounds__(kPassThreads) void bottom_up_leaf_pair_kernel(PassS
     return;
   }
   if (t.VB) store_pair(t.VB + (size_t)r.z * ld + h, m0, m1, both);  // dual pass: the best response's value
-  const double temp = t.mu * p0.x, itemp = inv_or_zero<TG>(temp);
+  const double temp = t.mu * p0.x, itemp = temp_inverse<TG>(temp);
   double sum0 = 0.0, sum1 = 0.0;
 #pragma unroll
-  for (int j = 0; j < kMaxActions; ++j) {
+  for (int j = 0; j < kLeafRegs; ++j)
     if (j < na) {
-      g0[j] = lse_weight<TG>(m0, g0[j], temp, itemp);
-      g1[j] = lse_weight<TG>(m1, g1[j], temp, itemp);
+      g0[j] = lse_weight_by_inverse<TG>(m0, g0[j], temp, itemp);
+      g1[j] = lse_weight_by_inverse<TG>(m1, g1[j], temp, itemp);
       sum0 += g0[j];
       sum1 += g1[j];
     }
+  for (int j = kLeafRegs; j < na; ++j) {
+    double2 x = more[(j - kLeafRegs) * kPassThreads];
+    x.x = lse_weight_by_inverse<TG>(m0, x.x, temp, itemp);
+    x.y = lse_weight_by_inverse<TG>(m1, x.y, temp, itemp);
+    sum0 += x.x;
+    sum1 += x.y;
+    more[(j - kLeafRegs) * kPassThreads] = x;
   }
   store_pair(Vrow, lse_value(m0, temp, sum0, p1.x), lse_value(m1, temp, sum1, p1.x), both);
-  if (t.QB) {
+  if (QB) {
     const double rs0 = inv_or_zero<TG>(sum0), rs1 = inv_or_zero<TG>(sum1);
 #pragma unroll
-    for (int j = 0; j < kMaxActions; ++j)
-      if (j < na)
-        store_pair((TG*)t.QB + (size_t)(s0 + j) * ld + h, qbar<TG>(g0[j], sum0, rs0), qbar<TG>(g1[j], sum1, rs1),
-                   both);
+    for (int j = 0; j < kLeafRegs; ++j)
+      if (j < na) store_pair(QB + j * ld, qbar<TG>(g0[j], sum0, rs0), qbar<TG>(g1[j], sum1, rs1), both);
+    for (int j = kLeafRegs; j < na; ++j) {
+      const double2 w = more[(j - kLeafRegs) * kPassThreads];
+      store_pair(QB + j * ld, qbar<TG>(w.x, sum0, rs0), qbar<TG>(w.y, sum1, rs1), both);
+    }
   }
 }
 
 // Levels above the lowest (every node has child nodes): the same evaluation
-// with the actions in parallel.  Block = (node, 64 x HP hands) x `blockDim.y`
-// wavefronts (the level's most actions, at most kInternalWaves); wavefront j
-// takes actions j, j + blockDim.y, ... for HP
-// adjacent hands per lane (HP = 2 on wide levels when every row is 2-element
-// aligned): its
+// with the actions in parallel, for levels of few nodes.  Block = (node, 64
+// hands) x `blockDim.y` wavefronts (the level's most actions, at most
+// kInternalWaves); wavefront j takes actions j, j + blockDim.y, ...: its
 // gradients and its children, whose value slots [cbeg[s], cbeg[s + 1]) are
 // read in batches of kChildBatch so that one round trip covers them all and
 // added in slot order.  The node's g~ and weights meet in LDS; the minimum,
 // the weight sum and the value are then formed in the same order as above, so
 // per hand the result is bitwise the one the one-wavefront form gives.
-template <class TG, int HP>
+template <class TG>
 __global__ __launch_bounds__(kPassThreads * kInternalWaves) void bottom_up_internal_kernel(PassSet a) {
-  static_assert(HP == 1 || HP == 2, "one or two hands per lane");
-  using V2 = typename std::conditional<std::is_same<TG, float>::value, float2, double2>::type;
   constexpr int kChildBatch = 8;
-  constexpr int W = HP * kPassThreads;
-  __shared__ double gl[kMaxActions][W];
-  __shared__ double wl[kMaxActions][W];
+  __shared__ double gl[kMaxActions][kPassThreads];
+  __shared__ double wl[kMaxActions][kPassThreads];
   int y = blockIdx.y, k = 0;
   while (k < a.count - 1 && y >= a.level_cnt[k]) {
     y -= a.level_cnt[k];
     ++k;
   }
   const TreePass& t = a.t[k];
-  const int lane = threadIdx.x, j = threadIdx.y;
-  const int h = HP * (blockIdx.x * kPassThreads + lane);  // the lane's first hand; h + 1 < ld when HP = 2
-  const bool both = HP == 2 && h + 1 < a.n;
+  const int lane = threadIdx.x, j = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  const int h = blockIdx.x * kPassThreads + lane;
   const size_t ld = a.ld;
   const int v = t.level_begin[a.level] + y;
   const FusedTabLayout L = fused_tab_layout(t.P.n_nodes, t.P.n_seq);
@@ -624,138 +649,241 @@ __global__ __launch_bounds__(kPassThreads * kInternalWaves) void bottom_up_inter
   const bool live = h < a.n;
   const bool act = live && j < na;  // this wavefront owns actions j, j + blockDim.y, ...
   const int nw = (int)blockDim.y;
-  auto load2 = [&](const TG* p, double& x0, double& x1) {
-    if constexpr (HP == 2) {
-      const V2 q = *(const V2*)p;
-      x0 = (double)q.x;
-      x1 = (double)q.y;
-    } else {
-      x0 = (double)p[0];
-      x1 = 0.0;
-    }
-  };
-  auto store2 = [&](auto* p, double x0, double x1) {
-    if constexpr (HP == 2)
-      store_pair(p, x0, x1, both);
-    else
-      p[0] = (std::remove_pointer_t<decltype(p)>)x0;
-  };
+  const TG* gA = (const TG*)t.gA;
+  const TG* gB = (const TG*)t.gB;
+  TG* g_out = (TG*)t.g_out;
   for (int jj = j; live && jj < na; jj += nw) {
     const size_t idx = (size_t)(s0 + jj) * ld + h;
-    double x0, x1, b0, b1;
-    load2((const TG*)t.gA + idx, x0, x1);
-    if (t.gB) {
-      load2((const TG*)t.gB + idx, b0, b1);
-      x0 = lin2(t.cA, x0, t.cB, b0);
-      x1 = lin2(t.cA, x1, t.cB, b1);
-    } else {
-      x0 = t.cA * x0;
-      x1 = t.cA * x1;
-    }
-    if (t.g_out) {
-      store2((TG*)t.g_out + idx, x0 * t.g_scale, x1 * t.g_scale);
-      x0 = (double)(TG)x0;  // continue with the stored gradient (g_scale = +-1)
-      x1 = (double)(TG)x1;
-    }
     const int c0 = cbeg[s0 + jj], c1 = cbeg[s0 + jj + 1];
-    for (int c = c0; c < c1; c += kChildBatch) {
-      double cv0[kChildBatch], cv1[kChildBatch];
-#pragma unroll
-      for (int u = 0; u < kChildBatch; ++u) {
-        cv0[u] = 0.0;
-        cv1[u] = 0.0;
-        if (c + u < c1) {
-          const double* vp = t.V + (size_t)(c + u) * ld + h;
-          if constexpr (HP == 2) {
-            const double2 q = *(const double2*)vp;
-            cv0[u] = q.x;
-            cv1[u] = q.y;
-          } else {
-            cv0[u] = vp[0];
-          }
-        }
-      }
+    double cv[kChildBatch];
+    auto load_children = [&](int c) {
 #pragma unroll
       for (int u = 0; u < kChildBatch; ++u)
-        if (c + u < c1) {
-          x0 += cv0[u];
-          x1 += cv1[u];
-        }
+        if (c + u < c1) cv[u] = t.V[(size_t)(c + u) * ld + h];
+    };
+    // the gradient and the first children are requested together
+    const TG A = gA[idx], B = gB ? gB[idx] : (TG)0;
+    load_children(c0);
+    double x = gB ? lin2(t.cA, (double)A, t.cB, (double)B) : t.cA * (double)A;
+    if (g_out) {
+      g_out[idx] = (TG)(x * t.g_scale);
+      x = (double)(TG)x;  // continue with the stored gradient (g_scale = +-1)
     }
-    gl[jj][lane] = x0;
-    if constexpr (HP == 2) gl[jj][kPassThreads + lane] = x1;
+    for (int c = c0; c < c1; c += kChildBatch) {
+      if (c > c0) load_children(c);
+#pragma unroll
+      for (int u = 0; u < kChildBatch; ++u)
+        if (c + u < c1) x += cv[u];
+    }
+    gl[jj][lane] = x;
   }
   __syncthreads();
-  double m0 = INFINITY, m1 = INFINITY;
+  // four actions of the node per LDS round trip (the last one repeated)
+  double m = INFINITY;
   if (act)
-    for (int i = 0; i < na; ++i) {
-      m0 = fmin(m0, gl[i][lane]);
-      if constexpr (HP == 2) m1 = fmin(m1, gl[i][kPassThreads + lane]);
-    }
+    for (int i = 0; i < na; i += 4)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m = fmin(m, gl[min(i + u, na - 1)][lane]);
   double* Vrow = t.V + (size_t)r.z * ld + h;
   if (!(t.mu > 0.0)) {
-    if (act && j == 0) store2(Vrow, m0, m1);
+    if (act && j == 0) Vrow[0] = m;
     return;
   }
-  const double temp = t.mu * p0.x, itemp = inv_or_zero<TG>(temp);
-  for (int jj = j; live && jj < na; jj += nw) {
-    double w1 = 0.0;
-    const double w0 = lse_weight<TG>(m0, gl[jj][lane], temp, itemp);
-    if constexpr (HP == 2) w1 = lse_weight<TG>(m1, gl[jj][kPassThreads + lane], temp, itemp);
-    wl[jj][lane] = w0;
-    if constexpr (HP == 2) wl[jj][kPassThreads + lane] = w1;
-  }
+  const double temp = t.mu * p0.x, itemp = temp_inverse<TG>(temp);
+  for (int jj = j; live && jj < na; jj += nw) wl[jj][lane] = lse_weight_by_inverse<TG>(m, gl[jj][lane], temp, itemp);
   __syncthreads();
   if (act) {
-    double sum0 = 0.0, sum1 = 0.0;
-    for (int i = 0; i < na; ++i) {
-      sum0 += wl[i][lane];
-      if constexpr (HP == 2) sum1 += wl[i][kPassThreads + lane];
-    }
-    if (j == 0)
-      store2(Vrow, lse_value(m0, temp, sum0, p1.x), HP == 2 ? lse_value(m1, temp, sum1, p1.x) : 0.0);
+    // rows up to the next multiple of four are read, never added
+    const double sum = add_run<kPassThreads>(0.0, &wl[0][lane], na);
+    if (j == 0) Vrow[0] = lse_value(m, temp, sum, p1.x);
     if (t.QB) {
-      const double rs0 = inv_or_zero<TG>(sum0), rs1 = inv_or_zero<TG>(sum1);
+      const double rs = inv_or_zero<TG>(sum);
       for (int jj = j; jj < na; jj += nw)
-        store2((TG*)t.QB + (size_t)(s0 + jj) * ld + h, qbar<TG>(wl[jj][lane], sum0, rs0),
-               HP == 2 ? qbar<TG>(wl[jj][kPassThreads + lane], sum1, rs1) : 0.0);
+        ((TG*)t.QB)[(size_t)(s0 + jj) * ld + h] = (TG)qbar<TG>(wl[jj][lane], sum, rs);
     }
   }
 }
 
-// Root sums of the level path: block k sums tree k, roots in order (value
-// slots C + r), hands strided over the threads, then a fixed-order reduction.
-__global__ __launch_bounds__(256) void root_sums_kernel(PassSet a, double* out) {
-  constexpr int kRootBatch = 4;                     // roots whose values are requested together
-  constexpr int kHandSteps = 8;                     // hands per thread and root (n <= 2048 = 256 x 8)
-  __shared__ double part[4];
-  const TreePass& t = a.t[blockIdx.x];
+// A wide level above the lowest: block = one wavefront for (node, 64 x HP
+// hands), as on the lowest level.  The node's gradient rows and its first
+// children are requested together; g~ and then the weights of its actions pass
+// through LDS, a lane's own column.  Per hand the operations and their order are
+// those above.
+template <class TG, int HP>
+__global__ __launch_bounds__(kPassThreads, HP == 2 ? 4 : 7) void bottom_up_wide_kernel(PassSet a) {
+  typedef TG VH __attribute__((ext_vector_type(HP)));
+  typedef double DH __attribute__((ext_vector_type(HP)));
+  constexpr int kRows = 4, kChildBatch = 8;
+  extern __shared__ double wide_rows[];  // [actions][64] DH: g~, then the weights; a lane's own column
+  DH* row = (DH*)wide_rows + threadIdx.x;
+  int y = blockIdx.y, k = 0;
+  while (k < a.count - 1 && y >= a.level_cnt[k]) {
+    y -= a.level_cnt[k];
+    ++k;
+  }
+  const TreePass& t = a.t[k];
+  const int h = HP * (blockIdx.x * kPassThreads + threadIdx.x);
+  if (h >= a.n) return;
+  const bool both = HP == 2 && h + 1 < a.n;
+  const size_t ld = a.ld;
+  const int v = t.level_begin[a.level] + y;
+  const FusedTabLayout L = fused_tab_layout(t.P.n_nodes, t.P.n_seq);
+  const unsigned char* tab = (const unsigned char*)t.P.fused_tab;
+  const int4 r = ((const int4*)(tab + L.rec))[v];
+  const double2 p0 = ((const double2*)(tab + L.prm))[2 * v], p1 = ((const double2*)(tab + L.prm))[2 * v + 1];
+  const int s0 = r.x, na = r.y;
+  const int* cend = (const int*)(tab + L.cbeg) + s0 + 1;
+  const TG* gA = (const TG*)t.gA + (size_t)s0 * ld + h;
+  const TG* gB = t.gB ? (const TG*)t.gB + (size_t)s0 * ld + h : nullptr;
+  TG* g_out = t.g_out ? (TG*)t.g_out + (size_t)s0 * ld + h : nullptr;
+  auto store = [&](auto* p, const DH& x) {
+    if constexpr (HP == 2)
+      store_pair(p, x[0], x[1], both);
+    else
+      p[0] = (std::remove_pointer_t<decltype(p)>)x[0];
+  };
+  const int c_first = cend[-1], c_last = cend[na - 1];
+  const double* Vc = t.V + h;
+  DH cv[kChildBatch];
+  auto load_children = [&](int c) {
+#pragma unroll
+    for (int u = 0; u < kChildBatch; ++u)
+      if (c + u < c_last) cv[u] = *(const DH*)(Vc + (size_t)(c + u) * ld);
+  };
+  load_children(c_first);
+  for (int j = 0; j < na; j += kRows) {
+    VH A[kRows], B[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (j + u < na) {
+        A[u] = *(const VH*)(gA + (size_t)(j + u) * ld);
+        if (gB) B[u] = *(const VH*)(gB + (size_t)(j + u) * ld);
+      }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (j + u < na) {
+        DH x;
+#pragma unroll
+        for (int e = 0; e < HP; ++e)
+          x[e] = gB ? lin2(t.cA, (double)A[u][e], t.cB, (double)B[u][e]) : t.cA * (double)A[u][e];
+        if (g_out) {
+          store(g_out + (size_t)(j + u) * ld, x * t.g_scale);
+#pragma unroll
+          for (int e = 0; e < HP; ++e) x[e] = (double)(TG)x[e];  // continue with the stored gradient (g_scale = +-1)
+        }
+        row[(j + u) * kPassThreads] = x;
+      }
+  }
+  // the children of all actions are consecutive value slots: added one after
+  // the other, on to the next action where an action's end
+  DH x = row[0], m = (DH)INFINITY;
+  int j = 0, end = cend[0];
+  auto close = [&]() {  // action j is complete
+    row[j * kPassThreads] = x;
+#pragma unroll
+    for (int e = 0; e < HP; ++e) m[e] = fmin(m[e], x[e]);
+    if (++j < na) {
+      x = row[j * kPassThreads];
+      end = cend[j];
+    }
+  };
+  for (int c = c_first; c < c_last; c += kChildBatch) {
+    if (c > c_first) load_children(c);
+#pragma unroll
+    for (int u = 0; u < kChildBatch; ++u)
+      if (c + u < c_last) {
+        while (c + u >= end) close();
+        x += cv[u];
+      }
+  }
+  while (j < na) close();
+  double* Vrow = t.V + (size_t)r.z * ld + h;
+  if (!(t.mu > 0.0)) {
+    store(Vrow, m);
+    return;
+  }
+  const double temp = t.mu * p0.x, itemp = temp_inverse<TG>(temp);
+  DH sum = (DH)0.0;
+  for (int i = 0; i < na; ++i) {
+    DH w = row[i * kPassThreads];
+#pragma unroll
+    for (int e = 0; e < HP; ++e) w[e] = lse_weight_by_inverse<TG>(m[e], w[e], temp, itemp);
+    row[i * kPassThreads] = w;
+    sum += w;
+  }
+  DH val;
+#pragma unroll
+  for (int e = 0; e < HP; ++e) val[e] = lse_value(m[e], temp, sum[e], p1.x);
+  store(Vrow, val);
+  if (t.QB) {
+    DH rs;
+#pragma unroll
+    for (int e = 0; e < HP; ++e) rs[e] = inv_or_zero<TG>(sum[e]);
+    TG* QB = (TG*)t.QB + (size_t)s0 * ld + h;
+#pragma unroll 2
+    for (int i = 0; i < na; ++i) {
+      DH w = row[i * kPassThreads];
+#pragma unroll
+      for (int e = 0; e < HP; ++e) w[e] = qbar<TG>(w[e], sum[e], rs[e]);
+      store(QB + (size_t)i * ld, w);
+    }
+  }
+}
+
+// Root sums of the level path (rows of n slots, n <= 2048): the hands are dealt
+// to 256 places h mod 256, a place adds root by root with h ascending; 64 places
+// are then added by halves, and the four sums in order.  That order is the
+// result's definition.  By itself the sum of one root of 1081 hands took 4.5 us,
+// nearly all of it the launch, so it rides on the first blocks of a top-down
+// pass where there is one.
+struct RootSum {
+  const double* rows;  // the first root's values
+  double* out;
+  int n_roots;
+};
+struct RootSums {
+  RootSum job[kMaxTrees];
+  int count, n, ld;
+};
+// The sum of 64 places, from place 64 w on, in lane 0.
+__device__ inline double root_sum_quarter(const RootSum& r, int n, int ld, int w, int lane) {
+  constexpr int kBatch = 8;  // loads in flight: the place's hands of one root, then the next root's
+  const int steps = (n + 255) / 256, total = r.n_roots * steps;
+  const int h0 = kPassThreads * w + lane;
   double s = 0.0;
-  const int C = t.P.n_nodes - t.P.n_roots;  // the r-th root's value slot is C + r
-  // each thread adds its hands h = tid + 256 m root by root, m ascending; the
-  // loads of kRootBatch roots are issued before the first add
-  for (int r0 = 0; r0 < t.P.n_roots; r0 += kRootBatch) {
-    double v[kRootBatch][kHandSteps];
+  int q = 0, m = 0;  // root and step of the next load
+  for (int i = 0; i < total; i += kBatch) {
+    double v[kBatch];
+    bool in[kBatch];
 #pragma unroll
-    for (int u = 0; u < kRootBatch; ++u) {
-      const double* row = t.V + (size_t)(C + r0 + u) * a.ld;
-#pragma unroll
-      for (int m = 0; m < kHandSteps; ++m) {
-        const int h = (int)threadIdx.x + 256 * m;
-        v[u][m] = (r0 + u < t.P.n_roots && h < a.n) ? row[h] : 0.0;
+    for (int u = 0; u < kBatch; ++u) {
+      const int h = h0 + 256 * m;
+      in[u] = i + u < total && h < n;
+      v[u] = in[u] ? r.rows[(size_t)q * ld + h] : 0.0;
+      if (++m == steps) {
+        m = 0;
+        ++q;
       }
     }
 #pragma unroll
-    for (int u = 0; u < kRootBatch; ++u)
-#pragma unroll
-      for (int m = 0; m < kHandSteps; ++m)
-        if (r0 + u < t.P.n_roots && (int)threadIdx.x + 256 * m < a.n) s += v[u][m];
+    for (int u = 0; u < kBatch; ++u)
+      if (in[u]) s += v[u];
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  return s;
+}
+// The sum by the block's first four wavefronts (256 threads).
+__device__ inline void root_sum(const RootSum& r, int n, int ld, int w, int lane) {
+  __shared__ double part[4];
+  const double s = root_sum_quarter(r, n, ld, w, lane);
+  if (lane == 0) part[w] = s;
   __syncthreads();
-  if (threadIdx.x == 0) out[blockIdx.x] = ((part[0] + part[1]) + part[2]) + part[3];
+  if (w == 0 && lane == 0) *r.out = ((part[0] + part[1]) + part[2]) + part[3];
+}
+
+__global__ __launch_bounds__(kPassThreads * kDownWaves) void root_sums_kernel(RootSums a) {
+  root_sum(a.job[blockIdx.x], a.n, a.ld, (int)threadIdx.y, (int)threadIdx.x);
 }
 
 // out[k] = sum of partial[k][0 .. nb) in order, block k = tree k.  The order of
@@ -772,106 +900,96 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 }
 
 // ---------------------------------------------------------------------------
-// Top-down pass of the level path, fully parallel: q[s] = q_bar[root] * ...
-// * q_bar[s] along the sequence's path (multiplied from the root down, the
-// path read from the precomputed root-first table, so every q_bar load is
-// issued at once), then the epilogue comb = (1 - tau) x_prev + tau q.
-// Padding slots are written 0.
+// Top-down pass of the level path: q[s] = q_bar[root] * ... * q_bar[s] along
+// the sequence's path, multiplied from the root down, then the epilogue
+// comb = (1 - tau) x_prev + tau q.  Padding slots are written 0.
+//
+// One wavefront per (node, 64 x HP hands), HP the hands of a 16-byte
+// access: the sequences of a node share the path above them, so its product is
+// formed once and every sequence costs its own row (a wavefront per sequence
+// spent its time on instructions, 149 vector and 117 scalar ones for three or four
+// products).  The path (root first) and the node's record are wavefront-uniform
+// loads, and every row of the first kStep ancestors and actions is in flight
+// before the first product; kStep 4 takes 74 registers and 7 wavefronts per SIMD
+// instead of 8.  Bound by memory: 5938 sequences x 1081 hands, 102 MB, 21.8 ->
+// 20.3 us (18.1 -> 13.0 in FP32, which read 8 bytes per lane), with the root
+// sums; with the epilogue, 206 MB, 33 us as before.
 // ---------------------------------------------------------------------------
 struct DownArgs {
   const int* anc;
+  const int4* rec;  // of a node: first sequence, actions
   const void* QB;
-  int n, ld, n_seq;
+  int n, ld, n_nodes;
   void* q_out;
   const void* x_prev;
   double tau;
   void* comb_out;
+  RootSums sums;  // root sums that ride along, on the grid's first blocks
 };
 
-template <class TS>
-__global__ __launch_bounds__(kPassThreads) void top_down_kernel(DownArgs a) {
+template <class TS, int HP>
+__global__ __launch_bounds__(kPassThreads * kDownWaves) void top_down_kernel(DownArgs a) {
+  typedef TS VH __attribute__((ext_vector_type(HP)));
+  constexpr int kStep = 3;
   const TS* QB = (const TS*)a.QB;
   TS* q_out = (TS*)a.q_out;
   TS* comb_out = (TS*)a.comb_out;
   const TS* x_prev = (const TS*)a.x_prev;
-  const int h = blockIdx.x * kPassThreads + threadIdx.x;
-  const int s = blockIdx.y;
-  if (h >= a.ld) return;
-  const size_t idx = (size_t)s * a.ld + h;
-  if (h >= a.n) {
-    if (q_out) q_out[idx] = (TS)0;
-    if (comb_out) comb_out[idx] = (TS)0;
+  // (hand block, node) pairs in hand-block-major order, kDownWaves a block, dealt
+  // to the XCDs in contiguous ranges: the blocks of one XCD share hand blocks,
+  // so the ancestor rows are re-read from that XCD's L2
+  const int n_sums = a.sums.count, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  if ((int)blockIdx.x < n_sums) {
+    root_sum(a.sums.job[blockIdx.x], a.sums.n, a.sums.ld, wave, (int)threadIdx.x);
     return;
   }
-  const int* path = a.anc + (size_t)s * kMaxDepth;
-  TS f[kMaxDepth];
+  const int pos = xcd_spread((int)blockIdx.x - n_sums, (int)gridDim.x - n_sums) * kDownWaves + wave;
+  const int hb = pos / a.n_nodes, v = pos - hb * a.n_nodes;
+  const int h = HP * (hb * kPassThreads + (int)threadIdx.x);
+  if (h >= a.ld) return;  // ld is a multiple of HP
+  const size_t ld = a.ld;
+  const int s0 = a.rec[v].x, na = a.rec[v].y;
+  const int* path = a.anc + (size_t)s0 * kMaxDepth;
+  VH above = (VH)(TS)1;
+  bool first = true;
+  for (int i = 0; i < na; i += kStep) {
+    VH own[kStep], xp[kStep];
 #pragma unroll
-  for (int j = 0; j < kMaxDepth; ++j) {
-    const int q = path[j];
-    f[j] = q >= 0 ? QB[(size_t)q * a.ld + h] : (TS)1;
-  }
-  TS val = (TS)1;
+    for (int u = 0; u < kStep; ++u)
+      if (i + u < na) {
+        own[u] = *(const VH*)(QB + (size_t)(s0 + i + u) * ld + h);
+        if (comb_out) xp[u] = *(const VH*)(x_prev + (size_t)(s0 + i + u) * ld + h);
+      }
+    for (int j = 0; first && j < kMaxDepth; j += kStep) {
+      VH f[kStep];
+      bool in[kStep];
 #pragma unroll
-  for (int j = 0; j < kMaxDepth; ++j)
-    if (path[j] >= 0) val *= f[j];
-  const TS xp = comb_out ? x_prev[idx] : (TS)0;
-  if (q_out) q_out[idx] = val;
-  if (comb_out) comb_out[idx] = (TS)(1.0 - a.tau) * xp + (TS)a.tau * val;
-}
-
-// The same with two adjacent hands per lane (one 16-byte access per row for
-// FP64, 8 bytes for FP32), halving the wavefronts; used when every row
-// pointer is aligned to two elements.  Per hand the arithmetic is the one
-// above.
-template <class TS>
-__global__ __launch_bounds__(kPassThreads) void top_down_pair_kernel(DownArgs a) {
-  using V2 = typename std::conditional<std::is_same<TS, float>::value, float2, double2>::type;
-  const TS* QB = (const TS*)a.QB;
-  TS* q_out = (TS*)a.q_out;
-  TS* comb_out = (TS*)a.comb_out;
-  const TS* x_prev = (const TS*)a.x_prev;
-  // one-dimensional grid of (hand block, sequence) pairs in hand-block-major
-  // order, dealt to the XCDs in contiguous ranges: the blocks of one XCD share
-  // hand blocks, so the ancestor rows each sequence multiplies along its path
-  // are re-read from that XCD's L2
-  const int nbx = (a.ld / 2 + kPassThreads - 1) / kPassThreads;
-  const int pos = xcd_spread((int)blockIdx.x, (int)gridDim.x);
-  const int s = pos % a.n_seq, hb = pos / a.n_seq;
-  const int h = 2 * (hb * kPassThreads + threadIdx.x);  // ld is even: h + 1 < ld too
-  if (hb >= nbx || h >= a.ld) return;
-  const size_t idx = (size_t)s * a.ld + h;
-  const int* path = a.anc + (size_t)s * kMaxDepth;
-  V2 f[kMaxDepth];
+      for (int u = 0; u < kStep; ++u) {
+        const int q = path[j + u];  // s0 closes the path, -1 after it
+        in[u] = q >= 0 && q != s0;
+        if (in[u]) f[u] = *(const VH*)(QB + (size_t)q * ld + h);
+      }
 #pragma unroll
-  for (int j = 0; j < kMaxDepth; ++j) {
-    const int q = path[j];
-    if (q >= 0) {
-      f[j] = *(const V2*)(QB + (size_t)q * a.ld + h);
-    } else {
-      f[j].x = (TS)1;
-      f[j].y = (TS)1;
+      for (int u = 0; u < kStep; ++u)
+        if (in[u]) above *= f[u];
+      if (!in[kStep - 1]) break;
     }
-  }
-  TS v0 = (TS)1, v1 = (TS)1;
+    first = false;
 #pragma unroll
-  for (int j = 0; j < kMaxDepth; ++j)
-    if (path[j] >= 0) {
-      v0 *= f[j].x;
-      v1 *= f[j].y;
-    }
-  const bool live0 = h < a.n, live1 = h + 1 < a.n;
-  if (q_out) {
-    V2 o;
-    o.x = live0 ? v0 : (TS)0;
-    o.y = live1 ? v1 : (TS)0;
-    *(V2*)(q_out + idx) = o;
-  }
-  if (comb_out) {
-    const V2 xp = *(const V2*)(x_prev + idx);
-    V2 o;
-    o.x = live0 ? (TS)(1.0 - a.tau) * xp.x + (TS)a.tau * v0 : (TS)0;
-    o.y = live1 ? (TS)(1.0 - a.tau) * xp.y + (TS)a.tau * v1 : (TS)0;
-    *(V2*)(comb_out + idx) = o;
+    for (int u = 0; u < kStep; ++u)
+      if (i + u < na) {
+        const size_t idx = (size_t)(s0 + i + u) * ld + h;
+        const VH val = above * own[u];
+        VH q, c;
+#pragma unroll
+        for (int e = 0; e < HP; ++e) {
+          const bool live = h + e < a.n;
+          q[e] = live ? val[e] : (TS)0;
+          if (comb_out) c[e] = live ? (TS)(1.0 - a.tau) * xp[u][e] + (TS)a.tau * val[e] : (TS)0;
+        }
+        if (q_out) *(VH*)(q_out + idx) = q;
+        if (comb_out) *(VH*)(comb_out + idx) = c;
+      }
   }
 }
 
@@ -992,10 +1110,10 @@ size_t fused_lds_bytes(int hands, int cap_nodes, int cap_seqs, bool dual) {
 // or five launches of at least 4 us each) until its launches fill the chip.
 // Where the fused pass has a block for every compute unit and more, and in its
 // one block of a general game, the paths meet near K = 3 (one step of EGT; 1081
-// hands: 286 sequences 98 against 101 us, 520 sequences 158 against 122;
-// general: 336 sequences 71 against 92 us, 936 sequences 91 against 96, 1240
-// sequences 96 against 97); with blocks for part of the chip only, near K = 6
-// (105 and 351 hands, 520 sequences: 84 against 92 and 88 against 100 us; 967
+// hands: 286 sequences 94 against 110 us, 520 sequences 158 against 127;
+// general: 744 sequences 69 against 81 us, 936 sequences 84 against 92, 1240
+// sequences 89 against 92); with blocks for part of the chip only, near K = 6
+// (105 and 351 hands, 520 sequences: 82 against 96 and 86 against 105 us; 967
 // sequences: 112 against 106 and 118 against 119).
 bool fits_fused(const egt_game* g) {
   const int seqs = std::max(g->hp[0].n_seq, g->hp[1].n_seq), nodes = std::max(g->hp[0].n_nodes, g->hp[1].n_nodes);
@@ -1086,6 +1204,43 @@ static hipError_t fused_launch(const egt_game* g, const Pass* p, int count, cons
   return hipGetLastError();
 }
 
+template <class TS, int HP>
+static hipError_t top_down_launch(const DownArgs& a, hipStream_t s) {
+  const int nbx = (a.ld / HP + kPassThreads - 1) / kPassThreads;
+  const dim3 grid((unsigned)(a.sums.count + (nbx * a.n_nodes + kDownWaves - 1) / kDownWaves));
+  hipLaunchKernelGGL((top_down_kernel<TS, HP>), grid, dim3(kPassThreads, kDownWaves), 0, s, a);
+  return hipGetLastError();
+}
+
+// Takes the root sums along (and clears the list) unless the tree is empty.
+static hipError_t top_down(const egt_game* g, int player, const void* QB, void* q_out, const void* x_prev, double tau,
+                           void* comb_out, hipStream_t s, Prec prec, RootSums& sums) {
+  const DPlayer& P = g->dp[player];
+  DownArgs a;
+  a.anc = P.anc;
+  a.rec = (const int4*)((const unsigned char*)P.fused_tab + fused_tab_layout(P.n_nodes, P.n_seq).rec);
+  a.QB = QB;
+  a.n = g->n;
+  a.ld = g->ld;
+  a.q_out = q_out;
+  a.x_prev = x_prev;
+  a.tau = tau;
+  a.comb_out = comb_out;
+  a.n_nodes = P.n_nodes;
+  if (a.n_nodes == 0) return hipSuccess;
+  a.sums = sums;
+  sums.count = 0;
+  // the widest access of up to 16 bytes that every row allows
+  const size_t elem = prec == kF32 ? sizeof(float) : sizeof(double);
+  const uintptr_t bits = (uintptr_t)QB | (uintptr_t)q_out | (uintptr_t)x_prev | (uintptr_t)comb_out;
+  auto fits = [&](int hands) { return g->ld % hands == 0 && bits % (hands * elem) == 0; };
+  if (prec == kF32)
+    return fits(4)   ? top_down_launch<float, 4>(a, s)
+           : fits(2) ? top_down_launch<float, 2>(a, s)
+                     : top_down_launch<float, 1>(a, s);
+  return fits(2) ? top_down_launch<double, 2>(a, s) : top_down_launch<double, 1>(a, s);
+}
+
 template <class TG>
 static hipError_t passes_launch(const egt_game* g, const Pass* p, int count, const Epilogue* epi, double* partial,
                                 hipStream_t s) {
@@ -1147,35 +1302,55 @@ static hipError_t passes_launch(const egt_game* g, const Pass* p, int count, con
     if (total == 0) continue;
     cur.level = l;
     if (l == 0 && pair) {
-      hipLaunchKernelGGL(bottom_up_leaf_pair_kernel<TG>, dim3(bx_pair, total), dim3(kPassThreads), 0, s, a);
+      int more = 0;  // actions beyond the registers
+      for (int k = 0; k < count; ++k)
+        if (a.t[k].n_levels > 0) more = std::max(more, g->hp[p[k].player].level_max_act[0] - kLeafRegs);
+      hipLaunchKernelGGL(bottom_up_leaf_pair_kernel<TG>, dim3(bx_pair, total), dim3(kPassThreads),
+                         (size_t)more * kPassThreads * sizeof(double2), s, a);
     } else if (l == 0) {
       hipLaunchKernelGGL(bottom_up_level_kernel<TG>, dim3(bx, total), dim3(kPassThreads), 0, s, a);
     } else {
-      // above the lowest level every node has children: a wavefront per action (at most kInternalWaves)
-      int wa = 1;
+      // above the lowest level every node has children
+      int max_act = 1;
       for (int k = 0; k < count; ++k)
-        if (l < a.t[k].n_levels) wa = std::max(wa, g->hp[p[k].player].level_max_act[l]);
-      wa = std::min(wa, kInternalWaves);  // a wavefront takes actions j, j + wa, ... beyond that
-      // two hands per lane only where the level fills the chip several times
-      // over; a narrow level is latency-bound and gains from more lanes
-      if (pair && (size_t)bx * total >= 4 * (size_t)g->n_cu)
-        hipLaunchKernelGGL((bottom_up_internal_kernel<TG, 2>), dim3(bx_pair, total), dim3(kPassThreads, wa), 0, s, ax);
+        if (l < a.t[k].n_levels) max_act = std::max(max_act, g->hp[p[k].player].level_max_act[l]);
+      const size_t row = kPassThreads * sizeof(double) * (size_t)max_act;
+      const int wa = std::min(max_act, kInternalWaves);  // a wavefront takes actions j, j + wa, ... beyond that
+      // A wavefront per node once the level has 8 (node, 64 hands) pairs for every
+      // compute unit: there a wavefront per action waits at its barriers in a second
+      // round of blocks (195 nodes x 1081 hands, 13 per unit: 17.2 -> 16.5 us, in FP32
+      // 14.2 -> 12.0); below, a node's children and exponentials one after the other
+      // take longer (61 nodes x 1081 hands, 4 per unit: one step of EGT 209 against 214
+      // us; 51 nodes of ten actions: 289 against 304).  With 32 and more, two hands per lane
+      // (780 nodes, four trees, 52 per unit: 39.0 -> 32.9 us).
+      if (pair && (size_t)bx * total >= 32 * (size_t)g->n_cu)
+        hipLaunchKernelGGL((bottom_up_wide_kernel<TG, 2>), dim3(bx_pair, total), dim3(kPassThreads), 2 * row, s, ax);
+      else if ((size_t)bx * total >= 8 * (size_t)g->n_cu)
+        hipLaunchKernelGGL((bottom_up_wide_kernel<TG, 1>), dim3(bx, total), dim3(kPassThreads), row, s, ax);
       else
-        hipLaunchKernelGGL((bottom_up_internal_kernel<TG, 1>), dim3(bx, total), dim3(kPassThreads, wa), 0, s, ax);
+        hipLaunchKernelGGL(bottom_up_internal_kernel<TG>, dim3(bx, total), dim3(kPassThreads, wa), 0, s, ax);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (partial) {
-    hipLaunchKernelGGL(root_sums_kernel, dim3(ax.count), dim3(256), 0, s, ax, partial);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  RootSums sums;
+  sums.count = 0;
+  sums.n = g->n;
+  sums.ld = g->ld;
+  for (int k = 0; partial && k < ax.count; ++k) {
+    const TreePass& t = ax.t[k];
+    // the r-th root's value slot follows the children's
+    sums.job[sums.count++] = RootSum{t.V + (size_t)(t.P.n_nodes - t.P.n_roots) * g->ld, partial + k, t.P.n_roots};
   }
   for (int k = 0; epi && k < count; ++k) {
     if (!epi[k].q_out && !epi[k].comb_out) continue;
-    const hipError_t e = launch_top_down(g, p[k].player, p[k].QB, epi[k].q_out, epi[k].x_prev, epi[k].tau,
-                                         epi[k].comb_out, s, std::is_same<TG, float>::value ? kF32 : kF64);
+    const hipError_t e = top_down(g, p[k].player, p[k].QB, epi[k].q_out, epi[k].x_prev, epi[k].tau, epi[k].comb_out, s,
+                                  std::is_same<TG, float>::value ? kF32 : kF64, sums);
     if (e != hipSuccess) return e;
+  }
+  if (sums.count) {  // no top-down pass took them
+    hipLaunchKernelGGL(root_sums_kernel, dim3(sums.count), dim3(kPassThreads, kDownWaves), 0, s, sums);
+    return hipGetLastError();
   }
   return hipSuccess;
 }
@@ -1203,33 +1378,9 @@ hipError_t launch_value(const egt_game* g, const Pass& p, const Epilogue* epi, d
 
 hipError_t launch_top_down(const egt_game* g, int player, const void* QB, void* q_out, const void* x_prev,
                            double tau, void* comb_out, hipStream_t s, Prec prec) {
-  DownArgs a;
-  a.anc = g->dp[player].anc;
-  a.QB = QB;
-  a.n = g->n;
-  a.ld = g->ld;
-  a.q_out = q_out;
-  a.x_prev = x_prev;
-  a.tau = tau;
-  a.comb_out = comb_out;
-  a.n_seq = g->dp[player].n_seq;
-  if (a.n_seq == 0) return hipSuccess;
-  const size_t pair_bytes = prec == kF32 ? 8 : 16;
-  auto aligned = [&](const void* ptr) { return ((uintptr_t)ptr % pair_bytes) == 0; };
-  if (g->ld % 2 == 0 && aligned(QB) && aligned(q_out) && aligned(x_prev) && aligned(comb_out)) {
-    const dim3 grid((unsigned)((g->ld / 2 + kPassThreads - 1) / kPassThreads) * (unsigned)g->dp[player].n_seq);
-    if (prec == kF32)
-      hipLaunchKernelGGL(top_down_pair_kernel<float>, grid, dim3(kPassThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL(top_down_pair_kernel<double>, grid, dim3(kPassThreads), 0, s, a);
-    return hipGetLastError();
-  }
-  const dim3 grid((unsigned)((g->ld + kPassThreads - 1) / kPassThreads), g->dp[player].n_seq);
-  if (prec == kF32)
-    hipLaunchKernelGGL(top_down_kernel<float>, grid, dim3(kPassThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL(top_down_kernel<double>, grid, dim3(kPassThreads), 0, s, a);
-  return hipGetLastError();
+  RootSums none;
+  none.count = 0;
+  return top_down(g, player, QB, q_out, x_prev, tau, comb_out, s, prec, none);
 }
 
 hipError_t launch_uniform(const egt_game* g, int player, double* out, hipStream_t s) {
