@@ -288,7 +288,6 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
     std::memcpy(img + L.prm + 32 * (size_t)i, prm, sizeof(prm));
   }
   std::memcpy(img + L.cbeg, hp.child_begin.data(), sizeof(int) * (size_t)(ns + 1));
-  if (ns) std::memcpy(img + L.spar, hp.seq_parent.data(), sizeof(int) * (size_t)ns);
   hp.seq_rec.resize(ns);
   hp.node_rec.resize(nn);
   for (int i = 0; i < nn; ++i) {
@@ -412,27 +411,16 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   GameOffsets::Player* po = g->offs.p;
   for (int p = 0; p < 2; ++p) {
     HostPlayer& hp = g->hp[p];
-    po[p].first = add(hp.node_first_seq.data(), hp.node_first_seq.size() * sizeof(int));
-    po[p].nact = add(hp.node_nact.data(), hp.node_nact.size() * sizeof(int));
-    po[p].beta = add(hp.node_beta.data(), hp.node_beta.size() * sizeof(double));
-    po[p].logn = add(hp.node_logn.data(), hp.node_logn.size() * sizeof(double));
-    po[p].spar = add(hp.seq_parent.data(), hp.seq_parent.size() * sizeof(int));
-    po[p].cbeg = add(hp.child_begin.data(), hp.child_begin.size() * sizeof(int));
-    po[p].child = add(hp.child.data(), hp.child.size() * sizeof(int));
-    po[p].tbeg = add(hp.term_begin.data(), hp.term_begin.size() * sizeof(int));
-    po[p].topp = add(hp.term_opp.data(), hp.term_opp.size() * sizeof(int));
-    po[p].tkind = add(hp.term_kind.data(), hp.term_kind.size() * sizeof(int));
-    po[p].tcoef = add(hp.term_coef.data(), hp.term_coef.size() * sizeof(double));
-    po[p].roots = add(hp.roots.data(), hp.roots.size() * sizeof(int));
     po[p].belief = add(b[p].data(), b[p].size() * sizeof(double));
     po[p].ftab = add(hp.fused_tab.data(), hp.fused_tab.size());
     po[p].rounds = add(hp.rounds.data(), hp.rounds.size() * sizeof(ProdRound));
     po[p].rbeg = add(hp.round_begin.data(), hp.round_begin.size() * sizeof(int));
     po[p].srec = add(hp.seq_rec.data(), hp.seq_rec.size() * sizeof(SeqRec));
     po[p].nrec = add(hp.node_rec.data(), hp.node_rec.size() * sizeof(NodeRec));
-    po[p].trec = add(hp.term_rec.data(), hp.term_rec.size() * sizeof(TermRec));
+    const bool paired = !hp.rounds.empty();  // the other product kernel's records stay on the host
+    po[p].trec = add(hp.term_rec.data(), paired ? 0 : hp.term_rec.size() * sizeof(TermRec));
     po[p].anc = add(hp.anc.data(), hp.anc.size() * sizeof(int));
-    po[p].titems = add(hp.term_items.data(), hp.term_items.size() * sizeof(TermItem));
+    po[p].titems = add(hp.term_items.data(), paired ? 0 : hp.term_items.size() * sizeof(TermItem));
     po[p].snact = add(hp.seq_nact.data(), hp.seq_nact.size() * sizeof(int));
     po[p].sptr = add(hp.sp_ptr.data(), hp.sp_ptr.size() * sizeof(int64_t));
     po[p].scol = add(hp.sp_col.data(), hp.sp_col.size() * sizeof(int));
@@ -805,18 +793,6 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.n_seq = hp.n_seq;
     dp.n_nodes = hp.n_nodes;
     dp.n_roots = (int)hp.roots.size();
-    dp.node_first_seq = (const int*)at(po[p].first);
-    dp.node_nact = (const int*)at(po[p].nact);
-    dp.node_beta = (const double*)at(po[p].beta);
-    dp.node_logn = (const double*)at(po[p].logn);
-    dp.seq_parent = (const int*)at(po[p].spar);
-    dp.child_begin = (const int*)at(po[p].cbeg);
-    dp.child = (const int*)at(po[p].child);
-    dp.term_begin = (const int*)at(po[p].tbeg);
-    dp.term_opp = (const int*)at(po[p].topp);
-    dp.term_kind = (const int*)at(po[p].tkind);
-    dp.term_coef = (const double*)at(po[p].tcoef);
-    dp.roots = (const int*)at(po[p].roots);
     dp.belief = (const double*)at(po[p].belief);
     dp.fused_tab = at(po[p].ftab);
     dp.n_round_blocks = hp.rounds.empty() ? 0 : (int)hp.round_begin.size() - 1;
@@ -827,7 +803,7 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.term_rec = (const TermRec*)at(po[p].trec);
     dp.anc = (const int*)at(po[p].anc);
     dp.term_stride = std::max(1, hp.max_terms_per_seq);
-    dp.n_items = (int)hp.term_items.size();
+    dp.n_items = hp.rounds.empty() ? (int)hp.term_items.size() : 0;
     dp.term_items = dp.n_items > 0 ? (const TermItem*)at(po[p].titems) : nullptr;
     dp.seq_nact = (const int*)at(po[p].snact);
     dp.sp_ptr = hp.sp_ptr.empty() ? nullptr : (const int64_t*)at(po[p].sptr);

@@ -35,20 +35,18 @@ struct NodeRec {
 //   rec  int4[N]    {first sequence, number of actions, value slot, 0}
 //   prm  double4[N] {beta, 1 / beta, log(number of actions), 0}
 //   cbeg int[S + 1] child-slot range of each sequence (CSR over child nodes)
-//   spar int[S]     parent sequence (-1 at a root node)
 // A node's value slot is its position in the child CSR; the r-th root node
 // takes slot C + r (C = number of non-root nodes), so a sequence's children
 // occupy the contiguous slots [cbeg[s], cbeg[s + 1]).
 struct FusedTabLayout {
-  int rec, prm, cbeg, spar, bytes;
+  int rec, prm, cbeg, bytes;
 };
 __host__ __device__ inline FusedTabLayout fused_tab_layout(int n_nodes, int n_seq) {
   FusedTabLayout L;
   L.rec = 0;
   L.prm = 16 * n_nodes;
   L.cbeg = 48 * n_nodes;
-  L.spar = L.cbeg + 4 * ((n_seq + 1 + 3) / 4 * 4);
-  L.bytes = L.spar + 4 * ((n_seq + 3) / 4 * 4);
+  L.bytes = L.cbeg + 4 * ((n_seq + 1 + 3) / 4 * 4);
   return L;
 }
 constexpr int kMaxPartials = 2048 / 4;      // root partial sums per tree (4 hands per block)
@@ -109,24 +107,12 @@ struct DPlayer {
   int n_seq;
   int n_nodes;
   int n_roots;
-  const int* node_first_seq;   // [n_nodes]
-  const int* node_nact;        // [n_nodes]
-  const double* node_beta;     // [n_nodes] dilation weight beta_j
-  const double* node_logn;     // [n_nodes] log(number of actions)
-  const int* seq_parent;       // [n_seq] parent sequence of the sequence's node, -1 at a root
-  const int* child_begin;      // [n_seq + 1] CSR: sequence -> child nodes
-  const int* child;            // child node ids
-  const int* term_begin;       // [n_seq + 1] CSR: sequence -> terminals ending there
-  const int* term_opp;         // opponent's last sequence at the terminal (-1 = empty)
-  const int* term_kind;        // 0 fold, 1 showdown
-  const double* term_coef;     // player 2's chips at the terminal (times the sign at a showdown)
-  const int* roots;            // [n_roots] root node ids
   const double* belief;        // [ld] this player's prior in slot order, 0 in the padding
   const void* fused_tab;       // the table image (FusedTabLayout)
   const SeqRec* seq_rec;       // [n_seq]
   const NodeRec* node_rec;     // [n_nodes]
   const int* anc;              // [n_seq][kMaxDepth] sequences on the path root -> s (s last), -1 after
-  const TermRec* term_rec;     // [n_seq][term_stride] terminals of each sequence, padded with kind -1
+  const TermRec* term_rec;     // [n_seq][term_stride] terminals of each sequence, padded with kind -1 (without rounds)
   int term_stride;             // max terminals per sequence (>= 1)
   const ProdRound* rounds;     // the paired product kernel's rounds, block by block, or null
   const int* round_begin;      // [n_round_blocks + 1]
@@ -186,9 +172,7 @@ struct TreePass {
   void* g_out;     // g_scale (cA gA + cB gB), or null (the epilogue's g_out)
   double g_scale;
   int n_levels;
-  int n_child;
   int level_begin[kMaxDepth + 1];
-  int seq_level_begin[kMaxDepth + 1];  // first sequence of each level's nodes (n_seq past the end)
 };
 
 // Up to kMaxTrees independent passes evaluated by the same launches.
@@ -270,8 +254,7 @@ struct DeviceBlock {  // one device allocation holding many tables
 // Offsets of every table in a game's upload image.
 struct GameOffsets {
   struct Player {
-    size_t first, nact, beta, logn, spar, cbeg, child, tbeg, topp, tkind, tcoef, roots, belief, ftab, trec, anc,
-        titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
+    size_t belief, ftab, trec, anc, titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
   } p[2];
   size_t cbeg, htab, hpos, cslot, hcard;
 };

@@ -1085,11 +1085,8 @@ static void fill_pass_set(const egt_game* g, const Pass* p, int count, PassSet& 
     t.g_out = nullptr;
     t.g_scale = 0.0;
     t.n_levels = hp.n_levels;
-    t.n_child = (int)hp.child.size();
     for (int l = 0; l <= kMaxDepth; ++l) {
-      const int lb = hp.level_begin[std::min(l, hp.n_levels)];
-      t.level_begin[l] = lb;
-      t.seq_level_begin[l] = lb < hp.n_nodes ? hp.node_first_seq[lb] : hp.n_seq;
+      t.level_begin[l] = hp.level_begin[std::min(l, hp.n_levels)];
     }
   }
 }
