@@ -407,11 +407,18 @@ __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdAr
 // round forms only the totals.  The card lists are gathered from the strength
 // order (a thread's quarter of a list, at most kQR slots, sits in registers as
 // indices), so nothing is scattered.  Rounds are dealt to the blocks at build
-// (ProdRound), three blocks a compute unit.  5938 sequences: 1081 hands 51.9 ->
-// 42.7 us, 595 hands 40.8 -> 29.7, 351 hands 31.4 -> 19.3, 105 hands 24.5 ->
-// 14.6; now LDS and VALU are each busy a third of the time (counters), the rest
-// is the latency of a round's chain between barriers at 12 wavefronts per
-// compute unit, which its LDS and registers allow.
+// (ProdRound), three blocks a compute unit.  With more than two hands per thread
+// the evaluation deals them strided over the block, although the scan takes
+// them contiguous: neighbouring lanes then read neighbouring slots of R (fewer
+// bank conflicts) and store whole lines of the row, and a fold reads its reach
+// back from R, which it leaves as it was (1081 hands, contiguous against
+// strided: 5938 sequences 43.2 -> 39.5 us, 1684 sequences 19.4 -> 17.3).
+// 5938 sequences: 1081 hands 51.9 -> 39.5 us, 595 hands 40.8 -> 29.7, 351 hands
+// 31.4 -> 19.3, 105 hands 24.5 -> 14.6.  LDS and VALU are each busy a third of
+// the time (counters), the rest is the latency of a round's chain between
+// barriers at 12 wavefronts per compute unit, which its LDS and registers allow
+// (16 wavefronts, two blocks of 512 threads with half the hands each: 45.3 us;
+// 24 of them spill: 57).
 // Every sum is the one product_kernel takes, in its order.
 struct RoundArgs {
   DPlayer own;
@@ -436,6 +443,10 @@ __global__ __launch_bounds__(kGroupThreads, MINW) void product_pairs_kernel(Roun
   const int gt = threadIdx.x, lane = gt & 63, wig = gt >> 6;
   const int chunk = (n + kGroupThreads - 1) / kGroupThreads;
   const int beg = min(gt * chunk, n), cnt = min(beg + chunk, n) - beg;
+  // the k-th hand this thread evaluates
+  constexpr bool strided = HPT > 2;
+  auto hand = [&](int k) { return strided ? gt + k * kGroupThreads : beg + k; };
+  auto has = [&](int k) { return strided ? gt + k * kGroupThreads < n : k < cnt; };
 
   double bo[HPT];
 #pragma unroll
@@ -518,7 +529,7 @@ __global__ __launch_bounds__(kGroupThreads, MINW) void product_pairs_kernel(Roun
       // the index table from the cache, each round: it arrives behind the scan
       uint4 ht[HPT];
 #pragma unroll
-      for (int k = 0; k < HPT; ++k) ht[k] = k < cnt ? a.H.htab[beg + k] : make_uint4(0u, 0u, 0u, 0u);
+      for (int k = 0; k < HPT; ++k) ht[k] = has(k) ? a.H.htab[hand(k)] : make_uint4(0u, 0u, 0u, 0u);
       // strength order: this thread's contiguous hands, and the group's scan
       double2 rloc[HPT];
       double2 local = make_double2(0.0, 0.0);
@@ -545,12 +556,12 @@ __global__ __launch_bounds__(kGroupThreads, MINW) void product_pairs_kernel(Roun
       const double2 T = R[n];
 #pragma unroll
       for (int k = 0; k < HPT; ++k) {
-        if (k < cnt) {
+        if (has(k)) {
           const uint4 t = ht[k];
           double2 op;
           if (rd.kind == 0) {
             op = T - E[t.y & 0xffffu];
-            if (cph == 2) op = op - E[t.z >> 16] + rloc[k];
+            if (cph == 2) op = op - E[t.z >> 16] + (strided ? R[hand(k)] : rloc[k]);  // a fold leaves the reaches in R
           } else {
             double2 weaker = R[t.w & 0xffffu] - E[t.x & 0xffffu];
             double2 stronger = (T - R[t.w >> 16]) - (E[t.y & 0xffffu] - E[t.x >> 16]);
@@ -575,9 +586,10 @@ __global__ __launch_bounds__(kGroupThreads, MINW) void product_pairs_kernel(Roun
         double* row = a.out + (size_t)rd.seq[j] * ld;
 #pragma unroll
         for (int k = 0; k < HPT; ++k) {
-          if (k < cnt) {
-            const double x = (j == 0 ? acc[k].x : acc[k].y) * (a.own.belief[beg + k] * a.H.invZ);
-            row[beg + k] = x;
+          if (has(k)) {
+            const int i = hand(k);
+            const double x = (j == 0 ? acc[k].x : acc[k].y) * (a.own.belief[i] * a.H.invZ);
+            row[i] = x;
             if constexpr (MAX) top = fmax(top, fabs(x));
           }
         }
