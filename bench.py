@@ -43,12 +43,12 @@ COUNTERS = {
     ("sbr_fused_kernel", "c1"): dict(fetch_kib=1109.1, write_kib=1895.5, fetch_factor=2.0, write_factor=1.0,
                                      source="egt_kernels.hip",
                                      sha256="594da6afbd9db2c1231e15d54b92ca2da7a1ad136d2accfa0da1237faf910e14"),
-    ("product_kernel", "c1"): dict(fetch_kib=1516.3, write_kib=1895.5, fetch_factor=2.0, write_factor=1.0,
+    ("product_kernel", "c1"): dict(fetch_kib=1520.8, write_kib=1895.5, fetch_factor=2.0, write_factor=1.0,
                                    source="egt_product.hip",
-                                   sha256="f9ed996af145dcbe783ed33e2ffbd5bebd3e69bdce311697b2b08513546207d2"),
-    ("product_pairs_kernel", "c3"): dict(fetch_kib=34093.9, write_kib=50612.7, fetch_factor=2.0, write_factor=1.0,
+                                   sha256="47414d3a9292e0f38b6aebcde1789071eef74ba319dae7cc665ec254c27b9cbc"),
+    ("product_pairs_kernel", "c3"): dict(fetch_kib=34088.3, write_kib=50473.0, fetch_factor=2.0, write_factor=1.0,
                                          source="egt_product.hip",
-                                         sha256="f9ed996af145dcbe783ed33e2ffbd5bebd3e69bdce311697b2b08513546207d2"),
+                                         sha256="47414d3a9292e0f38b6aebcde1789071eef74ba319dae7cc665ec254c27b9cbc"),
 }
 
 
