@@ -288,6 +288,15 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
     std::memcpy(img + L.prm + 32 * (size_t)i, prm, sizeof(prm));
   }
   std::memcpy(img + L.cbeg, hp.child_begin.data(), sizeof(int) * (size_t)(ns + 1));
+  // a node's sequences in nearly equal parts of at most kDownRows
+  hp.down.clear();
+  for (int i = 0; i < nn; ++i) {
+    const int na = hp.node_nact[i], parts = (na + kDownRows - 1) / kDownRows;
+    for (int k = 0; k < parts; ++k) {
+      const int beg = na * k / parts;
+      hp.down.push_back(make_int2(hp.node_first_seq[i] + beg, na * (k + 1) / parts - beg));
+    }
+  }
   hp.seq_rec.resize(ns);
   hp.node_rec.resize(nn);
   for (int i = 0; i < nn; ++i) {
@@ -419,6 +428,7 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
     po[p].nrec = add(hp.node_rec.data(), hp.node_rec.size() * sizeof(NodeRec));
     const bool paired = !hp.rounds.empty();  // the other product kernel's records stay on the host
     po[p].trec = add(hp.term_rec.data(), paired ? 0 : hp.term_rec.size() * sizeof(TermRec));
+    po[p].down = add(hp.down.data(), hp.down.size() * sizeof(int2));
     po[p].anc = add(hp.anc.data(), hp.anc.size() * sizeof(int));
     po[p].titems = add(hp.term_items.data(), paired ? 0 : hp.term_items.size() * sizeof(TermItem));
     po[p].snact = add(hp.seq_nact.data(), hp.seq_nact.size() * sizeof(int));
@@ -802,6 +812,8 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.node_rec = (const NodeRec*)at(po[p].nrec);
     dp.term_rec = (const TermRec*)at(po[p].trec);
     dp.anc = (const int*)at(po[p].anc);
+    dp.down = (const int2*)at(po[p].down);
+    dp.n_down = (int)hp.down.size();
     dp.term_stride = std::max(1, hp.max_terms_per_seq);
     dp.n_items = hp.rounds.empty() ? (int)hp.term_items.size() : 0;
     dp.term_items = dp.n_items > 0 ? (const TermItem*)at(po[p].titems) : nullptr;

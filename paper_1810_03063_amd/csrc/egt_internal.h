@@ -15,6 +15,7 @@ namespace egt {
 constexpr int kMaxActions = 16;  // actions per decision node
 constexpr int kMaxDepth = 16;    // sequences on a root-to-leaf chain of one player (and levels)
 constexpr int kMaxTrees = 4;     // trees evaluated by one bottom-up launch
+constexpr int kDownRows = 3;        // sequences of one work item of the top-down pass, at most
 constexpr int kFusedThreads = 512;  // threads of one single-launch pass block, at most
 constexpr int kFusedTasks = 5;      // (sequence, hand) pairs of one of its threads, at most
 
@@ -111,6 +112,8 @@ struct DPlayer {
   const void* fused_tab;       // the table image (FusedTabLayout)
   const SeqRec* seq_rec;       // [n_seq]
   const NodeRec* node_rec;     // [n_nodes]
+  const int2* down;            // [n_down] the top-down pass's work: {first sequence, sequences} of one node
+  int n_down;
   const int* anc;              // [n_seq][kMaxDepth] sequences on the path root -> s (s last), -1 after
   const TermRec* term_rec;     // [n_seq][term_stride] terminals of each sequence, padded with kind -1 (without rounds)
   int term_stride;             // max terminals per sequence (>= 1)
@@ -238,6 +241,7 @@ struct HostPlayer {
   std::vector<ProdRound> rounds;         // rounds of the paired product kernel and their first per block
   std::vector<int> round_begin;
   std::vector<int> anc;                  // [n_seq][kMaxDepth]
+  std::vector<int2> down;                // the top-down pass's work items
   std::vector<int> seq_nact;             // [n_seq] actions of the sequence's node
   std::vector<std::string> seq_keys;
   std::vector<int64_t> sp_ptr;           // general games: CSR rows of A (player 1) or A^T (player 2)
@@ -254,7 +258,7 @@ struct DeviceBlock {  // one device allocation holding many tables
 // Offsets of every table in a game's upload image.
 struct GameOffsets {
   struct Player {
-    size_t belief, ftab, trec, anc, titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
+    size_t belief, ftab, trec, anc, down, titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
   } p[2];
   size_t cbeg, htab, hpos, cslot, hcard;
 };

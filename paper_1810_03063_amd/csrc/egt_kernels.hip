@@ -904,22 +904,23 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 // the sequence's path, multiplied from the root down, then the epilogue
 // comb = (1 - tau) x_prev + tau q.  Padding slots are written 0.
 //
-// One wavefront per (node, 64 x HP hands), HP the hands of a 16-byte
-// access: the sequences of a node share the path above them, so its product is
-// formed once and every sequence costs its own row (a wavefront per sequence
-// spent its time on instructions, 149 vector and 117 scalar ones for three or four
-// products).  The path (root first) and the node's record are wavefront-uniform
-// loads, and every row of the first kStep ancestors and actions is in flight
-// before the first product; kStep 4 takes 74 registers and 7 wavefronts per SIMD
-// instead of 8.  Bound by memory: 5938 sequences x 1081 hands, 102 MB, 21.8 ->
-// 20.3 us (18.1 -> 13.0 in FP32, which read 8 bytes per lane), with the root
-// sums; with the epilogue, 206 MB, 33 us as before.
+// One wavefront per (up to kDownRows sequences of a node, 64 x HP hands), HP the
+// hands of a 16-byte access: the sequences of a node share the path above them,
+// so its product is formed once and every sequence costs its own row (a
+// wavefront per sequence spent its time on instructions, 149 vector and 117
+// scalar ones for three or four products; a wavefront per node left those of
+// ten actions to four rounds of loads: 33.8 us with the epilogue).  The path (root
+// first) and the item are wavefront-uniform loads, and every row of the item and
+// of the first kStep ancestors is in flight before the first product.  Bound by
+// memory: 5938 sequences x 1081 hands, 102 MB, 21.8 -> 19.8 us with the root sums
+// (18.1 -> 12.1 in FP32, which read 8 bytes per lane); with the epilogue, 154 to
+// 206 MB, 32 -> 29.2 us.
 // ---------------------------------------------------------------------------
 struct DownArgs {
   const int* anc;
-  const int4* rec;  // of a node: first sequence, actions
+  const int2* items;  // first sequence, sequences of one node
   const void* QB;
-  int n, ld, n_nodes;
+  int n, ld, n_items;
   void* q_out;
   const void* x_prev;
   double tau;
@@ -944,53 +945,49 @@ __global__ __launch_bounds__(kPassThreads * kDownWaves) void top_down_kernel(Dow
     return;
   }
   const int pos = xcd_spread((int)blockIdx.x - n_sums, (int)gridDim.x - n_sums) * kDownWaves + wave;
-  const int hb = pos / a.n_nodes, v = pos - hb * a.n_nodes;
+  const int hb = pos / a.n_items;
   const int h = HP * (hb * kPassThreads + (int)threadIdx.x);
   if (h >= a.ld) return;  // ld is a multiple of HP
-  const size_t ld = a.ld;
-  const int s0 = a.rec[v].x, na = a.rec[v].y;
+  const int2 item = a.items[pos - hb * a.n_items];
+  const int s0 = item.x, rows = item.y;
+  const size_t ld = a.ld, i0 = (size_t)s0 * ld + h;
   const int* path = a.anc + (size_t)s0 * kMaxDepth;
-  VH above = (VH)(TS)1;
-  bool first = true;
-  for (int i = 0; i < na; i += kStep) {
-    VH own[kStep], xp[kStep];
+  VH own[kDownRows], xp[kDownRows];
 #pragma unroll
-    for (int u = 0; u < kStep; ++u)
-      if (i + u < na) {
-        own[u] = *(const VH*)(QB + (size_t)(s0 + i + u) * ld + h);
-        if (comb_out) xp[u] = *(const VH*)(x_prev + (size_t)(s0 + i + u) * ld + h);
-      }
-    for (int j = 0; first && j < kMaxDepth; j += kStep) {
-      VH f[kStep];
-      bool in[kStep];
-#pragma unroll
-      for (int u = 0; u < kStep; ++u) {
-        const int q = path[j + u];  // s0 closes the path, -1 after it
-        in[u] = q >= 0 && q != s0;
-        if (in[u]) f[u] = *(const VH*)(QB + (size_t)q * ld + h);
-      }
-#pragma unroll
-      for (int u = 0; u < kStep; ++u)
-        if (in[u]) above *= f[u];
-      if (!in[kStep - 1]) break;
+  for (int u = 0; u < kDownRows; ++u)
+    if (u < rows) {
+      own[u] = *(const VH*)(QB + i0 + u * ld);
+      if (comb_out) xp[u] = *(const VH*)(x_prev + i0 + u * ld);
     }
-    first = false;
+  VH above = (VH)(TS)1;
+  for (int j = 0; j < kMaxDepth; j += kStep) {
+    VH f[kStep];
+    bool in[kStep];
+#pragma unroll
+    for (int u = 0; u < kStep; ++u) {
+      const int q = j + u < kMaxDepth ? path[j + u] : -1;  // s0 closes the path, -1 after it
+      in[u] = q >= 0 && q != s0;
+      if (in[u]) f[u] = *(const VH*)(QB + (size_t)q * ld + h);
+    }
 #pragma unroll
     for (int u = 0; u < kStep; ++u)
-      if (i + u < na) {
-        const size_t idx = (size_t)(s0 + i + u) * ld + h;
-        const VH val = above * own[u];
-        VH q, c;
-#pragma unroll
-        for (int e = 0; e < HP; ++e) {
-          const bool live = h + e < a.n;
-          q[e] = live ? val[e] : (TS)0;
-          if (comb_out) c[e] = live ? (TS)(1.0 - a.tau) * xp[u][e] + (TS)a.tau * val[e] : (TS)0;
-        }
-        if (q_out) *(VH*)(q_out + idx) = q;
-        if (comb_out) *(VH*)(comb_out + idx) = c;
-      }
+      if (in[u]) above *= f[u];
+    if (!in[kStep - 1]) break;
   }
+#pragma unroll
+  for (int u = 0; u < kDownRows; ++u)
+    if (u < rows) {
+      const VH val = above * own[u];
+      VH q, c;
+#pragma unroll
+      for (int e = 0; e < HP; ++e) {
+        const bool live = h + e < a.n;
+        q[e] = live ? val[e] : (TS)0;
+        if (comb_out) c[e] = live ? (TS)(1.0 - a.tau) * xp[u][e] + (TS)a.tau * val[e] : (TS)0;
+      }
+      if (q_out) *(VH*)(q_out + i0 + u * ld) = q;
+      if (comb_out) *(VH*)(comb_out + i0 + u * ld) = c;
+    }
 }
 
 // The uniform point: q[s] = q[parent] / n for every sequence s of a node with n
@@ -1204,7 +1201,7 @@ static hipError_t fused_launch(const egt_game* g, const Pass* p, int count, cons
 template <class TS, int HP>
 static hipError_t top_down_launch(const DownArgs& a, hipStream_t s) {
   const int nbx = (a.ld / HP + kPassThreads - 1) / kPassThreads;
-  const dim3 grid((unsigned)(a.sums.count + (nbx * a.n_nodes + kDownWaves - 1) / kDownWaves));
+  const dim3 grid((unsigned)(a.sums.count + (nbx * a.n_items + kDownWaves - 1) / kDownWaves));
   hipLaunchKernelGGL((top_down_kernel<TS, HP>), grid, dim3(kPassThreads, kDownWaves), 0, s, a);
   return hipGetLastError();
 }
@@ -1215,7 +1212,7 @@ static hipError_t top_down(const egt_game* g, int player, const void* QB, void* 
   const DPlayer& P = g->dp[player];
   DownArgs a;
   a.anc = P.anc;
-  a.rec = (const int4*)((const unsigned char*)P.fused_tab + fused_tab_layout(P.n_nodes, P.n_seq).rec);
+  a.items = P.down;
   a.QB = QB;
   a.n = g->n;
   a.ld = g->ld;
@@ -1223,8 +1220,8 @@ static hipError_t top_down(const egt_game* g, int player, const void* QB, void* 
   a.x_prev = x_prev;
   a.tau = tau;
   a.comb_out = comb_out;
-  a.n_nodes = P.n_nodes;
-  if (a.n_nodes == 0) return hipSuccess;
+  a.n_items = P.n_down;
+  if (a.n_items == 0) return hipSuccess;
   a.sums = sums;
   sums.count = 0;
   // the widest access of up to 16 bytes that every row allows
