@@ -40,9 +40,9 @@ CSRC = os.path.join(ROOT, "paper_1810_03063_amd", "csrc")
 # records the SHA-256 of the kernel's source file when the counters were
 # taken; a changed source makes the figure stale, and `traffic` is then null.
 COUNTERS = {
-    ("sbr_fused_kernel", "c1"): dict(fetch_kib=1110.1, write_kib=1895.5, fetch_factor=2.0, write_factor=1.0,
+    ("sbr_fused_kernel", "c1"): dict(fetch_kib=1109.1, write_kib=1895.5, fetch_factor=2.0, write_factor=1.0,
                                      source="egt_kernels.hip",
-                                     sha256="e28b7a51fc802c85bae96462fff3d383cc529fd1f32c9dc43a56e1ff6da9ac8b"),
+                                     sha256="4fa489b7096ccdc55c40c6fdb15b9f73521d1e9f7cefefead916c27e45cbc86d"),
     ("product_kernel", "c1"): dict(fetch_kib=1520.8, write_kib=1895.5, fetch_factor=2.0, write_factor=1.0,
                                    source="egt_product.hip",
                                    sha256="47414d3a9292e0f38b6aebcde1789071eef74ba319dae7cc665ec254c27b9cbc"),

@@ -912,9 +912,10 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 // ten actions to four rounds of loads: 33.8 us with the epilogue).  The path (root
 // first) and the item are wavefront-uniform loads, and every row of the item and
 // of the first kStep ancestors is in flight before the first product.  Bound by
-// memory: 5938 sequences x 1081 hands, 102 MB, 21.8 -> 19.8 us with the root sums
-// (18.1 -> 12.1 in FP32, which read 8 bytes per lane); with the epilogue, 154 to
-// 206 MB, 32 -> 29.2 us.
+// memory: 5938 sequences x 1081 hands, 102 MB, 21.8 -> 18.9 us with the root sums
+// (18.1 -> 11.0 in FP32, which read 8 bytes per lane); with the epilogue, 154 to
+// 206 MB, 32 -> 29.0 us (with the compiler's own 80 registers, 6 wavefronts per
+// SIMD instead of 8: 19.7, 12.1 and 29.4).
 // ---------------------------------------------------------------------------
 struct DownArgs {
   const int* anc;
@@ -929,7 +930,7 @@ struct DownArgs {
 };
 
 template <class TS, int HP>
-__global__ __launch_bounds__(kPassThreads * kDownWaves) void top_down_kernel(DownArgs a) {
+__global__ __launch_bounds__(kPassThreads * kDownWaves, 7) void top_down_kernel(DownArgs a) {
   typedef TS VH __attribute__((ext_vector_type(HP)));
   constexpr int kStep = 3;
   const TS* QB = (const TS*)a.QB;
