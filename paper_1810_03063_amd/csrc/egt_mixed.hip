@@ -143,13 +143,13 @@ __global__ __launch_bounds__(64 * kKWaves) void show_gemm_kernel(GemmArgs a) {
   __syncthreads();
   // one lane per output element: hands fastest, so each row is written coalesced
   const int h = m0 + (tid & 31), cl = tid >> 5, j = n0 + cl;
-  if (j < a.L) {  // a row's padding has prior 0
+  if (j < a.L) {
     float sum = 0.0f;
 #pragma unroll
     for (int w = 0; w < kKWaves; ++w) sum += red[(w * kTile + cl) * kRedStride + (tid & 31)];
     const double c = a.col_coef[j] * a.scale;
     float* row = a.out + (size_t)a.col_own[j] * a.ld;
-    row[h] = (float)(c * a.b_own[h] * (double)sum);
+    row[h] = h < a.n ? (float)(c * a.b_own[h] * (double)sum) : 0.0f;
   }
 }
 
@@ -307,13 +307,14 @@ __global__ __launch_bounds__(256) void show_gemm_tiled_kernel(GemmArgs a) {
   constexpr int kColsPerSweep = 256 / kTM;  // columns covered by one sweep of the threads
   const int row = tid % kTM, h = m0 + row;
   if (h >= a.ld) return;
-  const double bo = a.b_own[h];  // 0 in the padding
+  const bool live = h < a.n;  // the padding is written 0
+  const double bo = a.b_own[h];
 #pragma unroll 4
   for (int col = tid / kTM; col < kTN; col += kColsPerSweep) {
     const int j = n0 + col;
     if (j >= a.L) break;
     const double c = a.col_coef[j] * a.scale;
-    a.out[(size_t)a.col_own[j] * a.ld + h] = (float)(c * bo * (double)ct[col * kTCS + row]);
+    a.out[(size_t)a.col_own[j] * a.ld + h] = live ? (float)(c * bo * (double)ct[col * kTCS + row]) : 0.0f;
   }
 }
 
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
       }
     }
   }
-  // every element of a row has one writer; the padding has prior 0
+  // every element of a row has one writer; the padding is written 0
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const int j = n0 + 16 * c + (lane & 15);
@@ -453,6 +454,9 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
       float x[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = (float)(cf * a.b_own[h + r] * (double)(hi[t][c][r] + lo[t][c][r]));
+      if (h + 4 > a.n)  // on its own: selected with the products, their loads became conditional (28 -> 30.6 us)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = h + r < a.n ? x[r] : 0.0f;
       *(float4*)(row + h) = make_float4(x[0], x[1], x[2], x[3]);
     }
   }
