@@ -57,6 +57,14 @@ __device__ inline void split8(const float r[8], bf16x8& hi, bf16x8& lo) {
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
+// Reach 0 for the hands of k .. k + 7 past the last one: what an input holds in its
+// padding is not read as a value (0 x NaN would reach every row).
+__device__ inline void clear_padding(float r[8], int k, int n) {
+  if (k + 8 > n)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = k + e < n ? r[e] : 0.0f;
+}
+
 struct GemmArgs {
   const unsigned short* W;  // [ld][ld] BF16 bits, row h, contiguous h'
   int n, ld;
@@ -125,8 +133,9 @@ __global__ __launch_bounds__(64 * kKWaves) void show_gemm_kernel(GemmArgs a) {
     for (int u = 0; u < kBatch; ++u) {
       if (base + u * kKWaves >= nk) break;  // uniform within the wave
       // FP32 reach of the 8 hands, split into BF16 hi + lo
-      const float r[8] = {b0[u].x * v0[u].x, b0[u].y * v0[u].y, b0[u].z * v0[u].z, b0[u].w * v0[u].w,
-                          b1[u].x * v1[u].x, b1[u].y * v1[u].y, b1[u].z * v1[u].z, b1[u].w * v1[u].w};
+      float r[8] = {b0[u].x * v0[u].x, b0[u].y * v0[u].y, b0[u].z * v0[u].z, b0[u].w * v0[u].w,
+                    b1[u].x * v1[u].x, b1[u].y * v1[u].y, b1[u].z * v1[u].z, b1[u].w * v1[u].w};
+      clear_padding(r, (base + u * kKWaves) * 16 + 8 * half, a.n);
       bf16x8 hi, lo;
       split8(r, hi, lo);
       const bf16x8 am = *(const bf16x8*)&av[u];
@@ -236,8 +245,9 @@ __global__ __launch_bounds__(256) void show_gemm_tiled_kernel(GemmArgs a) {
     *(uint4*)&d.a[arow * kTKS + ak + 8] = q.a1;
     const int kb = s * kTK + bk;
     const float4 b0 = *(const float4*)&bopp[kb], b1 = *(const float4*)&bopp[kb + 4];
-    const float r[8] = {b0.x * q.v0.x, b0.y * q.v0.y, b0.z * q.v0.z, b0.w * q.v0.w,
-                        b1.x * q.v1.x, b1.y * q.v1.y, b1.z * q.v1.z, b1.w * q.v1.w};
+    float r[8] = {b0.x * q.v0.x, b0.y * q.v0.y, b0.z * q.v0.z, b0.w * q.v0.w,
+                  b1.x * q.v1.x, b1.y * q.v1.y, b1.z * q.v1.z, b1.w * q.v1.w};
+    clear_padding(r, kb, a.n);
     bf16x8 hi, lo;
     split8(r, hi, lo);
     *(bf16x8*)&d.bh[bcol * kTKS + bk] = hi;
@@ -363,12 +373,13 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
   const int total = kColsBlock * nk8;
   for (int base = tid; base < total; base += 64 * kColsWaves * kU) {
     float4 v[kU][2], b[kU][2];
-    int at[kU];
+    int at[kU], k0[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int i = base + u * 64 * kColsWaves;
       const int col = i / nk8, kc = i - col * nk8, j = n0 + col;
       at[u] = i < total ? kc * kColsBlock + (col ^ (kc & 7)) : -1;
+      k0[u] = 8 * kc;
       const bool ok = i < total && j < a.L;
       const float fill = ok ? 1.0f : 0.0f;  // the empty sequence has v = 1; no column has reach 0
       v[u][0] = v[u][1] = make_float4(fill, fill, fill, fill);
@@ -389,8 +400,9 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
     for (int u = 0; u < kU; ++u) {
       if (at[u] < 0) continue;
       const float4 b0 = b[u][0], b1 = b[u][1], v0 = v[u][0], v1 = v[u][1];
-      const float r[8] = {b0.x * v0.x, b0.y * v0.y, b0.z * v0.z, b0.w * v0.w,
-                          b1.x * v1.x, b1.y * v1.y, b1.z * v1.z, b1.w * v1.w};
+      float r[8] = {b0.x * v0.x, b0.y * v0.y, b0.z * v0.z, b0.w * v0.w,
+                    b1.x * v1.x, b1.y * v1.y, b1.z * v1.z, b1.w * v1.w};
+      clear_padding(r, k0[u], a.n);
       bf16x8 hi, lo;
       split8(r, hi, lo);
       Bh[at[u]] = __builtin_bit_cast(uint4, hi);

@@ -1,8 +1,8 @@
 """The padding of the precision form's products, entries n_hands .. ld - 1 of
 every row: written 0 whatever the other entries are (an infinite strategy entry
-reaches its rows, not their padding).  Games for each of the three showdown
-GEMMs, with hand counts that leave a partly filled unit of eight hands, and
-one-card hands whose rows are mostly padding."""
+reaches its rows, not their padding), and not read from an input.  Games for
+each of the three showdown GEMMs, with hand counts that leave a partly filled
+unit of eight hands, and one-card hands whose rows are mostly padding."""
 import numpy as np
 import pytest
 
@@ -64,4 +64,18 @@ def test_written_zero(egt, name, value):
         if value is not None:
             assert not torch.isfinite(out[:, :G.n]).all()
         assert torch.all(out[:, G.n:].contiguous().view(torch.int32) == 0), "the padding holds +0.0"
+    G.close()
+
+
+@pytest.mark.parametrize("name", list(GAMES))
+def test_input_padding_is_ignored(egt, name):
+    G = egt.Game(GAMES[name]())
+    print(f"[case] {name}: {G.n} hands, {G.n_seq} sequences", flush=True)
+    for p in (0, 1):
+        v = strategy(G, 1 - p, 4)
+        want = product(egt, G, p, v)
+        assert torch.isfinite(want).all()
+        for value in (np.nan, np.inf):
+            v[:, G.n:] = value
+            assert torch.equal(product(egt, G, p, v), want)
     G.close()
