@@ -57,6 +57,14 @@ __device__ inline void split8(const float r[8], bf16x8& hi, bf16x8& lo) {
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
+// Four floats of a caller's vector.  Its rows need not be 16-byte aligned (callers
+// promise 8 bytes); on gfx950 the access is one 16-byte instruction all the same.
+typedef float rowx4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 load_row4(const float* p) {
+  const rowx4 x = *(const rowx4*)p;
+  return make_float4(x.x, x.y, x.z, x.w);
+}
+
 // Reach 0 for the hands of k .. k + 7 past the last one: what an input holds in its
 // padding is not read as a value (0 x NaN would reach every row).
 __device__ inline void clear_padding(float r[8], int k, int n) {
@@ -121,8 +129,8 @@ __global__ __launch_bounds__(64 * kKWaves) void show_gemm_kernel(GemmArgs a) {
         av[u] = *(const uint4*)(wrow + ks * 16);
         if (cvalid) {
           if (vrow) {
-            v0[u] = *(const float4*)(vrow + k0);
-            v1[u] = *(const float4*)(vrow + k0 + 4);
+            v0[u] = load_row4(vrow + k0);
+            v1[u] = load_row4(vrow + k0 + 4);
           }
           b0[u] = *(const float4*)(a.b_opp32 + k0);
           b1[u] = *(const float4*)(a.b_opp32 + k0 + 4);
@@ -236,8 +244,8 @@ __global__ __launch_bounds__(256) void show_gemm_tiled_kernel(GemmArgs a) {
     const float vfill = bcol_ok ? 1.0f : 0.0f;
     q.v0 = q.v1 = make_float4(vfill, vfill, vfill, vfill);
     if (vsrc) {
-      q.v0 = *(const float4*)(vsrc + k0 + bk);
-      q.v1 = *(const float4*)(vsrc + k0 + bk + 4);
+      q.v0 = load_row4(vsrc + k0 + bk);
+      q.v1 = load_row4(vsrc + k0 + bk + 4);
     }
   };
   auto store_step = [&](const StepRegs& q, int s, TiledStage& d) {
@@ -387,9 +395,9 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
       if (ok) {
         const int o = a.col_opp[j];
         if (o >= 0) {
-          const float4* p = (const float4*)(a.v_opp + (size_t)o * a.ld + 8 * kc);
-          v[u][0] = p[0];
-          v[u][1] = p[1];
+          const float* p = a.v_opp + (size_t)o * a.ld + 8 * kc;
+          v[u][0] = load_row4(p);
+          v[u][1] = load_row4(p + 4);
         }
         const float4* q = (const float4*)(a.b_opp32 + 8 * kc);
         b[u][0] = q[0];
@@ -469,7 +477,7 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
       if (h + 4 > a.n)  // on its own: selected with the products, their loads became conditional (28 -> 30.6 us)
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[r] = h + r < a.n ? x[r] : 0.0f;
-      *(float4*)(row + h) = make_float4(x[0], x[1], x[2], x[3]);
+      *(rowx4*)(row + h) = (rowx4){x[0], x[1], x[2], x[3]};
     }
   }
 }
