@@ -310,17 +310,20 @@ using namespace egt;
 
 namespace {
 
+// Pairs per thread as in the fused smoothed best response.
 template <int HB>
-void launch_regret_fused(const RegretFusedArgs& a, dim3 grid, size_t lds, int pairs, hipStream_t s) {
+hipError_t launch_regret_fused(const RegretFusedArgs& a, dim3 grid, size_t lds, int pairs, hipStream_t s) {
   const dim3 block((unsigned)std::min(kFusedThreads, std::max(256, (pairs + 63) / 64 * 64)));
+  if (pairs > (HB == 4 ? kFusedTasks : 3) * kFusedThreads) return hipErrorInvalidValue;
   if (pairs <= kFusedThreads)
     hipLaunchKernelGGL((regret_fused_kernel<HB, 1>), grid, block, lds, s, a);
   else if (pairs <= 2 * kFusedThreads)
     hipLaunchKernelGGL((regret_fused_kernel<HB, 2>), grid, block, lds, s, a);
-  else if (pairs <= 3 * kFusedThreads)
+  else if (HB != 4 || pairs <= 3 * kFusedThreads)
     hipLaunchKernelGGL((regret_fused_kernel<HB, 3>), grid, block, lds, s, a);
-  else
-    hipLaunchKernelGGL((regret_fused_kernel<HB, 5>), grid, block, lds, s, a);
+  else if constexpr (HB == 4)
+    hipLaunchKernelGGL((regret_fused_kernel<HB, kFusedTasks>), grid, block, lds, s, a);
+  return hipGetLastError();
 }
 
 // One update of player p; its current strategy joins the average with
@@ -350,13 +353,9 @@ int cfr_update(egt_cfr* c, int p, double tau, hipStream_t s) {
     a.plus = c->variant != EGT_CFR_RM;
     const size_t lds = sizeof(double) * (size_t)hb * ((size_t)hp.n_seq + 2 * (size_t)hp.n_nodes + 3 * kFusedPad);
     const dim3 grid((unsigned)fused_hblocks(g));
-    if (hb == 4)
-      launch_regret_fused<4>(a, grid, lds, pairs, s);
-    else if (hb == 16)
-      launch_regret_fused<16>(a, grid, lds, pairs, s);
-    else
-      launch_regret_fused<1>(a, grid, lds, pairs, s);
-    EGT_HIP(hipGetLastError());
+    EGT_HIP(hb == 4    ? launch_regret_fused<4>(a, grid, lds, pairs, s)
+            : hb == 16 ? launch_regret_fused<16>(a, grid, lds, pairs, s)
+                       : launch_regret_fused<1>(a, grid, lds, pairs, s));
     return EGT_OK;
   }
   EGT_HIP(launch_axpby(vec_elems_of(g, p), 1.0 - tau, c->AVG[p], tau, c->X[p], c->AVG[p], s));

@@ -1118,18 +1118,21 @@ bool fits_fused(const egt_game* g) {
          fused_lds_bytes(g->fused_hands, nodes, seqs, false) <= (size_t)g->lds_per_block;
 }
 
-// 1, 2, 3 or 5 (sequence, hand) pairs per thread, the fewest that 512 threads allow.
+// 1, 2, 3 or 5 (sequence, hand) pairs per thread, the fewest that 512 threads
+// allow; more than three only with four hands per block (fits_fused).
 template <int HB, class TG>
-static void fused_launch_hands(const FusedArgs& a, int pairs, dim3 grid, size_t lds, hipStream_t s) {
+static hipError_t fused_launch_hands(const FusedArgs& a, int pairs, dim3 grid, size_t lds, hipStream_t s) {
   const dim3 block((unsigned)std::min(kFusedThreads, std::max(256, (pairs + 63) / 64 * 64)));
+  if (pairs > (HB == 4 ? kFusedTasks : 3) * kFusedThreads) return hipErrorInvalidValue;
   if (pairs <= kFusedThreads)
     hipLaunchKernelGGL((sbr_fused_kernel<HB, 1, TG>), grid, block, lds, s, a);
   else if (pairs <= 2 * kFusedThreads)
     hipLaunchKernelGGL((sbr_fused_kernel<HB, 2, TG>), grid, block, lds, s, a);
-  else if (pairs <= 3 * kFusedThreads)
+  else if (HB != 4 || pairs <= 3 * kFusedThreads)
     hipLaunchKernelGGL((sbr_fused_kernel<HB, 3, TG>), grid, block, lds, s, a);
-  else
-    hipLaunchKernelGGL((sbr_fused_kernel<HB, 5, TG>), grid, block, lds, s, a);
+  else if constexpr (HB == 4)
+    hipLaunchKernelGGL((sbr_fused_kernel<HB, kFusedTasks, TG>), grid, block, lds, s, a);
+  return hipGetLastError();
 }
 
 // All passes in one launch of the fused kernel.
@@ -1190,13 +1193,9 @@ static hipError_t fused_launch(const egt_game* g, const Pass* p, int count, cons
   const dim3 grid((unsigned)(a.n_hblocks * nt));
   const size_t lds = fused_lds_bytes(hb, a.cap_nodes, a.cap_seqs, in_kernel);
   const int pairs = a.cap_seqs * hb;
-  if (hb == 4)
-    fused_launch_hands<4, TG>(a, pairs, grid, lds, s);
-  else if (hb == 16)
-    fused_launch_hands<16, TG>(a, pairs, grid, lds, s);
-  else
-    fused_launch_hands<1, TG>(a, pairs, grid, lds, s);
-  return hipGetLastError();
+  return hb == 4    ? fused_launch_hands<4, TG>(a, pairs, grid, lds, s)
+         : hb == 16 ? fused_launch_hands<16, TG>(a, pairs, grid, lds, s)
+                    : fused_launch_hands<1, TG>(a, pairs, grid, lds, s);
 }
 
 template <class TS, int HP>
