@@ -134,7 +134,7 @@ def product_roofline(egt, torch, G, reps, config):
     n_fold, n_show = G.terminals()
     bytes_ = 8.0 * G.n * ((n_fold + n_show) + G.n_seq[0])
     gbs = bytes_ / avg_s / 1e9
-    kernel = "product_pairs_kernel" if min(G.n_seq) > 640 else "product_kernel"
+    kernel = "product_pairs_kernel" if G.routes()["paired_product"] else "product_kernel"
     traffic = traffic_bytes(kernel, config)
     return dict(kernel=kernel, bound="hbm", achieved=round(gbs, 3), peak=HBM_PEAK_GBS, unit="GB/s",
                 frac=round(gbs / HBM_PEAK_GBS, 6), traffic=round(traffic) if traffic else None,
@@ -147,8 +147,8 @@ def sbr_roofline(egt, torch, G, reps, config):
     """The smoothed best response, launched as egt_smoothed_br without the
     value on a product A y.  Algorithmic bytes per launch: the gradient read
     and the strategy written, 8-byte doubles over every (sequence, hand) of the
-    player: 16 * n_seq * n.  Trees whose tables fit one block's LDS run it as
-    one launch (sbr_fused_kernel), larger ones level by level."""
+    player: 16 * n_seq * n.  Small trees run it as one launch
+    (sbr_fused_kernel), larger ones level by level."""
     y = egt.uniform(G, 1)
     g = egt.gradient(G, 0, y)
     q = G.empty(0)
@@ -156,7 +156,7 @@ def sbr_roofline(egt, torch, G, reps, config):
     avg_s = _timed(torch, lambda: egt.smoothed_br(G, 0, g, mu, q, want_value=False), reps)
     bytes_ = 16.0 * G.n_seq[0] * G.n
     gbs = bytes_ / avg_s / 1e9
-    fused = G.n_seq[0] < 1000
+    fused = G.routes()["pass_hands"] > 0
     kernel = "sbr_fused_kernel" if fused else "level-path passes"
     traffic = traffic_bytes(kernel, config) if fused else None
     return dict(kernel=kernel, bound="hbm", achieved=round(gbs, 3), peak=HBM_PEAK_GBS, unit="GB/s",

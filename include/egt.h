@@ -177,6 +177,13 @@ int egt_game_layout(const egt_game* game, int player, int32_t* hand_perm, char* 
 /* Total number of terminal histories (fold, showdown) of the game. */
 int egt_game_terminals(const egt_game* game, int64_t* n_fold, int64_t* n_show);
 
+/* Which kernels the game's operations run (host outputs, any may be NULL):
+ * *paired_product = 1 when egt_gradient takes two terminals per round, else 0;
+ * *pass_hands = hands per block when the smoothed best response is one launch,
+ * 0 when it is a launch per level; *column_gemm = 1 when egt_gradient_mixed
+ * evaluates the showdowns by column blocks, else 0. */
+int egt_game_routes(const egt_game* game, int32_t* paired_product, int32_t* pass_hands, int32_t* column_gemm);
+
 /* ------------------------------------------------------------------------ */
 /* Hot-path operations                                                        */
 /* ------------------------------------------------------------------------ */

@@ -148,6 +148,14 @@ int egt_game_terminals(const egt_game* g, int64_t* n_fold, int64_t* n_show) {
   return EGT_OK;
 }
 
+int egt_game_routes(const egt_game* g, int32_t* paired_product, int32_t* pass_hands, int32_t* column_gemm) {
+  if (!g) return fail(EGT_EINVAL, "null game");
+  if (paired_product) *paired_product = g->dp[0].rounds ? 1 : 0;
+  if (pass_hands) *pass_hands = g->fused_passes ? g->fused_hands : 0;
+  if (column_gemm) *column_gemm = !g->general && takes_column_gemm(g) ? 1 : 0;
+  return EGT_OK;
+}
+
 int egt_gradient(const egt_game* g, int player, const double* strat_other, double* grad_out,
                  hipStream_t stream) {
   if (!g || bad_player(player) || !strat_other || !grad_out)

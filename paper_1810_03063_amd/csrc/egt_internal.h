@@ -430,6 +430,8 @@ hipError_t launch_gradient_fold_f32(const egt_game* g, int player, const float* 
 // the product: showdown part (BF16 hi/lo MFMA GEMM, FP32 output) + fold part
 // (FP32 O(n)).
 int ensure_mixed_tables(const egt_game* g);
+// Whether both players' showdowns are evaluated by column blocks.
+bool takes_column_gemm(const egt_game* g);
 // The same tables as a host image (no device work): its size, then the upload
 // into caller memory (owned = false: the memory is not the game's to free).
 int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, MixedOffsets* off);

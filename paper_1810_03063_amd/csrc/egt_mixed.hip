@@ -484,6 +484,11 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
 
 }  // namespace
 
+bool takes_column_gemm(const egt_game* g) {
+  auto columns = [&](int p) { return std::count(g->hp[p].term_kind.begin(), g->hp[p].term_kind.end(), 1); };
+  return g->ld <= kColsMaxLd && columns(0) >= kColsMinColumns && columns(1) >= kColsMinColumns;
+}
+
 // W (BF16 bits; in the column-block GEMM's operand order when both players take
 // it), and per player the FP32 prior, the showdown column lists and the fold
 // rounds, as one host image: W at 0, the rest at `off`.
@@ -538,7 +543,7 @@ int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, Mixed
         }
   }
   // slot order: strength ascending; compatibility from the cards of the slots
-  off->by_columns = kpad <= kColsMaxLd && (int)own[0].size() >= kColsMinColumns && (int)own[1].size() >= kColsMinColumns;
+  off->by_columns = takes_column_gemm(g);
   std::vector<unsigned short> W((size_t)kpad * kpad, 0);
   for (int i = 0; i < n; ++i) {
     for (int k = 0; k < n; ++k) {

@@ -93,6 +93,8 @@ _free_game = _decl("egt_free_game", ctypes.c_int, _p)
 _game_dims = _decl("egt_game_dims", ctypes.c_int, _p, ctypes.c_int, ctypes.POINTER(_i64),
                    ctypes.POINTER(_i64), ctypes.POINTER(_i64), ctypes.POINTER(_i64))
 _game_layout = _decl("egt_game_layout", ctypes.c_int, _p, ctypes.c_int, _p, _p, _i64, ctypes.POINTER(_i64))
+_game_routes = _decl("egt_game_routes", ctypes.c_int, _p, ctypes.POINTER(_i32), ctypes.POINTER(_i32),
+                     ctypes.POINTER(_i32))
 _game_terminals = _decl("egt_game_terminals", ctypes.c_int, _p, ctypes.POINTER(_i64), ctypes.POINTER(_i64))
 _gradient = _decl("egt_gradient", ctypes.c_int, _p, ctypes.c_int, _p, _p, _p)
 _smoothed_br = _decl("egt_smoothed_br", ctypes.c_int, _p, ctypes.c_int, _p, _f64, _p, _p, _p)
@@ -154,7 +156,7 @@ EXPORTED = [
     "egt_batch_poll", "egt_batch_retire", "egt_batch_usage", "egt_saddle_gap_noalloc",
     "egt_batch_strategies", "egt_cfr_create", "egt_cfr_destroy", "egt_cfr_step", "egt_cfr_gap", "egt_cfr_get",
     "egt_cfr_solve", "egt_batch_admit_desc", "egt_fom_create", "egt_fom_destroy", "egt_fom_step", "egt_fom_get", "egt_fom_gap",
-    "egt_build_general_game",
+    "egt_build_general_game", "egt_game_routes",
 ]
 
 
@@ -259,6 +261,12 @@ class Game:
         f, s = _i64(), _i64()
         _check(_game_terminals(self._h, ctypes.byref(f), ctypes.byref(s)))
         return f.value, s.value
+
+    def routes(self):
+        """Which kernels the game's operations run (egt_game_routes)."""
+        r = [_i32(), _i32(), _i32()]
+        _check(_game_routes(self._h, *(ctypes.byref(x) for x in r)))
+        return dict(zip(("paired_product", "pass_hands", "column_gemm"), (x.value for x in r)))
 
     def empty(self, p, device="cuda", dtype=torch.float64):
         return torch.zeros((self.n_seq[p], self.ld), dtype=dtype, device=device)
