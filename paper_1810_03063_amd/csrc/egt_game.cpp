@@ -261,11 +261,12 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
   if (mx > kMaxDepth) return fail(EGT_EINVAL, "a player's sequence chain is deeper than 16");
   hp.max_chain = mx;
   // root-first path of every sequence, for the fully parallel top-down pass
-  hp.anc.assign((size_t)ns * kMaxDepth, -1);
+  hp.anc_stride = (mx + kPathStep - 1) / kPathStep * kPathStep;
+  hp.anc.assign((size_t)ns * hp.anc_stride, -1);
   for (int s = 0; s < ns; ++s) {
     int path[kMaxDepth], d = 0;
     for (int q = s; q >= 0; q = hp.seq_parent[q]) path[d++] = q;
-    for (int j = 0; j < d; ++j) hp.anc[(size_t)s * kMaxDepth + j] = path[d - 1 - j];
+    for (int j = 0; j < d; ++j) hp.anc[(size_t)s * hp.anc_stride + j] = path[d - 1 - j];
   }
   hp.max_level_width = 0;
   hp.level_max_act.assign(hp.n_levels, 0);
@@ -391,8 +392,7 @@ const char* last_error_cstr() { return g_last_error.c_str(); }
 // The upload image of every table (one device block), the device views' sizes
 // and the device attributes the launchers use.
 int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vector<uint4>& htab,
-                 const std::vector<unsigned>& hpos, const std::vector<unsigned short>& card_slot,
-                 const std::vector<double> (&b)[2]) {
+                 const std::vector<unsigned>& hpos, const std::vector<double> (&b)[2]) {
   const int n = g->n, cph = g->cph, nc = g->n_cards;
   const double Z = g->Z;
   EGT_HIP(hipGetDevice(&g->device));
@@ -402,6 +402,7 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   EGT_HIP(hipDeviceGetAttribute(&g->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, g->device));
   if (g->lds_per_block < 64 * 1024) g->lds_per_block = 64 * 1024;
   if (g->lds_per_cu < g->lds_per_block) g->lds_per_cu = g->lds_per_block;
+  g->fused_passes = fits_fused(g);
   const int round_blocks = g->general ? 0 : paired_product_blocks(g, card_begin);
   for (int p = 0; p < 2 && round_blocks > 0; ++p) schedule_rounds(g->hp[p], round_blocks);
   struct Piece {
@@ -421,11 +422,13 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   for (int p = 0; p < 2; ++p) {
     HostPlayer& hp = g->hp[p];
     po[p].belief = add(b[p].data(), b[p].size() * sizeof(double));
-    po[p].ftab = add(hp.fused_tab.data(), hp.fused_tab.size());
+    // the level path and the single-launch passes read tables of their own
+    const bool levels = !g->fused_passes;
+    po[p].ftab = add(hp.fused_tab.data(), levels ? hp.fused_tab.size() : 0);
     po[p].rounds = add(hp.rounds.data(), hp.rounds.size() * sizeof(ProdRound));
     po[p].rbeg = add(hp.round_begin.data(), hp.round_begin.size() * sizeof(int));
-    po[p].srec = add(hp.seq_rec.data(), hp.seq_rec.size() * sizeof(SeqRec));
-    po[p].nrec = add(hp.node_rec.data(), hp.node_rec.size() * sizeof(NodeRec));
+    po[p].srec = add(hp.seq_rec.data(), levels ? 0 : hp.seq_rec.size() * sizeof(SeqRec));
+    po[p].nrec = add(hp.node_rec.data(), levels ? 0 : hp.node_rec.size() * sizeof(NodeRec));
     const bool paired = !hp.rounds.empty();  // the other product kernel's records stay on the host
     po[p].trec = add(hp.term_rec.data(), paired ? 0 : hp.term_rec.size() * sizeof(TermRec));
     po[p].down = add(hp.down.data(), hp.down.size() * sizeof(int2));
@@ -439,11 +442,7 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   g->offs.cbeg = add(card_begin.data(), card_begin.size() * sizeof(int));
   g->offs.htab = add(htab.data(), htab.size() * sizeof(uint4));
   g->offs.hpos = add(hpos.data(), hpos.size() * sizeof(unsigned));
-  g->offs.cslot = add(card_slot.data(), card_slot.size() * sizeof(unsigned short));
-  std::vector<unsigned> hand_cards(n);
-  for (int i = 0; i < n; ++i)
-    hand_cards[i] = (unsigned)g->slot_cards[(size_t)i * cph] | (cph == 2 ? (unsigned)g->slot_cards[(size_t)i * cph + 1] << 16 : 0u);
-  g->offs.hcard = add(hand_cards.data(), hand_cards.size() * sizeof(unsigned));
+  g->offs.cslot = add(g->card_slot.data(), round_blocks > 0 ? g->card_slot.size() * sizeof(unsigned short) : 0);
 
   g->img.assign(total, 0);
   for (const Piece& pc : pieces)
@@ -454,7 +453,6 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   g->dh.n_cards = nc;
   g->dh.n_card_slots = card_begin[nc] + nc;
   g->dh.invZ = 1.0 / Z;
-  g->fused_passes = fits_fused(g);
   return EGT_OK;
 }
 
@@ -666,9 +664,8 @@ int build_game_host(const egt_game_desc* d, egt_game** out) {
   if (!(Z > 0) || !std::isfinite(Z)) return fail(EGT_EINVAL, "no compatible deal has positive belief");
   g->Z = Z;
 
-  std::vector<unsigned short> card_slot;
-  for (const auto& L : lists) card_slot.insert(card_slot.end(), L.begin(), L.end());
-  int rc = finish_image(g, card_begin, htab, hpos, card_slot, b);
+  for (const auto& L : lists) g->card_slot.insert(g->card_slot.end(), L.begin(), L.end());
+  int rc = finish_image(g, card_begin, htab, hpos, b);
   if (rc) return rc;
   *out = guard.release();
   return EGT_OK;
@@ -779,7 +776,7 @@ int build_general_host(const egt_general_desc* d, egt_game** out) {
   const std::vector<int> card_begin = {0, 1};
   const std::vector<uint4> htab = {make_uint4(0u, 0u, 0u, 0u)};
   const std::vector<unsigned> hpos = {0u};
-  const int rc = finish_image(g, card_begin, htab, hpos, {0}, b);
+  const int rc = finish_image(g, card_begin, htab, hpos, b);
   if (rc) return rc;
   *out = guard.release();
   return EGT_OK;
@@ -804,14 +801,16 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.n_nodes = hp.n_nodes;
     dp.n_roots = (int)hp.roots.size();
     dp.belief = (const double*)at(po[p].belief);
-    dp.fused_tab = at(po[p].ftab);
+    const bool levels = !g->fused_passes;
+    dp.fused_tab = levels ? at(po[p].ftab) : nullptr;
     dp.n_round_blocks = hp.rounds.empty() ? 0 : (int)hp.round_begin.size() - 1;
     dp.rounds = hp.rounds.empty() ? nullptr : (const ProdRound*)at(po[p].rounds);
     dp.round_begin = (const int*)at(po[p].rbeg);
-    dp.seq_rec = (const SeqRec*)at(po[p].srec);
-    dp.node_rec = (const NodeRec*)at(po[p].nrec);
+    dp.seq_rec = levels ? nullptr : (const SeqRec*)at(po[p].srec);
+    dp.node_rec = levels ? nullptr : (const NodeRec*)at(po[p].nrec);
     dp.term_rec = (const TermRec*)at(po[p].trec);
     dp.anc = (const int*)at(po[p].anc);
+    dp.anc_stride = hp.anc_stride;
     dp.down = (const int2*)at(po[p].down);
     dp.n_down = (int)hp.down.size();
     dp.term_stride = std::max(1, hp.max_terms_per_seq);
@@ -826,7 +825,6 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
   g->dh.htab = (const uint4*)at(g->offs.htab);
   g->dh.hpos = (const unsigned*)at(g->offs.hpos);
   g->dh.card_slot = (const unsigned short*)at(g->offs.cslot);
-  g->dh.hand_cards = (const unsigned*)at(g->offs.hcard);
   return EGT_OK;
 }
 

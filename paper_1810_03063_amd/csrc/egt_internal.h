@@ -16,6 +16,7 @@ constexpr int kMaxActions = 16;  // actions per decision node
 constexpr int kMaxDepth = 16;    // sequences on a root-to-leaf chain of one player (and levels)
 constexpr int kMaxTrees = 4;     // trees evaluated by one bottom-up launch
 constexpr int kDownRows = 3;        // sequences of one work item of the top-down pass, at most
+constexpr int kPathStep = 3;        // ancestors whose rows the top-down pass requests at once
 constexpr int kFusedThreads = 512;  // threads of one single-launch pass block, at most
 constexpr int kFusedTasks = 5;      // (sequence, hand) pairs of one of its threads, at most
 
@@ -109,12 +110,13 @@ struct DPlayer {
   int n_nodes;
   int n_roots;
   const double* belief;        // [ld] this player's prior in slot order, 0 in the padding
-  const void* fused_tab;       // the table image (FusedTabLayout)
-  const SeqRec* seq_rec;       // [n_seq]
-  const NodeRec* node_rec;     // [n_nodes]
+  const void* fused_tab;       // the table image (FusedTabLayout), in games of the level path
+  const SeqRec* seq_rec;       // [n_seq], in games of the single-launch passes
+  const NodeRec* node_rec;     // [n_nodes], the same
   const int2* down;            // [n_down] the top-down pass's work: {first sequence, sequences} of one node
   int n_down;
-  const int* anc;              // [n_seq][kMaxDepth] sequences on the path root -> s (s last), -1 after
+  const int* anc;              // [n_seq][anc_stride] sequences on the path root -> s (s last), -1 after
+  int anc_stride;              // the longest path, rounded up to kPathStep
   const TermRec* term_rec;     // [n_seq][term_stride] terminals of each sequence, padded with kind -1 (without rounds)
   int term_stride;             // max terminals per sequence (>= 1)
   const ProdRound* rounds;     // the paired product kernel's rounds, block by block, or null
@@ -153,8 +155,7 @@ struct DHands {
   const int* card_begin;       // [n_cards + 1]
   const uint4* htab;           // [n]
   const unsigned* hpos;        // [n]
-  const unsigned short* card_slot;  // [card_begin[n_cards]] the slots holding each card, ascending
-  const unsigned* hand_cards;       // [n] the hand's cards a | b << 16
+  const unsigned short* card_slot;  // [card_begin[n_cards]] the slots holding each card, ascending (with rounds)
   double invZ;                 // 1 / sum of b1 b2 over compatible deals
 };
 
@@ -240,7 +241,8 @@ struct HostPlayer {
   std::vector<TermItem> term_items;      // work items of the looping product kernel (at most two terminals each)
   std::vector<ProdRound> rounds;         // rounds of the paired product kernel and their first per block
   std::vector<int> round_begin;
-  std::vector<int> anc;                  // [n_seq][kMaxDepth]
+  std::vector<int> anc;                  // [n_seq][anc_stride]
+  int anc_stride = 0;
   std::vector<int2> down;                // the top-down pass's work items
   std::vector<int> seq_nact;             // [n_seq] actions of the sequence's node
   std::vector<std::string> seq_keys;
@@ -260,7 +262,7 @@ struct GameOffsets {
   struct Player {
     size_t belief, ftab, trec, anc, down, titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
   } p[2];
-  size_t cbeg, htab, hpos, cslot, hcard;
+  size_t cbeg, htab, hpos, cslot;
 };
 
 // Scratch of the single-operation entry points (egt_smoothed_br,
@@ -277,17 +279,17 @@ struct Workspace {
   double* hpart_dev = nullptr;
 };
 
-// One round of the precision form's fold kernel: a fold terminal of each of one or
-// four sequences (fields as ProdRound); bit j of `add`: sequence j's row already holds
-// its showdown.
-struct FoldRound {
-  int opp[4];
-  int seq[4];
-  float coef[4];
-  int kind;  // 0 fold, -1 no terminal: zero rows
-  int add;
-  int last;
-  int pad;
+// One round of the precision form's fold kernel: a fold terminal of each of W = 1 or
+// 4 sequences (opp, seq and coef as in ProdRound).  Flags: bit j, sequence j's row
+// already holds its showdown; kFoldNone, no terminal (zero rows); kFoldLast, the
+// sequences end with it.
+constexpr int kFoldNone = 1 << 8, kFoldLast = 1 << 9;
+template <int W>
+struct alignas(16) FoldRound {
+  int opp[W];
+  int seq[W];
+  float coef[W];
+  int flags;
 };
 
 // Where the pieces of a precision-form table image lie, per player.
@@ -296,6 +298,7 @@ struct MixedOffsets {
     size_t own, opp, coef, b32, folds;
     int n_show, n_folds, fold_width;
   } p[2];
+  size_t cslot, hcard;
   bool by_columns;
 };
 
@@ -313,7 +316,9 @@ struct MixedTables {
   const int* col_opp[2] = {nullptr, nullptr};
   const double* col_coef[2] = {nullptr, nullptr};
   const float* belief32[2] = {nullptr, nullptr};  // [ld] each player's prior in FP32
-  const FoldRound* folds[2] = {nullptr, nullptr};
+  const unsigned short* card_slot = nullptr;  // [card_begin[n_cards]] the slots holding each card, ascending
+  const unsigned* hand_cards = nullptr;       // [n] the hand's cards a | b << 16
+  const void* folds[2] = {nullptr, nullptr};  // FoldRound<fold_width>[n_folds]
   int n_folds[2] = {0, 0};
   int fold_width[2] = {1, 1};  // sequences per fold round
 };
@@ -330,6 +335,7 @@ struct egt_game {
   egt::HostPlayer hp[2];
   std::vector<int> perm;  // slot -> caller hand index
   std::vector<int> slot_cards, slot_strength;  // cards [n * cph] and strengths [n] in slot order
+  std::vector<unsigned short> card_slot;       // the slots holding each card, ascending, card by card
   std::vector<double> hbelief[2];              // priors in slot order, [ld]
   egt::DPlayer dp[2];
   egt::DHands dh;

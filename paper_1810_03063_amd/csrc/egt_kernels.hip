@@ -911,7 +911,7 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 // scalar ones for three or four products; a wavefront per node left those of
 // ten actions to four rounds of loads: 33.8 us with the epilogue).  The path (root
 // first) and the item are wavefront-uniform loads, and every row of the item and
-// of the first kStep ancestors is in flight before the first product.  Bound by
+// of the first kPathStep ancestors is in flight before the first product.  Bound by
 // memory: 5938 sequences x 1081 hands, 102 MB, 21.8 -> 18.9 us with the root sums
 // (18.1 -> 11.0 in FP32, which read 8 bytes per lane); with the epilogue, 154 to
 // 206 MB, 32 -> 29.0 us (with the compiler's own 80 registers, 6 wavefronts per
@@ -919,6 +919,7 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 // ---------------------------------------------------------------------------
 struct DownArgs {
   const int* anc;
+  int anc_stride;
   const int2* items;  // first sequence, sequences of one node
   const void* QB;
   int n, ld, n_items;
@@ -932,7 +933,6 @@ struct DownArgs {
 template <class TS, int HP>
 __global__ __launch_bounds__(kPassThreads * kDownWaves, 7) void top_down_kernel(DownArgs a) {
   typedef TS VH __attribute__((ext_vector_type(HP)));
-  constexpr int kStep = 3;
   const TS* QB = (const TS*)a.QB;
   TS* q_out = (TS*)a.q_out;
   TS* comb_out = (TS*)a.comb_out;
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(kPassThreads * kDownWaves, 7) void top_down_kernel(
   const int2 item = a.items[pos - hb * a.n_items];
   const int s0 = item.x, rows = item.y;
   const size_t ld = a.ld, i0 = (size_t)s0 * ld + h;
-  const int* path = a.anc + (size_t)s0 * kMaxDepth;
+  const int* path = a.anc + (size_t)s0 * a.anc_stride;
   VH own[kDownRows], xp[kDownRows];
 #pragma unroll
   for (int u = 0; u < kDownRows; ++u)
@@ -961,19 +961,19 @@ __global__ __launch_bounds__(kPassThreads * kDownWaves, 7) void top_down_kernel(
       if (comb_out) xp[u] = *(const VH*)(x_prev + i0 + u * ld);
     }
   VH above = (VH)(TS)1;
-  for (int j = 0; j < kMaxDepth; j += kStep) {
-    VH f[kStep];
-    bool in[kStep];
+  for (int j = 0; j < a.anc_stride; j += kPathStep) {  // a multiple of kPathStep
+    VH f[kPathStep];
+    bool in[kPathStep];
 #pragma unroll
-    for (int u = 0; u < kStep; ++u) {
-      const int q = j + u < kMaxDepth ? path[j + u] : -1;  // s0 closes the path, -1 after it
+    for (int u = 0; u < kPathStep; ++u) {
+      const int q = path[j + u];  // s0 closes the path, -1 after it
       in[u] = q >= 0 && q != s0;
       if (in[u]) f[u] = *(const VH*)(QB + (size_t)q * ld + h);
     }
 #pragma unroll
-    for (int u = 0; u < kStep; ++u)
+    for (int u = 0; u < kPathStep; ++u)
       if (in[u]) above *= f[u];
-    if (!in[kStep - 1]) break;
+    if (!in[kPathStep - 1]) break;
   }
 #pragma unroll
   for (int u = 0; u < kDownRows; ++u)
@@ -995,6 +995,7 @@ __global__ __launch_bounds__(kPassThreads * kDownWaves, 7) void top_down_kernel(
 // actions, from the root down along the sequence's root-first path.
 struct UniformArgs {
   const int* anc;
+  int anc_stride;
   const int* seq_nact;
   int n, ld;
   double* out;
@@ -1004,9 +1005,9 @@ __global__ __launch_bounds__(kPassThreads) void uniform_kernel(UniformArgs a) {
   const int h = blockIdx.x * kPassThreads + threadIdx.x;
   const int s = blockIdx.y;
   if (h >= a.ld) return;
-  const int* path = a.anc + (size_t)s * kMaxDepth;
+  const int* path = a.anc + (size_t)s * a.anc_stride;
   double val = 1.0;
-  for (int j = 0; j < kMaxDepth && path[j] >= 0; ++j) val = val / (double)a.seq_nact[path[j]];
+  for (int j = 0; j < a.anc_stride && path[j] >= 0; ++j) val = val / (double)a.seq_nact[path[j]];
   a.out[(size_t)s * a.ld + h] = h < a.n ? val : 0.0;
 }
 
@@ -1212,6 +1213,7 @@ static hipError_t top_down(const egt_game* g, int player, const void* QB, void* 
   const DPlayer& P = g->dp[player];
   DownArgs a;
   a.anc = P.anc;
+  a.anc_stride = P.anc_stride;
   a.items = P.down;
   a.QB = QB;
   a.n = g->n;
@@ -1380,6 +1382,7 @@ hipError_t launch_top_down(const egt_game* g, int player, const void* QB, void* 
 hipError_t launch_uniform(const egt_game* g, int player, double* out, hipStream_t s) {
   UniformArgs a;
   a.anc = g->dp[player].anc;
+  a.anc_stride = g->dp[player].anc_stride;
   a.seq_nact = g->dp[player].seq_nact;
   a.n = g->n;
   a.ld = g->ld;

@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "egt_internal.h"
@@ -498,7 +499,8 @@ int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, Mixed
   const int kpad = g->ld;  // rows and columns padded like every vector
   std::vector<int> own[2], opp[2];
   std::vector<double> coef[2];
-  std::vector<FoldRound> folds[2];
+  std::vector<FoldRound<1>> folds1[2];
+  std::vector<FoldRound<4>> folds4[2];
   for (int p = 0; p < 2; ++p) {
     const HostPlayer& hp = g->hp[p];
     std::vector<std::vector<int>> by_folds;  // by_folds[k]: sequences with k fold terminals
@@ -524,24 +526,38 @@ int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, Mixed
     // would be more than four blocks per compute unit
     const size_t w = hp.n_seq > 4 * g->n_cu ? 4 : 1;
     off->p[p].fold_width = (int)w;
-    for (size_t nf = 0; nf < by_folds.size(); ++nf)
-      for (size_t i = 0; i < by_folds[nf].size(); i += w)
-        for (size_t k = 0; k < std::max<size_t>(nf, 1); ++k) {
-          FoldRound r{{-1, -1, -1, -1}, {-1, -1, -1, -1}, {0.0f, 0.0f, 0.0f, 0.0f}, nf ? 0 : -1, 0, k + 1 >= nf, 0};
-          for (size_t j = 0; j < w && i + j < by_folds[nf].size(); ++j) {
-            const int s = by_folds[nf][i + j];
-            r.seq[j] = s;
-            if (has_show[s]) r.add |= 1 << j;
-            size_t seen = 0;
-            for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t)
-              if (hp.term_kind[t] == 0 && seen++ == k) {
-                r.opp[j] = hp.term_opp[t];
-                r.coef[j] = (float)hp.term_coef[t];
-              }
+    auto deal = [&](auto& rounds, auto width) {
+      constexpr int W = decltype(width)::value;
+      for (size_t nf = 0; nf < by_folds.size(); ++nf)
+        for (size_t i = 0; i < by_folds[nf].size(); i += W)
+          for (size_t k = 0; k < std::max<size_t>(nf, 1); ++k) {
+            FoldRound<W> r{};
+            r.flags = (nf ? 0 : kFoldNone) | (k + 1 >= nf ? kFoldLast : 0);
+            for (int j = 0; j < W; ++j) {
+              r.opp[j] = r.seq[j] = -1;
+              if (i + j >= by_folds[nf].size()) continue;
+              const int s = by_folds[nf][i + j];
+              r.seq[j] = s;
+              if (has_show[s]) r.flags |= 1 << j;
+              size_t seen = 0;
+              for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t)
+                if (hp.term_kind[t] == 0 && seen++ == k) {
+                  r.opp[j] = hp.term_opp[t];
+                  r.coef[j] = (float)hp.term_coef[t];
+                }
+            }
+            rounds.push_back(r);
           }
-          folds[p].push_back(r);
-        }
+    };
+    if (w == 4)
+      deal(folds4[p], std::integral_constant<int, 4>());
+    else
+      deal(folds1[p], std::integral_constant<int, 1>());
   }
+  std::vector<unsigned> hand_cards(n);
+  for (int i = 0; i < n; ++i)
+    hand_cards[i] = (unsigned)g->slot_cards[(size_t)i * g->cph] |
+                    (g->cph == 2 ? (unsigned)g->slot_cards[(size_t)i * g->cph + 1] << 16 : 0u);
   // slot order: strength ascending; compatibility from the cards of the slots
   off->by_columns = takes_column_gemm(g);
   std::vector<unsigned short> W((size_t)kpad * kpad, 0);
@@ -574,10 +590,12 @@ int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, Mixed
     o.own = add(sizeof(int) * own[p].size());
     o.opp = add(sizeof(int) * opp[p].size());
     o.coef = add(sizeof(double) * coef[p].size());
-    o.folds = add(sizeof(FoldRound) * folds[p].size());
+    o.folds = add(sizeof(FoldRound<1>) * folds1[p].size() + sizeof(FoldRound<4>) * folds4[p].size());
     o.n_show = (int)own[p].size();
-    o.n_folds = (int)folds[p].size();
+    o.n_folds = (int)(folds1[p].size() + folds4[p].size());
   }
+  off->cslot = add(sizeof(unsigned short) * g->card_slot.size());
+  off->hcard = add(sizeof(unsigned) * hand_cards.size());
   img.assign(total, 0);
   auto put = [&](size_t at, const void* src, size_t bytes) {
     if (bytes) std::memcpy(img.data() + at, src, bytes);
@@ -589,8 +607,11 @@ int mixed_tables_image(const egt_game* g, std::vector<unsigned char>& img, Mixed
     put(o.own, own[p].data(), sizeof(int) * own[p].size());
     put(o.opp, opp[p].data(), sizeof(int) * opp[p].size());
     put(o.coef, coef[p].data(), sizeof(double) * coef[p].size());
-    put(o.folds, folds[p].data(), sizeof(FoldRound) * folds[p].size());
+    put(o.folds, folds1[p].data(), sizeof(FoldRound<1>) * folds1[p].size());
+    put(o.folds, folds4[p].data(), sizeof(FoldRound<4>) * folds4[p].size());
   }
+  put(off->cslot, g->card_slot.data(), sizeof(unsigned short) * g->card_slot.size());
+  put(off->hcard, hand_cards.data(), sizeof(unsigned) * hand_cards.size());
   return EGT_OK;
 }
 
@@ -606,10 +627,12 @@ static void point_mixed_tables(egt_game* g, const MixedOffsets& off, void* dev, 
     g->mx.col_opp[p] = (const int*)(base + o.opp);
     g->mx.col_coef[p] = (const double*)(base + o.coef);
     g->mx.belief32[p] = (const float*)(base + o.b32);
-    g->mx.folds[p] = (const FoldRound*)(base + o.folds);
+    g->mx.folds[p] = base + o.folds;
     g->mx.n_folds[p] = o.n_folds;
     g->mx.fold_width[p] = o.fold_width;
   }
+  g->mx.card_slot = (const unsigned short*)(base + off.cslot);
+  g->mx.hand_cards = (const unsigned*)(base + off.hcard);
   g->mx.owned = owned;
   g->mx.block = dev;
 }

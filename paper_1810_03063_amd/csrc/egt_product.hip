@@ -630,7 +630,9 @@ struct FoldArgs {
   DPlayer own;
   const double* b_opp;
   DHands H;
-  const FoldRound* rounds;
+  const unsigned short* card_slot;
+  const unsigned* hand_cards;
+  const void* rounds;  // FoldRound<W>
   int n_rounds;
   const float* v_opp;
   float* out;
@@ -677,14 +679,15 @@ __global__ __launch_bounds__(kGroupThreads) void fold_kernel(FoldArgs a) {
   for (int k = 0; k < HPT; ++k) {
     const int i = tid + k * kGroupThreads;
     bo[k] = i < n ? (float)a.b_opp[i] : 0.0f;
-    cards[k] = i < n ? a.H.hand_cards[i] : 0u;
+    cards[k] = i < n ? a.hand_cards[i] : 0u;
   }
   // rounds in contiguous ranges, whole items (a group of sequences' rounds, the
   // last marked) per block: a range starts behind a last round
   const int per = (a.n_rounds + (int)gridDim.x - 1) / (int)gridDim.x;
+  const FoldRound<W>* rounds = (const FoldRound<W>*)a.rounds;
   auto item_start = [&](int r) {
     r = min(r, a.n_rounds);
-    while (r > 0 && r < a.n_rounds && !a.rounds[r - 1].last) ++r;
+    while (r > 0 && r < a.n_rounds && !(rounds[r - 1].flags & kFoldLast)) ++r;
     return r;
   };
   int ri = item_start((int)blockIdx.x * per);
@@ -697,8 +700,8 @@ __global__ __launch_bounds__(kGroupThreads) void fold_kernel(FoldArgs a) {
     const int qlen = (len + 3) >> 2, lo = min((tid & 3) * qlen, len), hi = min(lo + qlen, len);
 #pragma unroll
     for (int j = 0; j < kQR / 2; ++j) {
-      const unsigned s0 = lo + 2 * j < hi ? a.H.card_slot[cb + lo + 2 * j] : 0u;
-      const unsigned s1 = lo + 2 * j + 1 < hi ? a.H.card_slot[cb + lo + 2 * j + 1] : 0u;
+      const unsigned s0 = lo + 2 * j < hi ? a.card_slot[cb + lo + 2 * j] : 0u;
+      const unsigned s1 = lo + 2 * j + 1 < hi ? a.card_slot[cb + lo + 2 * j + 1] : 0u;
       slots[j] = s0 | (s1 << 16);
     }
   }
@@ -706,8 +709,8 @@ __global__ __launch_bounds__(kGroupThreads) void fold_kernel(FoldArgs a) {
 #pragma unroll
   for (int k = 0; k < HPT; ++k) acc[k] = zero;
   for (; ri < rend; ++ri) {
-    const FoldRound rd = a.rounds[ri];  // uniform
-    if (rd.kind == 0) {
+    const FoldRound<W> rd = rounds[ri];  // uniform
+    if (!(rd.flags & kFoldNone)) {
       V r[HPT];
       V loc = zero;
       float v[W][HPT];
@@ -744,7 +747,7 @@ __global__ __launch_bounds__(kGroupThreads) void fold_kernel(FoldArgs a) {
             if (lo + j < hi) part = part + R[(slots[j / 2] >> (16 * (j & 1))) & 0xffffu];
           k = lo + kQR;
         }
-        for (; k < hi; ++k) part = part + R[a.H.card_slot[cb + k]];
+        for (; k < hi; ++k) part = part + R[a.card_slot[cb + k]];
         const V p0 = lanes_of<W>([&](int j) { return quad_float<0x00>(part.x[j]); });
         const V p1 = lanes_of<W>([&](int j) { return quad_float<0x55>(part.x[j]); });
         const V p2 = lanes_of<W>([&](int j) { return quad_float<0xaa>(part.x[j]); });
@@ -761,7 +764,7 @@ __global__ __launch_bounds__(kGroupThreads) void fold_kernel(FoldArgs a) {
       }
       if (ri + 1 < rend) __syncthreads();  // the next round rewrites R and C
     }
-    if (rd.last) {
+    if (rd.flags & kFoldLast) {
       float scale[HPT];
 #pragma unroll
       for (int k = 0; k < HPT; ++k) {
@@ -774,12 +777,12 @@ __global__ __launch_bounds__(kGroupThreads) void fold_kernel(FoldArgs a) {
 #pragma unroll
         for (int k = 0; k < HPT; ++k) {
           const int i = tid + k * kGroupThreads;
-          cur[j][k] = ((rd.add >> j) & 1) && rd.seq[j] >= 0 && i < n ? a.out[(size_t)rd.seq[j] * ld + i] : 0.0f;
+          cur[j][k] = ((rd.flags >> j) & 1) && rd.seq[j] >= 0 && i < n ? a.out[(size_t)rd.seq[j] * ld + i] : 0.0f;
         }
 #pragma unroll
       for (int j = 0; j < W; ++j) {
         if (rd.seq[j] < 0) continue;
-        const bool add = (rd.add >> j) & 1;
+        const bool add = (rd.flags >> j) & 1;
         float* out = a.out + (size_t)rd.seq[j] * ld;
 #pragma unroll
         for (int k = 0; k < HPT; ++k) {
@@ -948,6 +951,8 @@ hipError_t launch_gradient_fold_f32(const egt_game* g, int player, const float* 
   a.own = P;
   a.b_opp = g->dp[1 - player].belief;
   a.H = g->dh;
+  a.card_slot = g->mx.card_slot;
+  a.hand_cards = g->mx.hand_cards;
   a.rounds = g->mx.folds[player];
   a.n_rounds = g->mx.n_folds[player];
   a.v_opp = v_opp;
