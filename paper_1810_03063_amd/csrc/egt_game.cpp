@@ -14,7 +14,6 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
-#include <map>
 #include <memory>
 #include <numeric>
 #include <set>
@@ -275,20 +274,6 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
     for (int i = hp.level_begin[l]; i < hp.level_begin[l + 1]; ++i)
       hp.level_max_act[l] = std::max(hp.level_max_act[l], hp.node_nact[i]);
   }
-  // table image, sequence and node records
-  const FusedTabLayout L = fused_tab_layout(nn, ns);
-  hp.fused_tab.assign((size_t)L.bytes, 0);
-  std::vector<int> vslot(nn, -1);
-  for (size_t j = 0; j < hp.child.size(); ++j) vslot[hp.child[j]] = (int)j;
-  for (size_t r = 0; r < hp.roots.size(); ++r) vslot[hp.roots[r]] = (int)(hp.child.size() + r);
-  unsigned char* img = hp.fused_tab.data();
-  for (int i = 0; i < nn; ++i) {
-    const int rec[4] = {hp.node_first_seq[i], hp.node_nact[i], vslot[i], 0};
-    const double prm[4] = {hp.node_beta[i], 1.0 / hp.node_beta[i], hp.node_logn[i], 0.0};
-    std::memcpy(img + L.rec + 16 * (size_t)i, rec, sizeof(rec));
-    std::memcpy(img + L.prm + 32 * (size_t)i, prm, sizeof(prm));
-  }
-  std::memcpy(img + L.cbeg, hp.child_begin.data(), sizeof(int) * (size_t)(ns + 1));
   // a node's sequences in nearly equal parts of at most kDownRows
   hp.down.clear();
   for (int i = 0; i < nn; ++i) {
@@ -297,6 +282,29 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
       const int beg = na * k / parts;
       hp.down.push_back(make_int2(hp.node_first_seq[i] + beg, na * (k + 1) / parts - beg));
     }
+  }
+  return EGT_OK;
+}
+
+// The tables of the passes that the game runs: the level path's image, or the
+// single-launch passes' sequence and node records.
+void pass_tables(HostPlayer& hp, bool levels) {
+  const int nn = hp.n_nodes, ns = hp.n_seq;
+  std::vector<int> vslot(nn, -1);
+  for (size_t j = 0; j < hp.child.size(); ++j) vslot[hp.child[j]] = (int)j;
+  for (size_t r = 0; r < hp.roots.size(); ++r) vslot[hp.roots[r]] = (int)(hp.child.size() + r);
+  if (levels) {
+    const FusedTabLayout L = fused_tab_layout(nn, ns);
+    hp.fused_tab.assign((size_t)L.bytes, 0);
+    unsigned char* img = hp.fused_tab.data();
+    for (int i = 0; i < nn; ++i) {
+      const int rec[4] = {hp.node_first_seq[i], hp.node_nact[i], vslot[i], 0};
+      const double prm[4] = {hp.node_beta[i], 1.0 / hp.node_beta[i], hp.node_logn[i], 0.0};
+      std::memcpy(img + L.rec + 16 * (size_t)i, rec, sizeof(rec));
+      std::memcpy(img + L.prm + 32 * (size_t)i, prm, sizeof(prm));
+    }
+    std::memcpy(img + L.cbeg, hp.child_begin.data(), sizeof(int) * (size_t)(ns + 1));
+    return;
   }
   hp.seq_rec.resize(ns);
   hp.node_rec.resize(nn);
@@ -307,71 +315,103 @@ int finish_player(const Enumerator& en, int p, HostPlayer& hp, std::vector<int>&
       hp.seq_rec[s] = SeqRec{hp.seq_parent[s], hp.child_begin[s], hp.child_begin[s + 1] - hp.child_begin[s], vslot[i],
                              lev, hp.node_nact[i], {0, 0}};
   }
-  return EGT_OK;
+}
+
+// Terminal records of product_kernel, and its work items where a sequence has at
+// most two terminals.
+void product_terms(HostPlayer& hp) {
+  const int stride = std::max(1, hp.max_terms_per_seq);
+  hp.term_rec.assign((size_t)hp.n_seq * stride, TermRec{-1, -1, 0.0});
+  for (int s = 0; s < hp.n_seq; ++s)
+    for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t)
+      hp.term_rec[(size_t)s * stride + (t - hp.term_begin[s])] = TermRec{hp.term_opp[t], hp.term_kind[t], hp.term_coef[t]};
+  // work items for blocks that loop over sequences: two-terminal sequences
+  // whole, one-terminal sequences in pairs, empty sequences alone
+  hp.term_items.clear();
+  if (hp.max_terms_per_seq <= 2) {
+    const TermRec none{-1, -1, 0.0};
+    int pending = -1;
+    for (int s = 0; s < hp.n_seq; ++s) {
+      const int cnt = hp.term_begin[s + 1] - hp.term_begin[s];
+      const TermRec* r = &hp.term_rec[(size_t)s * stride];
+      if (cnt == 2) {
+        hp.term_items.push_back(TermItem{{r[0], r[1]}, {s, s}, {0, 0}});
+      } else if (cnt == 0) {
+        hp.term_items.push_back(TermItem{{none, none}, {s, -1}, {0, 0}});
+      } else if (pending < 0) {
+        pending = s;
+      } else {
+        hp.term_items.push_back(TermItem{{hp.term_rec[(size_t)pending * stride], r[0]}, {pending, s}, {0, 0}});
+        pending = -1;
+      }
+    }
+    if (pending >= 0)
+      hp.term_items.push_back(TermItem{{hp.term_rec[(size_t)pending * stride], none}, {pending, -1}, {0, 0}});
+  }
 }
 
 // Rounds of the paired product kernel for `blocks` blocks: sequences with the
 // same numbers of folds and showdowns are paired, a pair's rounds (its folds,
-// then its showdowns) go to one block, the most loaded pair first to the least
+// then its showdowns) go to one block, the most loaded pair first to a least
 // loaded block.  A fold round takes about half a showdown round's LDS traffic.
 void schedule_rounds(HostPlayer& hp, int blocks) {
-  struct Item {
-    std::vector<ProdRound> r;
-    int cost;
+  struct Pair {
+    int s[2], folds, shows, block;
+    int cost() const { return folds + 2 * shows; }
+    int rounds() const { return std::max(1, folds + shows); }
   };
-  std::vector<Item> items;
-  std::map<std::pair<int, int>, int> pending;  // (folds, showdowns) -> unpaired sequence
-  auto emit = [&](int s0, int s1) {
-    Item it;
-    it.cost = 0;
-    const int seq[2] = {s0, s1};
-    std::vector<int> t[2][2];  // [kind][slot]
-    for (int j = 0; j < 2; ++j)
-      if (seq[j] >= 0)
-        for (int q = hp.term_begin[seq[j]]; q < hp.term_begin[seq[j] + 1]; ++q) t[hp.term_kind[q]][j].push_back(q);
-    for (int kind = 0; kind < 2; ++kind)
-      for (size_t k = 0; k < t[kind][0].size(); ++k) {
-        ProdRound r{{-1, -1}, {s0, s1}, {0.0, 0.0}, kind, 0};
-        for (int j = 0; j < 2; ++j)
-          if (k < t[kind][j].size()) {
-            r.opp[j] = hp.term_opp[t[kind][j][k]];
-            r.coef[j] = hp.term_coef[t[kind][j][k]];
-          }
-        it.r.push_back(r);
-        it.cost += kind == 0 ? 1 : 2;
-      }
-    if (it.r.empty()) it.r.push_back(ProdRound{{-1, -1}, {s0, s1}, {0.0, 0.0}, -1, 0});
-    it.r.back().last = 1;
-    items.push_back(std::move(it));
-  };
+  const int stride = hp.max_terms_per_seq + 1;
+  std::vector<int> pending((size_t)stride * stride, -1);  // unpaired sequence of (folds, showdowns)
+  std::vector<Pair> pairs;
+  pairs.reserve(hp.n_seq / 2 + pending.size());
   for (int s = 0; s < hp.n_seq; ++s) {
-    std::pair<int, int> key{0, 0};
-    for (int q = hp.term_begin[s]; q < hp.term_begin[s + 1]; ++q) ++(hp.term_kind[q] == 0 ? key.first : key.second);
-    const auto at = pending.find(key);
-    if (at == pending.end()) {
-      pending[key] = s;
+    int shows = 0;
+    for (int q = hp.term_begin[s]; q < hp.term_begin[s + 1]; ++q) shows += hp.term_kind[q];
+    const int folds = hp.term_begin[s + 1] - hp.term_begin[s] - shows;
+    int& at = pending[(size_t)folds * stride + shows];
+    if (at < 0) {
+      at = s;
     } else {
-      emit(at->second, s);
-      pending.erase(at);
+      pairs.push_back(Pair{{at, s}, folds, shows, 0});
+      at = -1;
     }
   }
-  for (const auto& p : pending) emit(p.second, -1);
-  std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
-  blocks = std::max(1, std::min(blocks, (int)items.size()));
-  std::vector<std::vector<const Item*>> of(blocks);
-  std::set<std::pair<int, int>> load;  // (cost, block)
-  for (int b = 0; b < blocks; ++b) load.insert({0, b});
-  for (const Item& it : items) {
-    const std::pair<int, int> least = *load.begin();
-    load.erase(load.begin());
-    of[least.second].push_back(&it);
-    load.insert({least.first + it.cost, least.second});
+  for (int k = 0; k < stride * stride; ++k)
+    if (pending[k] >= 0) pairs.push_back(Pair{{pending[k], -1}, k / stride, k % stride, 0});
+  std::stable_sort(pairs.begin(), pairs.end(), [](const Pair& a, const Pair& b) { return a.cost() > b.cost(); });
+  blocks = std::max(1, std::min(blocks, (int)pairs.size()));
+  // blocks by load: a ring of lists, as a pair moves its block up by at most the first pair's cost
+  const int ring = (pairs.empty() ? 0 : pairs[0].cost()) + 1;
+  std::vector<std::vector<int>> at_load(ring);
+  for (int b = 0; b < blocks; ++b) at_load[0].push_back(b);
+  hp.round_begin.assign(blocks + 1, 0);
+  size_t load = 0, next = 0;
+  for (Pair& p : pairs) {
+    while (next == at_load[load % ring].size()) {
+      at_load[load % ring].clear();
+      ++load;
+      next = 0;
+    }
+    p.block = at_load[load % ring][next++];
+    at_load[(load + p.cost()) % ring].push_back(p.block);
+    hp.round_begin[p.block + 1] += p.rounds();
   }
-  hp.rounds.clear();
-  hp.round_begin.assign(1, 0);
-  for (const auto& list : of) {
-    for (const Item* it : list) hp.rounds.insert(hp.rounds.end(), it->r.begin(), it->r.end());
-    hp.round_begin.push_back((int)hp.rounds.size());
+  for (int b = 0; b < blocks; ++b) hp.round_begin[b + 1] += hp.round_begin[b];
+  hp.rounds.resize(hp.round_begin[blocks]);
+  std::vector<int> at(hp.round_begin.begin(), hp.round_begin.end() - 1);
+  for (const Pair& p : pairs) {
+    ProdRound* r = &hp.rounds[at[p.block]];
+    at[p.block] += p.rounds();
+    for (int k = 0; k < p.rounds(); ++k)
+      r[k] = ProdRound{{-1, -1}, {p.s[0], p.s[1]}, {0.0, 0.0}, p.folds + p.shows == 0 ? -1 : k >= p.folds, k + 1 == p.rounds()};
+    for (int j = 0; j < 2; ++j) {
+      int k[2] = {0, p.folds};  // the next round of each kind
+      for (int q = p.s[j] >= 0 ? hp.term_begin[p.s[j]] : 0; p.s[j] >= 0 && q < hp.term_begin[p.s[j] + 1]; ++q) {
+        ProdRound& to = r[k[hp.term_kind[q]]++];
+        to.opp[j] = hp.term_opp[q];
+        to.coef[j] = hp.term_coef[q];
+      }
+    }
   }
 }
 
@@ -404,7 +444,13 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   if (g->lds_per_cu < g->lds_per_block) g->lds_per_cu = g->lds_per_block;
   g->fused_passes = fits_fused(g);
   const int round_blocks = g->general ? 0 : paired_product_blocks(g, card_begin);
-  for (int p = 0; p < 2 && round_blocks > 0; ++p) schedule_rounds(g->hp[p], round_blocks);
+  for (HostPlayer& hp : g->hp) {
+    pass_tables(hp, !g->fused_passes);
+    if (round_blocks > 0)
+      schedule_rounds(hp, round_blocks);
+    else if (!g->general)
+      product_terms(hp);
+  }
   struct Piece {
     const void* src;
     size_t bytes;
@@ -422,18 +468,15 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   for (int p = 0; p < 2; ++p) {
     HostPlayer& hp = g->hp[p];
     po[p].belief = add(b[p].data(), b[p].size() * sizeof(double));
-    // the level path and the single-launch passes read tables of their own
-    const bool levels = !g->fused_passes;
-    po[p].ftab = add(hp.fused_tab.data(), levels ? hp.fused_tab.size() : 0);
+    po[p].ftab = add(hp.fused_tab.data(), hp.fused_tab.size());
     po[p].rounds = add(hp.rounds.data(), hp.rounds.size() * sizeof(ProdRound));
     po[p].rbeg = add(hp.round_begin.data(), hp.round_begin.size() * sizeof(int));
-    po[p].srec = add(hp.seq_rec.data(), levels ? 0 : hp.seq_rec.size() * sizeof(SeqRec));
-    po[p].nrec = add(hp.node_rec.data(), levels ? 0 : hp.node_rec.size() * sizeof(NodeRec));
-    const bool paired = !hp.rounds.empty();  // the other product kernel's records stay on the host
-    po[p].trec = add(hp.term_rec.data(), paired ? 0 : hp.term_rec.size() * sizeof(TermRec));
+    po[p].srec = add(hp.seq_rec.data(), hp.seq_rec.size() * sizeof(SeqRec));
+    po[p].nrec = add(hp.node_rec.data(), hp.node_rec.size() * sizeof(NodeRec));
+    po[p].trec = add(hp.term_rec.data(), hp.term_rec.size() * sizeof(TermRec));
     po[p].down = add(hp.down.data(), hp.down.size() * sizeof(int2));
     po[p].anc = add(hp.anc.data(), hp.anc.size() * sizeof(int));
-    po[p].titems = add(hp.term_items.data(), paired ? 0 : hp.term_items.size() * sizeof(TermItem));
+    po[p].titems = add(hp.term_items.data(), hp.term_items.size() * sizeof(TermItem));
     po[p].snact = add(hp.seq_nact.data(), hp.seq_nact.size() * sizeof(int));
     po[p].sptr = add(hp.sp_ptr.data(), hp.sp_ptr.size() * sizeof(int64_t));
     po[p].scol = add(hp.sp_col.data(), hp.sp_col.size() * sizeof(int));
@@ -555,34 +598,6 @@ int build_game_host(const egt_game_desc* d, egt_game** out) {
       }
       hp.term_begin[s + 1] = (int)hp.term_opp.size();
       hp.max_terms_per_seq = std::max(hp.max_terms_per_seq, (int)by[s].size());
-    }
-    const int stride = std::max(1, hp.max_terms_per_seq);
-    hp.term_rec.assign((size_t)hp.n_seq * stride, TermRec{-1, -1, 0.0});
-    for (int s = 0; s < hp.n_seq; ++s)
-      for (int t = hp.term_begin[s]; t < hp.term_begin[s + 1]; ++t)
-        hp.term_rec[(size_t)s * stride + (t - hp.term_begin[s])] = TermRec{hp.term_opp[t], hp.term_kind[t], hp.term_coef[t]};
-    // work items for blocks that loop over sequences: two-terminal sequences
-    // whole, one-terminal sequences in pairs, empty sequences alone
-    hp.term_items.clear();
-    if (hp.max_terms_per_seq <= 2) {
-      const TermRec none{-1, -1, 0.0};
-      int pending = -1;
-      for (int s = 0; s < hp.n_seq; ++s) {
-        const int cnt = hp.term_begin[s + 1] - hp.term_begin[s];
-        const TermRec* r = &hp.term_rec[(size_t)s * stride];
-        if (cnt == 2) {
-          hp.term_items.push_back(TermItem{{r[0], r[1]}, {s, s}, {0, 0}});
-        } else if (cnt == 0) {
-          hp.term_items.push_back(TermItem{{none, none}, {s, -1}, {0, 0}});
-        } else if (pending < 0) {
-          pending = s;
-        } else {
-          hp.term_items.push_back(TermItem{{hp.term_rec[(size_t)pending * stride], r[0]}, {pending, s}, {0, 0}});
-          pending = -1;
-        }
-      }
-      if (pending >= 0)
-        hp.term_items.push_back(TermItem{{hp.term_rec[(size_t)pending * stride], none}, {pending, -1}, {0, 0}});
     }
   }
   // enough 4-hand blocks to spread over the chip; 16-hand blocks for small hand
@@ -719,8 +734,6 @@ int build_general_host(const egt_general_desc* d, egt_game** out) {
     HostPlayer& hp = g->hp[p];
     hp.term_begin.assign(hp.n_seq + 1, 0);
     hp.max_terms_per_seq = 0;
-    hp.term_rec.assign((size_t)hp.n_seq, TermRec{-1, -1, 0.0});
-    hp.term_items.clear();
   }
   // payoff triples in library numbering; repeated pairs added in input order
   struct Trip {
