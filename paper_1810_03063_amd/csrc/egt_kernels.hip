@@ -8,7 +8,7 @@
 //    mu = 0 gives the best response;
 //  * the same steps one level per launch for large trees:
 //    bottom_up_leaf_pair_kernel (lowest level) or bottom_up_level_kernel
-//    (its one-hand-per-lane form), bottom_up_wide_kernel (levels of many nodes
+//    (its one-hand-per-lane form, for few nodes or unaligned rows), bottom_up_wide_kernel (levels of many nodes
 //    with children, a wavefront per node) or bottom_up_internal_kernel (of few,
 //    a wavefront per action, at most 8), top_down_kernel, and root_sums_kernel
 //    where no top-down pass takes the root sums along;
@@ -496,8 +496,8 @@ __global__ __launch_bounds__(kPassThreads) void bottom_up_level_kernel(PassSet a
 
 // The lowest level (no node has children) with two adjacent hands per lane:
 // one 16-byte access per gradient row (8 bytes in FP32), half the wavefronts.
-// Used when every row pointer is aligned to two elements; per hand the
-// arithmetic is the one above, and slots h >= n are not written.
+// Used for levels of many nodes when every row pointer is aligned to two elements;
+// per hand the arithmetic is the one above, and slots h >= n are not written.
 //
 // A wavefront's rows are all requested before the first is used, and only the
 // first kLeafRegs actions of a node live in registers (most nodes have two;
@@ -904,7 +904,8 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 // the sequence's path, multiplied from the root down, then the epilogue
 // comb = (1 - tau) x_prev + tau q.  Padding slots are written 0.
 //
-// One wavefront per (up to kDownRows sequences of a node, 64 x HP hands), HP the
+// One wavefront per (up to kDownRows sequences of a node, 64 x HP hands) where
+// there are many (top_down_launch), HP the
 // hands of a 16-byte access: the sequences of a node share the path above them,
 // so its product is formed once and every sequence costs its own row (a
 // wavefront per sequence spent its time on instructions, 149 vector and 117
@@ -920,7 +921,7 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 struct DownArgs {
   const int* anc;
   int anc_stride;
-  const int2* items;  // first sequence, sequences of one node
+  const int2* items;  // first sequence, sequences of one node; null: every sequence by itself
   const void* QB;
   int n, ld, n_items;
   void* q_out;
@@ -949,7 +950,7 @@ __global__ __launch_bounds__(kPassThreads * kDownWaves, 7) void top_down_kernel(
   const int hb = pos / a.n_items;
   const int h = HP * (hb * kPassThreads + (int)threadIdx.x);
   if (h >= a.ld) return;  // ld is a multiple of HP
-  const int2 item = a.items[pos - hb * a.n_items];
+  const int2 item = a.items ? a.items[pos - hb * a.n_items] : make_int2(pos - hb * a.n_items, 1);
   const int s0 = item.x, rows = item.y;
   const size_t ld = a.ld, i0 = (size_t)s0 * ld + h;
   const int* path = a.anc + (size_t)s0 * a.anc_stride;
@@ -1199,9 +1200,18 @@ static hipError_t fused_launch(const egt_game* g, const Pass* p, int count, cons
                     : fused_launch_hands<1, TG>(a, pairs, grid, lds, s);
 }
 
+// A wavefront for every sequence while that is at most 16 per compute unit: there
+// a part's rows one after the other take longer than their shared path saves
+// (whole pass, parts against sequences: 967 sequences x 105 hands, 4 per unit, 19.8
+// against 19.5 us; 520 x 1081, 18 per unit, 21.7 and 21.5; 5938 x 105, 23 per unit,
+// 29.3 both, in FP32 25.4 and 25.7; 1684 x 595, 33 per unit, 30.8 and 31.2).
 template <class TS, int HP>
-static hipError_t top_down_launch(const DownArgs& a, hipStream_t s) {
+static hipError_t top_down_launch(DownArgs a, int n_seq, int n_cu, hipStream_t s) {
   const int nbx = (a.ld / HP + kPassThreads - 1) / kPassThreads;
+  if ((int64_t)nbx * n_seq <= 16 * (int64_t)n_cu) {
+    a.items = nullptr;
+    a.n_items = n_seq;
+  }
   const dim3 grid((unsigned)(a.sums.count + (nbx * a.n_items + kDownWaves - 1) / kDownWaves));
   hipLaunchKernelGGL((top_down_kernel<TS, HP>), grid, dim3(kPassThreads, kDownWaves), 0, s, a);
   return hipGetLastError();
@@ -1231,10 +1241,10 @@ static hipError_t top_down(const egt_game* g, int player, const void* QB, void* 
   const uintptr_t bits = (uintptr_t)QB | (uintptr_t)q_out | (uintptr_t)x_prev | (uintptr_t)comb_out;
   auto fits = [&](int hands) { return g->ld % hands == 0 && bits % (hands * elem) == 0; };
   if (prec == kF32)
-    return fits(4)   ? top_down_launch<float, 4>(a, s)
-           : fits(2) ? top_down_launch<float, 2>(a, s)
-                     : top_down_launch<float, 1>(a, s);
-  return fits(2) ? top_down_launch<double, 2>(a, s) : top_down_launch<double, 1>(a, s);
+    return fits(4)   ? top_down_launch<float, 4>(a, P.n_seq, g->n_cu, s)
+           : fits(2) ? top_down_launch<float, 2>(a, P.n_seq, g->n_cu, s)
+                     : top_down_launch<float, 1>(a, P.n_seq, g->n_cu, s);
+  return fits(2) ? top_down_launch<double, 2>(a, P.n_seq, g->n_cu, s) : top_down_launch<double, 1>(a, P.n_seq, g->n_cu, s);
 }
 
 template <class TG>
@@ -1297,7 +1307,17 @@ static hipError_t passes_launch(const egt_game* g, const Pass* p, int count, con
     }
     if (total == 0) continue;
     cur.level = l;
-    if (l == 0 && pair) {
+    // Two hands per lane from 16 (node, 128 hands) wavefronts per compute unit on.
+    // Below, a pass with exponentials is faster with one hand per lane, whose
+    // actions all stay in registers (whole pass, two against one: 315 nodes x 105
+    // hands 21.9 against 19.8 us, in FP32 19.2 and 18.0; 168 nodes x 1081 hands,
+    // 6 per unit, 23.1 and 21.7, FP32 19.6 and 19.2; 949 nodes x 595 hands, 19 per
+    // unit, 35.0 and 33.8, FP32 28.0 and 28.3; 1777 nodes x 1081 hands, 62 per unit,
+    // 69.4 and 69.2, FP32 52.3 and 54.4).  Best responses only load and compare: two
+    // hands are the faster form at every size (15.1 against 17.3 us at the first).
+    bool smooth = true;
+    for (int k = 0; k < count; ++k) smooth = smooth && a.t[k].mu > 0.0;
+    if (l == 0 && pair && (!smooth || (size_t)bx_pair * total >= 16 * (size_t)g->n_cu)) {
       int more = 0;  // actions beyond the registers
       for (int k = 0; k < count; ++k)
         if (a.t[k].n_levels > 0) more = std::max(more, g->hp[p[k].player].level_max_act[0] - kLeafRegs);
