@@ -359,6 +359,7 @@ __global__ __launch_bounds__(256) void show_gemm_tiled_kernel(GemmArgs a) {
 // kc = hand / 8: writes (consecutive kc of a column) and reads (16 columns of a
 // kc) both spread over the banks.
 constexpr int kColsBlock = 32, kColsWaves = 12;
+constexpr int kColsMinColumns = 256;
 constexpr int kColsMaxLd = 1216;  // the reaches of a block fit LDS
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
@@ -481,22 +482,20 @@ __global__ __launch_bounds__(64 * kColsWaves, 3) void show_gemm_cols_kernel(Gemm
 
 }  // namespace
 
-// Tiles of the K-split form.
-static int64_t k_split_tiles(const egt_game* g, int64_t columns) { return (columns + kTile - 1) / kTile * (g->ld / kTile); }
-
-// While the K-split form's tiles are one per compute unit, they are done at once and
-// it is the faster form; a second round of them takes longer than the column
-// blocks, however many hands make the tiles (whole product, columns against
-// K-split: 351 hands 187 tiles 11.5 against 10.1 us, 396 tiles 13.5 and 14.6; 465
-// hands 255 tiles 12.8 and 11.0; 595 hands 209 tiles 14.3 and 11.9, 323 tiles 14.9
-// and 16.7; 741 hands 144 tiles 15.5 and 13.1, 264 tiles 16.0 and 19.0; 1081 hands
+// Column blocks wherever the tiled form would do (same bits: each element adds its
+// hi and its lo products in the same order), and from kColsMinColumns on once the K-split
+// form's tiles are more than one per compute unit; up to there those are all done
+// at once and it is the faster form (whole product, columns against K-split: 595
+// hands 209 tiles 14.3 against 11.9 us, 741 hands 264 tiles 16.0 and 19.0; 1081 hands
 // 204 tiles 18.1 and 15.8, 374 tiles 19.0 and 26.1).
 bool takes_column_gemm(const egt_game* g) {
-  auto second_round = [&](int p) {
+  auto fits = [&](int p) {
     const std::vector<int>& kinds = g->hp[p].term_kind;
-    return k_split_tiles(g, std::count(kinds.begin(), kinds.end(), 1)) > g->n_cu;
+    const int64_t columns = std::count(kinds.begin(), kinds.end(), 1);
+    const int64_t tiles = (columns + kTile - 1) / kTile * (g->ld / kTile);
+    return columns >= kTiledMinColumns || (columns >= kColsMinColumns && tiles > g->n_cu);
   };
-  return g->ld <= kColsMaxLd && second_round(0) && second_round(1);
+  return g->ld <= kColsMaxLd && fits(0) && fits(1);
 }
 
 // W (BF16 bits; in the column-block GEMM's operand order when both players take
@@ -707,7 +706,7 @@ hipError_t launch_show_gemm(const egt_game* g, int player, const float* v_opp, f
       hipLaunchKernelGGL(show_gemm_cols_kernel<3>, grid, block, lds, s, a, parts_of(3));
     return hipGetLastError();
   }
-  if (a.L >= kTiledMinColumns && k_split_tiles(g, a.L) > g->n_cu) {
+  if (a.L >= kTiledMinColumns) {
     // enough columns for operand reuse to pay: the tiled form
     const unsigned tiles = (unsigned)(((a.L + kTN - 1) / kTN) * ((g->ld + kTM - 1) / kTM));
     hipLaunchKernelGGL(show_gemm_tiled_kernel, dim3(tiles), dim3(256), tiled_lds_bytes(g->ld), s, a);

@@ -22,18 +22,15 @@ GAMES = {
     "three_pairs_16_hands": (tree(5, QUARTERS, 1), 76, 0, 16, 0),
     "four_hands": (tree(5, SIZES, 1), 109, 0, 4, 0),
     "five_pairs": (tree(8, SIZES, 2), 520, 0, 4, 0),
-    "six_pairs": (tree(8, QUARTERS, 3), 808, 1, 0, 0),
-    "105h_columns": (tree(5, SEVEN, 4), 5938, 1, 0, 1),  # 496 tiles of 32 columns x 32 hands
-    "351h_columns": (tree(8, QUARTERS, 4), 1684, 1, 0, 1),  # 396
+    "six_pairs": (tree(8, QUARTERS, 3), 808, 1, 0, 1),
     "595h_209_tiles": (tree(10, SIZES, 2), 520, 0, 0, 0),
-    "595h_323_tiles": (tree(10, QUARTERS, 3), 808, 1, 0, 1),
     "741h_264_tiles": (tree(11, SIZES, 2), 520, 0, 0, 1),
     "1081h_three_pairs": (tree(13, QUARTERS, 2), 286, 0, 4, 0),
     "1081h_five_pairs": (tree(13, SIZES, 2), 520, 0, 0, 1),
     "1081h_columns": (tree(13, SEVEN, 3), 3001, 1, 0, 1),
     "1176h": (tree(13, QUARTERS, 3, n_board=3), 808, 1, 0, 1),
     "1300h": (lambda: many_hands(1300, 3), 2524, 0, 0, 0),
-    "one_card_few": (lambda: one_card(60), None, 1, 0, 0),
+    "one_card_few": (lambda: one_card(60), None, 1, 0, 1),
 }
 
 
