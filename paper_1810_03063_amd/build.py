@@ -38,13 +38,14 @@ FLAGS = [
 ]
 
 
-# The fused passes hold the constants of exp, log and divisions in registers for
-# their whole level loop when the compiler hoists them there (the smoothed best
-# response: 100 registers and two blocks per compute unit instead of 64 and four).
+# sbr_fused_kernel alone wants the switch: without it the compiler hoists the constants
+# of exp, log and divisions out of the level loop, and the kernel spills (223
+# sequences x 1081 hands, both responses with values: 48.3 us without, 28.5 with). The other
+# kernels of the file keep their registers and times either way (launch-per-level
+# passes 146.3 and 146.8 us, FP32 108.1 and 107.8); the products and the regret update
+# measured the same without it, so their files are built plainly.
 SOURCE_FLAGS = {
     "egt_kernels.hip": ["-mllvm", "-disable-machine-licm"],
-    "egt_cfr.hip": ["-mllvm", "-disable-machine-licm"],
-    "egt_product.hip": ["-mllvm", "-disable-machine-licm"],
 }
 
 
