@@ -41,7 +41,7 @@ namespace {
 constexpr int kLanes = 64;
 
 struct RegretArgs {
-  const void* tab;  // the player's table image (FusedTabLayout)
+  const void* tab;  // the player's table image (LevelTabLayout)
   int n_nodes, n_seq;
   int node0;        // first node of the level
   int n, ld;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kLanes) void regret_level_kernel(RegretArgs a) {
   if (h >= a.n) return;
   const int v = a.node0 + (int)blockIdx.y;
   const size_t ld = a.ld;
-  const FusedTabLayout L = fused_tab_layout(a.n_nodes, a.n_seq);
+  const LevelTabLayout L = level_tab_layout(a.n_nodes, a.n_seq);
   const unsigned char* tab = (const unsigned char*)a.tab;
   const int4 r = ((const int4*)(tab + L.rec))[v];
   const int* cbeg = (const int*)(tab + L.cbeg);
@@ -361,7 +361,7 @@ int cfr_update(egt_cfr* c, int p, double tau, hipStream_t s) {
   EGT_HIP(launch_axpby(vec_elems_of(g, p), 1.0 - tau, c->AVG[p], tau, c->X[p], c->AVG[p], s));
   const unsigned bx = (unsigned)((g->n + kLanes - 1) / kLanes);
   RegretArgs a;
-  a.tab = g->dp[p].fused_tab;
+  a.tab = g->dp[p].level_tab;
   a.n_nodes = hp.n_nodes;
   a.n_seq = hp.n_seq;
   a.n = g->n;

@@ -294,9 +294,9 @@ void pass_tables(HostPlayer& hp, bool levels) {
   for (size_t j = 0; j < hp.child.size(); ++j) vslot[hp.child[j]] = (int)j;
   for (size_t r = 0; r < hp.roots.size(); ++r) vslot[hp.roots[r]] = (int)(hp.child.size() + r);
   if (levels) {
-    const FusedTabLayout L = fused_tab_layout(nn, ns);
-    hp.fused_tab.assign((size_t)L.bytes, 0);
-    unsigned char* img = hp.fused_tab.data();
+    const LevelTabLayout L = level_tab_layout(nn, ns);
+    hp.level_tab.assign((size_t)L.bytes, 0);
+    unsigned char* img = hp.level_tab.data();
     for (int i = 0; i < nn; ++i) {
       const int rec[4] = {hp.node_first_seq[i], hp.node_nact[i], vslot[i], 0};
       const double prm[4] = {hp.node_beta[i], 1.0 / hp.node_beta[i], hp.node_logn[i], 0.0};
@@ -468,7 +468,7 @@ int finish_image(egt_game* g, const std::vector<int>& card_begin, const std::vec
   for (int p = 0; p < 2; ++p) {
     HostPlayer& hp = g->hp[p];
     po[p].belief = add(b[p].data(), b[p].size() * sizeof(double));
-    po[p].ftab = add(hp.fused_tab.data(), hp.fused_tab.size());
+    po[p].ltab = add(hp.level_tab.data(), hp.level_tab.size());
     po[p].rounds = add(hp.rounds.data(), hp.rounds.size() * sizeof(ProdRound));
     po[p].rbeg = add(hp.round_begin.data(), hp.round_begin.size() * sizeof(int));
     po[p].srec = add(hp.seq_rec.data(), hp.seq_rec.size() * sizeof(SeqRec));
@@ -815,7 +815,7 @@ int upload_game(egt_game* g, void* dev, bool owned, hipStream_t stream) {
     dp.n_roots = (int)hp.roots.size();
     dp.belief = (const double*)at(po[p].belief);
     const bool levels = !g->fused_passes;
-    dp.fused_tab = levels ? at(po[p].ftab) : nullptr;
+    dp.level_tab = levels ? at(po[p].ltab) : nullptr;
     dp.n_round_blocks = hp.rounds.empty() ? 0 : (int)hp.round_begin.size() - 1;
     dp.rounds = hp.rounds.empty() ? nullptr : (const ProdRound*)at(po[p].rounds);
     dp.round_begin = (const int*)at(po[p].rbeg);

@@ -40,11 +40,11 @@ struct NodeRec {
 // A node's value slot is its position in the child CSR; the r-th root node
 // takes slot C + r (C = number of non-root nodes), so a sequence's children
 // occupy the contiguous slots [cbeg[s], cbeg[s + 1]).
-struct FusedTabLayout {
+struct LevelTabLayout {
   int rec, prm, cbeg, bytes;
 };
-__host__ __device__ inline FusedTabLayout fused_tab_layout(int n_nodes, int n_seq) {
-  FusedTabLayout L;
+__host__ __device__ inline LevelTabLayout level_tab_layout(int n_nodes, int n_seq) {
+  LevelTabLayout L;
   L.rec = 0;
   L.prm = 16 * n_nodes;
   L.cbeg = 48 * n_nodes;
@@ -110,7 +110,7 @@ struct DPlayer {
   int n_nodes;
   int n_roots;
   const double* belief;        // [ld] this player's prior in slot order, 0 in the padding
-  const void* fused_tab;       // the table image (FusedTabLayout), in games of the level path
+  const void* level_tab;       // the table image (LevelTabLayout), in games of the level path
   const SeqRec* seq_rec;       // [n_seq], in games of the single-launch passes
   const NodeRec* node_rec;     // [n_nodes], the same
   const int2* down;            // [n_down] the top-down pass's work: {first sequence, sequences} of one node
@@ -169,7 +169,7 @@ struct TreePass {
   const void* gB;
   double cB;
   double mu;
-  double* V;       // node values by value slot (FusedTabLayout): always FP64
+  double* V;       // node values by value slot (LevelTabLayout): always FP64
   double* VB;      // dual pass: also the best response's node values (the level path's lowest level, or the
                    // whole single-launch pass), or null
   void* QB;        // q_bar in the launch's precision
@@ -234,7 +234,7 @@ struct HostPlayer {
   std::vector<int> term_begin, term_opp, term_kind;
   std::vector<double> term_coef;
   std::vector<int> roots;
-  std::vector<unsigned char> fused_tab;  // table image (FusedTabLayout)
+  std::vector<unsigned char> level_tab;  // table image (LevelTabLayout)
   std::vector<SeqRec> seq_rec;
   std::vector<NodeRec> node_rec;
   std::vector<TermRec> term_rec;         // [n_seq][max(1, max_terms_per_seq)]
@@ -260,7 +260,7 @@ struct DeviceBlock {  // one device allocation holding many tables
 // Offsets of every table in a game's upload image.
 struct GameOffsets {
   struct Player {
-    size_t belief, ftab, trec, anc, down, titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
+    size_t belief, ltab, trec, anc, down, titems, snact, sptr, scol, sval, srec, nrec, rounds, rbeg;
   } p[2];
   size_t cbeg, htab, hpos, cslot;
 };
@@ -348,7 +348,7 @@ struct egt_game {
   int device = 0;
   double max_beta = 0;
   bool general = false;       // a general game (egt_build_general_game): CSR products, one live slot
-  bool fused_passes = false;  // both treeplexes' tables fit one block's LDS: single-launch passes
+  bool fused_passes = false;  // small trees (fits_fused): single-launch passes
   int fused_hands = 4;        // hands per block of the single-launch pass (4 or 16; 1 in a general game)
 };
 

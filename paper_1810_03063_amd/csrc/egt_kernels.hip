@@ -1,6 +1,6 @@
 // HIP kernels of the EGT hot path for gfx950 (CDNA4, 64-lane wavefronts).
 //
-//  * sbr_fused_kernel  : for trees whose tables fit in LDS, a whole smoothed
+//  * sbr_fused_kernel  : for small trees (fits_fused), a whole smoothed
 //    best response (Section 4, Eq. 4 and the leaf / internal-simplex
 //    derivation) in one launch: bottom-up over every level, root-value
 //    partial sums, then the top-down rebuild q_i = q_{p_j} q_bar_i with the
@@ -118,7 +118,7 @@ __device__ inline double lin2(double cA, double a, double cB, double b) { return
 // ---------------------------------------------------------------------------
 
 // ---------------------------------------------------------------------------
-// Fused pass for trees that fit in LDS: block = (tree k, HB hands).
+// Fused pass for small trees (fits_fused): block = (tree k, HB hands).
 //
 // A launch moves a few MB; its time is the chain of dependent steps of each
 // level and the instructions around them: index arithmetic, loops over a node's
@@ -443,8 +443,8 @@ __global__ __launch_bounds__(kPassThreads) void bottom_up_level_kernel(PassSet a
   if (h >= a.n) return;
   const size_t ld = a.ld;
   const int v = t.level_begin[a.level] + y;
-  const FusedTabLayout L = fused_tab_layout(t.P.n_nodes, t.P.n_seq);
-  const unsigned char* tab = (const unsigned char*)t.P.fused_tab;
+  const LevelTabLayout L = level_tab_layout(t.P.n_nodes, t.P.n_seq);
+  const unsigned char* tab = (const unsigned char*)t.P.level_tab;
   const int4 r = ((const int4*)(tab + L.rec))[v];
   const double2 p0 = ((const double2*)(tab + L.prm))[2 * v], p1 = ((const double2*)(tab + L.prm))[2 * v + 1];
   const int* cbeg = (const int*)(tab + L.cbeg);
@@ -536,8 +536,8 @@ __global__ __launch_bounds__(kPassThreads, 8) void bottom_up_leaf_pair_kernel(Pa
   const bool both = h + 1 < a.n;
   const size_t ld = a.ld;
   const int v = t.level_begin[a.level] + y;
-  const FusedTabLayout L = fused_tab_layout(t.P.n_nodes, t.P.n_seq);
-  const unsigned char* tab = (const unsigned char*)t.P.fused_tab;
+  const LevelTabLayout L = level_tab_layout(t.P.n_nodes, t.P.n_seq);
+  const unsigned char* tab = (const unsigned char*)t.P.level_tab;
   const int4 r = ((const int4*)(tab + L.rec))[v];
   const double2 p0 = ((const double2*)(tab + L.prm))[2 * v], p1 = ((const double2*)(tab + L.prm))[2 * v + 1];
   const int s0 = r.x, na = r.y;
@@ -640,8 +640,8 @@ __global__ __launch_bounds__(kPassThreads * kInternalWaves) void bottom_up_inter
   const int h = blockIdx.x * kPassThreads + lane;
   const size_t ld = a.ld;
   const int v = t.level_begin[a.level] + y;
-  const FusedTabLayout L = fused_tab_layout(t.P.n_nodes, t.P.n_seq);
-  const unsigned char* tab = (const unsigned char*)t.P.fused_tab;
+  const LevelTabLayout L = level_tab_layout(t.P.n_nodes, t.P.n_seq);
+  const unsigned char* tab = (const unsigned char*)t.P.level_tab;
   const int4 r = ((const int4*)(tab + L.rec))[v];
   const double2 p0 = ((const double2*)(tab + L.prm))[2 * v], p1 = ((const double2*)(tab + L.prm))[2 * v + 1];
   const int* cbeg = (const int*)(tab + L.cbeg);
@@ -727,8 +727,8 @@ __global__ __launch_bounds__(kPassThreads, HP == 2 ? 4 : 7) void bottom_up_wide_
   const bool both = HP == 2 && h + 1 < a.n;
   const size_t ld = a.ld;
   const int v = t.level_begin[a.level] + y;
-  const FusedTabLayout L = fused_tab_layout(t.P.n_nodes, t.P.n_seq);
-  const unsigned char* tab = (const unsigned char*)t.P.fused_tab;
+  const LevelTabLayout L = level_tab_layout(t.P.n_nodes, t.P.n_seq);
+  const unsigned char* tab = (const unsigned char*)t.P.level_tab;
   const int4 r = ((const int4*)(tab + L.rec))[v];
   const double2 p0 = ((const double2*)(tab + L.prm))[2 * v], p1 = ((const double2*)(tab + L.prm))[2 * v + 1];
   const int s0 = r.x, na = r.y;
@@ -904,11 +904,10 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial
 // the sequence's path, multiplied from the root down, then the epilogue
 // comb = (1 - tau) x_prev + tau q.  Padding slots are written 0.
 //
-// One wavefront per (up to kDownRows sequences of a node, 64 x HP hands) where
-// there are many (top_down_launch), HP the
+// One wavefront per (up to kDownRows sequences of a node, 64 x HP hands), HP the
 // hands of a 16-byte access: the sequences of a node share the path above them,
-// so its product is formed once and every sequence costs its own row (a
-// wavefront per sequence spent its time on instructions, 149 vector and 117
+// so its product is formed once and every sequence costs its own row (on a large
+// tree, a wavefront per sequence spent its time on instructions, 149 vector and 117
 // scalar ones for three or four products; a wavefront per node left those of
 // ten actions to four rounds of loads: 33.8 us with the epilogue).  The path (root
 // first) and the item are wavefront-uniform loads, and every row of the item and

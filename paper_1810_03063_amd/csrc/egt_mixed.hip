@@ -171,7 +171,8 @@ __global__ __launch_bounds__(64 * kKWaves) void show_gemm_kernel(GemmArgs a) {
   }
 }
 
-// Many showdown columns (large trees): a tiled GEMM with operand reuse.
+// Many showdown columns where the column-block form below is left out (more than
+// kColsMaxLd hands, or a player with fewer columns): a tiled GEMM with operand reuse.
 // Block = 128 output hands x 64 columns, four waves, wave w owning rows
 // 32 w .. 32 w + 31 of the tile as two 32 x 32 MFMA tiles.  K (the opponent's
 // hands) advances in steps of kTK = 32 (ld is a multiple of 32): the block
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(256) void show_gemm_tiled_kernel(GemmArgs a) {
 // stored that way: 1 KB contiguous per 16 hands x 32), two steps ahead in
 // registers, the reaches from LDS.  MT is the smallest for which a block per
 // compute unit is enough (3958 columns x 1088 hands: MT = 3, 248 blocks).
-// That product: 51.0 -> 28.9 us, of which 13 in the contraction (8.3 at the MFMA
+// That product: 51.0 -> 28 us, of which 13 in the contraction (8.3 at the MFMA
 // peak) and 5 forming the reaches.
 // Operand layouts of v_mfma_f32_16x16x32_bf16 (lane l, element e < 8):
 //   A[l % 16][8 (l / 16) + e], B[8 (l / 16) + e][l % 16];

@@ -407,18 +407,21 @@ __global__ __launch_bounds__(2 * kGroupThreads, MINW) void product_kernel(ProdAr
 // round forms only the totals.  The card lists are gathered from the strength
 // order (a thread's quarter of a list, at most kQR slots, sits in registers as
 // indices), so nothing is scattered.  Rounds are dealt to the blocks at build
-// (ProdRound), three blocks a compute unit.  With more than two hands per thread
+// (ProdRound), a compute unit holding as many blocks as its LDS lets in, at most four
+// up to 512 hands and three above.  With more than two hands per thread
 // the evaluation deals them strided over the block, although the scan takes
 // them contiguous: neighbouring lanes then read neighbouring slots of R (fewer
 // bank conflicts) and store whole lines of the row, and a fold reads its reach
-// back from R, which it leaves as it was (1081 hands, contiguous against
-// strided: 5938 sequences 43.2 -> 39.5 us, 1684 sequences 19.4 -> 17.3).
-// 5938 sequences: 1081 hands 51.9 -> 39.5 us, 595 hands 40.8 -> 29.7, 351 hands
-// 31.4 -> 19.3, 105 hands 24.5 -> 14.6.  LDS and VALU are each busy a third of
-// the time (counters), the rest is the latency of a round's chain between
-// barriers at 12 wavefronts per compute unit, which its LDS and registers allow
-// (16 wavefronts, two blocks of 512 threads with half the hands each: 45.3 us;
-// 24 of them spill: 57).
+// back from R, which it leaves as it was (1081 hands, strided instead of
+// contiguous: 5938 sequences 3.7 us less, 1684 sequences 2.1).
+// 5938 sequences, one player's product repeated, product_kernel against this one:
+// 1081 hands 53.0 -> 40.2 us (player 2's 52.2 -> 38.7; the two in turn, each behind the
+// other's vectors, 44 each), 595 hands 41.3 -> 30.2, 351 hands 32.1 -> 19.6, 105 hands
+// 24.8 -> 14.6.  LDS and VALU are each busy a third of the time (counters at 1081
+// hands), the rest is the latency of a round's chain between barriers at, for five
+// hands per thread, 12 wavefronts per compute unit, which its LDS and registers allow
+// (16 wavefronts, two blocks of 512 threads with half the hands each, took 5.8 us
+// more; 24 of them spill and took 17 more).
 // Every sum is the one product_kernel takes, in its order.
 struct RoundArgs {
   DPlayer own;
